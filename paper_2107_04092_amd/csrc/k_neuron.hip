@@ -296,117 +296,219 @@ __global__ __launch_bounds__(NB) void k_neuron(NeuronArgs a, CompactArgs lst)
 // kSmallBlock) in registers from the first step to the last. Each step:
 // (1) the neuron update of every neuron (the same arithmetic as k_neuron;
 // from the second step on the input is the LDS accumulator, exact like the
-// fixed-point partial sums), fire and transmit masks, and the spike list in
-// ascending order into ring slot t mod D; (3) delivery of ring slot
-// (t-D+1) mod D, a wave per transmitted row, lanes over its targets, 64-bit
-// fixed-point LDS atomics. At the end the state goes back to the arrays and
-// the accumulator becomes partial sum 0, where the next neuron update (of
-// either path) reads it.
+// fixed-point partial sums), which clears the accumulator as it reads it;
+// the fire mask of every 64 neurons and its spike count go to LDS; (3)
+// delivery of the spikes of step t-D+1, 64-bit fixed-point LDS atomics. At
+// the end the state goes back to the arrays and the accumulator becomes
+// partial sum 0, where the next neuron update (of either path) reads it.
+//
+// One CU runs everything, so a step is bound by the chain from the neuron
+// update to the accumulator, and two barriers are all it waits for: the
+// spikes before each mask word come from a wave scan that every wave makes
+// for itself; with D = 1 a wave finds the source of the q-th spike in the
+// masks (kth_spike), so the list written to the ring is never read back (a
+// store and a load through L2, about 1 us); with D > 1 the ring's list is
+// older than the step and is loaded before the neuron update. A spike's row
+// is shared by several waves when there are fewer spikes than waves, so a
+// row of a few hundred targets is one round of loads. Launches of several
+// steps stage the row pointers in LDS (b.lds_rows), which takes their load
+// out of every step's chain; one step reads them where they are.
+// Measured per step: 4,000 CUBA neurons 4.25 -> 2.26 us, 1,000 LIF
+// neurons 1.9 -> 1.04 us (one thread scanning the counts, the list read
+// back and four barriers before).
 
-template <int M, int H>
+// The source of spike q (0-based, q below the total) of the step: word is
+// the mask word holding it, found from the exclusive prefix counts `excl` of
+// the words (lane w: word w; words <= 64).
+__device__ __forceinline__ int kth_spike(const uint64_t *masks, int excl, int cnt, int q, int lane)
+{
+    const int word = __ffsll((long long)ballot64(excl <= q && q < excl + cnt)) - 1;
+    const int w = max(word, 0);
+    const int r = q - __builtin_amdgcn_readlane(excl, w);
+    const uint64_t m = masks[w];
+    const uint64_t hit = ballot64(((m >> lane) & 1ull) &&
+                                  (int)__popcll(m & ((1ull << lane) - 1ull)) == r);
+    return w * kWave + max(__ffsll((long long)hit) - 1, 0);
+}
+
+template <int M, int H, int R>
 __global__ __launch_bounds__(kSmallBlock) void k_small_steps(NeuronArgs a, SmallArgs b)
 {
     constexpr int NWV = kSmallBlock / kWave;
-    extern __shared__ long long acc[];  // nacc * n
-    __shared__ int s_cnt[kSmallRounds * NWV];
-    __shared__ int s_total;
+    constexpr int NWORD = R * NWV;       // mask words
+    constexpr int NP = R * kSmallBlock;  // accumulators per input, padded: every lane has one
+    constexpr int NACC = M == 1 ? 2 : 1;
+    static_assert(NWORD <= kWave, "one mask word per lane");
+    extern __shared__ long long acc[];  // NACC * NP, then (b.lds_rows) n + 1 row pointers
+    __shared__ uint64_t s_m[NWORD];
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     const int n = a.n;
-    const int rounds = (n + kSmallBlock - 1) / kSmallBlock;  // <= kSmallRounds
-    const int span = b.nacc * n;
-    const StepClock ck = *a.clk;
+    int32_t *rp = reinterpret_cast<int32_t *>(acc + NACC * NP);
+    const StepClock ck = load_clock(a.clk);
+    const bool d1 = b.delay == 1;
     long long events = 0, spikes = 0;
-    NState st[kSmallRounds];
+    NState st[R];
+    float ae0[R], ai0[R];  // the input of the first step
 #pragma unroll
-    for (int r = 0; r < kSmallRounds; ++r) {
+    for (int r = 0; r < R; ++r) {
         const int i = r * kSmallBlock + tid;
-        if (r < rounds && i < n) nstate_load<M, H>(a, i, st[r]);
+        const int ic = min(i, n - 1);
+        nstate_load<M, H>(a, ic, st[r]);
+        ae0[r] = ai0[r] = 0.f;
+        if (M != 2) {
+            const float fe = a.ain[ic], fi = M == 1 ? a.ain[n + ic] : 0.f;
+            long long se = a.apart[ic], si = M == 1 ? a.apart[n + ic] : 0;
+            for (int c = 1; c < ck.n_parts; ++c) {
+                se += a.apart[c * a.part_stride + ic];
+                if (M == 1) si += a.apart[c * a.part_stride + n + ic];
+            }
+            ae0[r] = ck.input_forced ? fe : ck.n_parts > 0 ? from_fix(se) : 0.f;
+            ai0[r] = ck.input_forced ? fi : ck.n_parts > 0 ? from_fix(si) : 0.f;
+        }
+        if (i >= n) {  // a lane without a neuron never leaves its refractory period
+            st[r].r = INT32_MAX;
+            st[r].h0 = st[r].h1 = 0ull;
+        }
     }
+    if (b.lds_rows)
+        for (int x = tid; x <= n; x += kSmallBlock) rp[x] = (int32_t)b.row_ptr[x];
+    int slot = ring_slot(ck.t, b.delay);
+    uint32_t fired[R] = {};  // spikes of the steps not yet in the history words
+    // the fired bits of the last `steps` steps (1 .. 32) into the histories
+    auto fold = [&](int steps) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (H == 2) st[r].h1 = (st[r].h1 << steps) | (st[r].h0 >> (64 - steps));
+            st[r].h0 = (st[r].h0 << steps) | (uint64_t)fired[r];
+            fired[r] = 0u;
+        }
+    };
     for (int k = 0; k < b.steps; ++k) {
         const int64_t t = ck.t + k;
-        const int slot = (int)(t % b.delay);
         int32_t *list = b.ring + (int64_t)slot * n;
-        // (1) neuron update
-        int sp[kSmallRounds];
+        // the list of step t-D+1 (D > 1: written before this step)
+        const int tslot = slot + 1 == b.delay ? 0 : slot + 1;
+        const int32_t *tlist = b.ring + (int64_t)tslot * n;
+        int ntx = d1 ? 0 : min(max(b.ring_cnt[tslot], 0), n);
+        // (1) neuron update: every accumulator read, then cleared
+        float ae[R], ai[R];
+        if (M != 2 && k > 0) {
+            long long se[R], si[R];
 #pragma unroll
-        for (int r = 0; r < kSmallRounds; ++r) {
-            sp[r] = 0;
-            if (r >= rounds) continue;  // workgroup-uniform
+            for (int r = 0; r < R; ++r) {
+                se[r] = acc[r * kSmallBlock + tid];
+                si[r] = M == 1 ? acc[NP + r * kSmallBlock + tid] : 0;
+            }
+            bool small = true;
+#pragma unroll
+            for (int r = 0; r < R; ++r) small = small && fix_small(se[r]) && fix_small(si[r]);
+            if (!ballot64(!small)) {  // any input in earnest
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    ae[r] = from_fix_small(se[r]);
+                    ai[r] = M == 1 ? from_fix_small(si[r]) : 0.f;
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    ae[r] = from_fix(se[r]);
+                    ai[r] = M == 1 ? from_fix(si[r]) : 0.f;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                ae[r] = ae0[r];
+                ai[r] = ai0[r];
+            }
+        }
+        uint64_t m[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
             const int i = r * kSmallBlock + tid;
-            uint64_t hw0 = 0ull, hw1 = 0ull;
-            if (i < n) {
-                float ae = 0.f, ai = 0.f;
-                if (M != 2) {
-                    if (k == 0) {
-                        neuron_input(a, ck.input_forced, ck.n_parts, i, ae, ai);
-                    } else {
-                        ae = from_fix(acc[i]);
-                        if (M == 1) ai = from_fix(acc[n + i]);
-                    }
-                }
-                sp[r] = neuron_advance<M, H>(a, i, t, ae, ai, st[r]);
-                hw0 = st[r].h0;
-                hw1 = st[r].h1;
-            }
-            const uint64_t m = ballot64(sp[r]);
-            const uint64_t txm = ballot64((hw0 >> a.dm1) & 1ull);
-            const uint64_t rcm = ballot64((hw0 | hw1) != 0ull);
-            if (lane == 0) {
-                const int word = r * NWV + wave;
-                if (word * kWave < n) {
-                    a.mask[word] = m;
-                    a.txmask[word] = txm;
-                    a.recent[word] = rcm;
-                }
-                s_cnt[word] = __popcll(m);
-            }
+            acc[i] = 0;
+            if (M == 1) acc[NP + i] = 0;
+            const int sp = neuron_dynamics<M>(a, i, t, ae[r], ai[r], st[r]) && (M != 2 || i < n);
+            fired[r] = (fired[r] << 1) | (uint32_t)sp;
+            m[r] = ballot64(sp);
         }
-        __syncthreads();  // every input read, every count written
-        for (int x = tid; x < span; x += kSmallBlock) acc[x] = 0;
-        if (tid == 0) {  // exclusive offsets in (round, wave) = ascending order
-            int o = 0;
-            for (int q = 0; q < rounds * NWV; ++q) {
-                const int c = s_cnt[q];
-                s_cnt[q] = o;
-                o += c;
-            }
-            s_total = o;
-            b.ring_cnt[slot] = o;
+        {
+            uint64_t mine = m[0];  // lane r stores the wave's mask of round r
+#pragma unroll
+            for (int r = 1; r < R; ++r) mine = lane == r ? m[r] : mine;
+            if (lane < R) s_m[lane * NWV + wave] = mine;
         }
-        __syncthreads();
+        if (((k + 1) & 31) == 0) fold(32);
+        __syncthreads();  // every input read and cleared, every mask written
+        // spikes before each mask word, in (round, wave) = ascending order
+        const int cnt = lane < NWORD ? (int)__popcll(s_m[min(lane, NWORD - 1)]) : 0;
+        const int incl = wave_incl_scan(cnt, 0, AddOp{});
+        const int excl = incl - cnt;
+        const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
+        spikes += total;
+        if (d1) ntx = total;
+        // (3) delivery: 2^lg waves per row, each a stretch of 64 targets at a
+        // time, two loads in flight
+        const int lg = ntx > 0 && ntx < NWV ? 31 - __clz(NWV / ntx) : 0;
+        const int rows_at_once = NWV >> lg, part = wave & ((1 << lg) - 1);
+        for (int q = wave >> lg; q < ntx; q += rows_at_once) {  // wave-uniform
+            const int src = d1 ? kth_spike(s_m, excl, cnt, q, lane)
+                               : min(max(tlist[q], 0), n - 1);
+            const int64_t rs = b.lds_rows ? (int64_t)rp[src] : b.row_ptr[src];
+            const int64_t re = b.lds_rows ? (int64_t)rp[src + 1] : b.row_ptr[src + 1];
+            const int half = (M == 1 && src >= b.n_exc) ? NP : 0;
+            const int stride = kWave << lg;
+            for (int64_t e = rs + part * kWave + lane; e < re; e += 2 * stride) {
+                const bool two = e + stride < re;
+                const int64_t e1 = two ? e + stride : e;
+                const int c0 = b.col[e], c1 = b.col[e1];
+                const float w0 = b.w[e], w1 = b.w[e1];
+                atomicAdd((unsigned long long *)(acc + c0 + half), (unsigned long long)to_fix(w0));
+                if (two)
+                    atomicAdd((unsigned long long *)(acc + c1 + half),
+                              (unsigned long long)to_fix(w1));
+            }
+            if (lane == 0 && part == 0) events += re - rs;
+        }
+        // the spike list, off the delivery's chain
         const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
-        for (int r = 0; r < kSmallRounds; ++r) {
-            if (r >= rounds) continue;
-            const uint64_t m = ballot64(sp[r]);
-            if (sp[r]) list[s_cnt[r * NWV + wave] + __popcll(m & below)] = r * kSmallBlock + tid;
+        for (int r = 0; r < R; ++r) {
+            if (!m[r]) continue;  // wave-uniform
+            const int word = r * NWV + wave;
+            if ((m[r] >> lane) & 1ull)
+                list[__builtin_amdgcn_readlane(excl, word) + (int)__popcll(m[r] & below)] =
+                    word * kWave + lane;
         }
-        spikes += s_total;
-        __syncthreads();  // the list (global) and the cleared accumulator
-        // (3) delivery of the spikes of step t-D+1 (this step's for D = 1)
-        const int tslot = (int)((t - (b.delay - 1) + (int64_t)b.delay * 64) % b.delay);
-        const int32_t *tlist = b.ring + (int64_t)tslot * n;
-        const int ntx = min(max(b.ring_cnt[tslot], 0), n);
-        for (int q = wave; q < ntx; q += NWV) {  // wave-uniform
-            const int src = min(max(tlist[q], 0), n - 1);
-            const int64_t rs = b.row_ptr[src], re = b.row_ptr[src + 1];
-            const int half = (b.nacc == 2 && src >= b.n_exc) ? n : 0;
-            for (int64_t e = rs + lane; e < re; e += kWave)
-                atomicAdd((unsigned long long *)(acc + b.col[e] + half),
-                          (unsigned long long)to_fix(b.w[e]));
-            if (lane == 0) events += re - rs;
-        }
+        if (tid == 0) b.ring_cnt[slot] = total;
         __syncthreads();  // accumulation done before the next step reads it
+        slot = tslot;
+    }
+    if (b.steps & 31) {
+        const int rest = b.steps & 31;
+#pragma unroll
+        for (int r = 0; r < R; ++r) fired[r] &= (1u << rest) - 1u;
+        fold(rest);
     }
 #pragma unroll
-    for (int r = 0; r < kSmallRounds; ++r) {
-        const int i = r * kSmallBlock + tid;
-        if (r < rounds && i < n) {
+    for (int r = 0; r < R; ++r) {
+        const int i = r * kSmallBlock + tid, word = r * NWV + wave;
+        // the masks of the last step
+        const uint64_t m = ballot64((st[r].h0 & 1ull) && i < n);
+        const uint64_t txm = ballot64(((st[r].h0 >> a.dm1) & 1ull) && i < n);
+        const uint64_t rcm = ballot64((st[r].h0 | st[r].h1) != 0ull && i < n);
+        if (lane == 0 && word * kWave < n) {
+            a.mask[word] = m;
+            a.txmask[word] = txm;
+            a.recent[word] = rcm;
+        }
+        if (i < n) {
             nstate_store<M, H>(a, i, st[r]);
             a.code[i] = hist_code(st[r].h0, st[r].h1);
+            b.apart[i] = acc[i];
+            if (M == 1) b.apart[n + i] = acc[NP + i];
         }
     }
-    for (int x = tid; x < span; x += kSmallBlock) b.apart[x] = acc[x];
     // the list scans of the other kernels find no stale step tag after these steps
     for (int x = tid; x < b.status_words; x += kSmallBlock) b.status[x] = 0ull;
     if (lane == 0 && events) atomicAdd((unsigned long long *)b.dlv_stats, (unsigned long long)events);
@@ -789,17 +891,28 @@ hipError_t launch_steps(hipStream_t s, const NeuronArgs &a, const BatchArgs &b)
     return hipGetLastError();
 }
 
-template <int M, int H>
-hipError_t launch_small(hipStream_t s, const NeuronArgs &a, const SmallArgs &b, size_t lds,
-                        KernelEvents ev)
+template <int M, int H, int R>
+hipError_t launch_small_r(hipStream_t s, const NeuronArgs &a, const SmallArgs &b, KernelEvents ev)
 {
     static std::mutex mu;
     static int granted = 48 * 1024;
+    const size_t lds = (size_t)(M == 1 ? 2 : 1) * R * kSmallBlock * sizeof(long long) +
+                       (b.lds_rows ? ((size_t)a.n + 1) * sizeof(int32_t) : 0);
     const hipError_t e =
-        allow_dynamic_lds((const void *)k_small_steps<M, H>, (int)lds, mu, granted);
+        allow_dynamic_lds((const void *)k_small_steps<M, H, R>, (int)lds, mu, granted);
     if (e != hipSuccess) return e;
-    launch_kernel(k_small_steps<M, H>, dim3(1), dim3(kSmallBlock), lds, s, ev, a, b);
+    launch_kernel(k_small_steps<M, H, R>, dim3(1), dim3(kSmallBlock), lds, s, ev, a, b);
     return hipGetLastError();
+}
+
+// the rounds of kSmallBlock neurons a thread holds: 1, 2 or 4
+template <int M, int H>
+hipError_t launch_small(hipStream_t s, const NeuronArgs &a, const SmallArgs &b, KernelEvents ev)
+{
+    static_assert(kSmallRounds == 4, "the rounds instantiated below");
+    if (a.n <= kSmallBlock) return launch_small_r<M, H, 1>(s, a, b, ev);
+    if (a.n <= 2 * kSmallBlock) return launch_small_r<M, H, 2>(s, a, b, ev);
+    return launch_small_r<M, H, 4>(s, a, b, ev);
 }
 
 }  // namespace
@@ -854,15 +967,16 @@ hipError_t launch_copy_bytes(hipStream_t s, void *dst, const void *src, int64_t 
 hipError_t launch_small_steps(hipStream_t s, const NeuronArgs &a, const SmallArgs &b,
                               KernelEvents ev)
 {
-    const size_t lds = (size_t)b.nacc * a.n * sizeof(long long);
+    if (a.n < 1 || a.n > kSmallRounds * kSmallBlock || b.nacc != (a.model == 1 ? 2 : 1))
+        return hipErrorInvalidValue;
     const int m = a.model == 1 ? 1 : a.model == 2 ? 2 : 0;
     switch (m * 2 + (a.hw == 2)) {
-    case 0: return launch_small<0, 1>(s, a, b, lds, ev);
-    case 1: return launch_small<0, 2>(s, a, b, lds, ev);
-    case 2: return launch_small<1, 1>(s, a, b, lds, ev);
-    case 3: return launch_small<1, 2>(s, a, b, lds, ev);
-    case 4: return launch_small<2, 1>(s, a, b, lds, ev);
-    default: return launch_small<2, 2>(s, a, b, lds, ev);
+    case 0: return launch_small<0, 1>(s, a, b, ev);
+    case 1: return launch_small<0, 2>(s, a, b, ev);
+    case 2: return launch_small<1, 1>(s, a, b, ev);
+    case 3: return launch_small<1, 2>(s, a, b, ev);
+    case 4: return launch_small<2, 1>(s, a, b, ev);
+    default: return launch_small<2, 2>(s, a, b, ev);
     }
 }
 

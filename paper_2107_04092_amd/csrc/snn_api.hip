@@ -1455,6 +1455,8 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
         b.n_exc = c->cfg.n_exc;
         b.nacc = c->nacc;
         b.steps = k;
+        // (32-bit row pointers: at most 4096 rows of at most 16384 edges here)
+        b.lds_rows = k >= kSmallStage && c->n_edges <= INT32_MAX;
         if ((st = check_hip(c, launch_small_steps(c->stream, a, b), "small-network steps")))
             return st;
         c->t += k;

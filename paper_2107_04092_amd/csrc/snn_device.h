@@ -46,6 +46,19 @@ __device__ __forceinline__ float pow_mu(float w, float mu)
 __device__ __forceinline__ long long to_fix(float x) { return __float2ll_rn(x * kFixScale); }
 // fixed point -> fp32, one correctly rounded conversion (the scaling is exact)
 __device__ __forceinline__ float from_fix(long long s) { return __ll2float_rn(s) * kFixUnit; }
+// A sum below 2^50 in size (any input below 2^18 mV) goes through double: added
+// to the bits of 1.5 2^52 it is that number's mantissa, and subtracting the
+// number again leaves the sum exactly, so the one conversion that follows
+// rounds as __ll2float_rn does, in a third of its instructions.
+__device__ __forceinline__ bool fix_small(long long s)
+{
+    return (unsigned)((int)(s >> 32) + (1 << 18)) < (1u << 19);
+}
+__device__ __forceinline__ float from_fix_small(long long s)  // fix_small(s)
+{
+    const double d = __longlong_as_double(s + 0x4338000000000000ll) - 6755399441055744.0;
+    return (float)d * kFixUnit;
+}
 
 // Adds v to a 64-bit counter in global memory without waiting for it (an
 // atomic whose result is unused needs no round trip; a read-modify-write

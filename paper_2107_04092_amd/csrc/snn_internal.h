@@ -293,7 +293,11 @@ struct SmallArgs {
     unsigned long long *status;
     int32_t status_words;
     int32_t n_exc, nacc, steps;
+    int32_t lds_rows;           // 1: the row pointers are staged in LDS (32 bits each)
 };
+// steps per launch from which staging the row pointers pays (one step reads
+// each spike's pair once)
+constexpr int kSmallStage = 4;
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallRounds = 4;     // neurons per thread: n <= 4096
 constexpr int kSmallMaxAcc = 8192;  // nacc * n accumulators (64 KiB of LDS)

@@ -135,62 +135,46 @@ __device__ __forceinline__ int poisson_count(const NeuronArgs &a, int64_t t, int
     return k;
 }
 
-// One neuron's update at step t (i < n) on its state in registers, with
-// input (ae, ai): its dynamics in a fixed fp32 operation order, its post
-// trace and its history words. Returns whether it spiked.
+// The dynamics of one neuron at step t (i < n) on its state in registers,
+// with input (ae, ai), in a fixed fp32 operation order. Returns whether it
+// spiked. A refractory neuron counts down and holds the reset potential: both
+// outcomes are computed and selected, so a wave with a few refractory neurons
+// does not walk two branches.
+template <int M>
+__device__ __forceinline__ int neuron_dynamics(const NeuronArgs &a, int i, int64_t t, float ae,
+                                               float ai, NState &st)
+{
+    if (nmodel<M>(a) == 2) return rng32(a.seed, 4, (uint64_t)t, (uint64_t)i) < a.fire_thr;
+    const bool held = st.r > 0;
+    float v;
+    if (nmodel<M>(a) == 1) {
+        st.ie = __fadd_rn(__fmul_rn(st.ie, a.d_e), ae);
+        st.ii = __fadd_rn(__fmul_rn(st.ii, a.d_i), ai);
+        float x = __fsub_rn(a.v_inf, st.v);
+        x = __fadd_rn(x, st.ie);
+        x = __fadd_rn(x, st.ii);
+        v = __fadd_rn(st.v, __fmul_rn(x, a.k_m));
+    } else {
+        float x = 0.f;
+        if (a.poisson_len > 0 && !held) {
+            x = __fmul_rn(a.j_ext, (float)poisson_count(a, t, i));
+        }
+        const float b = __fmul_rn(__fsub_rn(a.v_inf, st.v), a.k_m);
+        v = __fadd_rn(__fadd_rn(__fadd_rn(st.v, b), ae), x);
+    }
+    const bool s = !held && v >= a.v_th;
+    st.v = held || s ? a.v_reset : v;
+    st.r = s ? a.ref_steps : held ? st.r - 1 : st.r;
+    return s;
+}
+
+// One neuron's update at step t (i < n): its dynamics, its post trace and its
+// history words. Returns whether it spiked.
 template <int M, int H>
 __device__ __forceinline__ int neuron_advance(const NeuronArgs &a, int i, int64_t t, float ae,
                                               float ai, NState &st)
 {
-    int s = 0;
-    if (nmodel<M>(a) == 2) {
-        s = rng32(a.seed, 4, (uint64_t)t, (uint64_t)i) < a.fire_thr;
-    } else {
-        float v = st.v;
-        int r = st.r;
-        if (nmodel<M>(a) == 1) {
-            const float ie = __fadd_rn(__fmul_rn(st.ie, a.d_e), ae);
-            const float ii = __fadd_rn(__fmul_rn(st.ii, a.d_i), ai);
-            st.ie = ie;
-            st.ii = ii;
-            if (r > 0) {
-                r -= 1;
-                v = a.v_reset;
-            } else {
-                float x = __fsub_rn(a.v_inf, v);
-                x = __fadd_rn(x, ie);
-                x = __fadd_rn(x, ii);
-                v = __fadd_rn(v, __fmul_rn(x, a.k_m));
-                if (v >= a.v_th) {
-                    s = 1;
-                    v = a.v_reset;
-                    r = a.ref_steps;
-                }
-            }
-        } else {
-            if (r > 0) {
-                r -= 1;
-                v = a.v_reset;
-            } else {
-                float x = 0.f;
-                if (a.poisson_len > 0) {
-                    x = __fmul_rn(a.j_ext, (float)poisson_count(a, t, i));
-                }
-                const float d = __fsub_rn(a.v_inf, v);
-                const float b = __fmul_rn(d, a.k_m);
-                const float c = __fadd_rn(v, b);
-                v = __fadd_rn(c, ae);
-                v = __fadd_rn(v, x);
-                if (v >= a.v_th) {
-                    s = 1;
-                    v = a.v_reset;
-                    r = a.ref_steps;
-                }
-            }
-        }
-        st.v = v;
-        st.r = r;
-    }
+    const int s = neuron_dynamics<M>(a, i, t, ae, ai, st);
     if (nplastic<M>(a)) {
         // post trace seen by a pre spike at step t: posts strictly before t
         st.y = __fmul_rn(__fadd_rn(st.y, (float)(st.h0 & 1ull)), a.d_minus);
