@@ -648,7 +648,8 @@ NeuronArgs neuron_args(snn_ctx *c)
     a.d_minus = c->d_minus;
     a.fire_thr = c->fire_thr;
     a.seed = c->cfg.seed;
-    for (int q = 0; q < kMaxPoisson; ++q) a.poisson[q] = c->cfg.poisson_cdf[q];
+    for (int q = 0; q < kMaxPoisson; ++q)
+        a.poisson[q] = q < a.poisson_len ? c->cfg.poisson_cdf[q] : 0xFFFFFFFFu;
     return a;
 }
 

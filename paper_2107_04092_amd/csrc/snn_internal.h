@@ -91,7 +91,7 @@ struct NeuronArgs {
     float k_m, v_th, v_reset, v_inf, d_e, d_i, j_ext, d_minus;
     uint32_t fire_thr;
     uint64_t seed;
-    uint32_t poisson[kMaxPoisson];
+    uint32_t poisson[kMaxPoisson];  // entries past poisson_len: the largest word
 };
 
 struct RowInfo;

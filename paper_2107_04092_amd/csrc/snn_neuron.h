@@ -122,17 +122,24 @@ __device__ __forceinline__ void neuron_input(const NeuronArgs &a, int forced, in
 }
 
 // The external Poisson count of neuron i at step t: the number of CDF
-// thresholds at or below one 32-bit draw (inversion). Unrolled over the
-// table's capacity, so the thresholds are loaded once, not waited for inside
-// a loop.
+// thresholds at or below one 32-bit draw (inversion). The table is
+// non-decreasing and padded to its capacity with the largest word (which only
+// the largest draw reaches, and that one counts every entry of the table:
+// hence the minimum), so it is walked in groups of four and left once no lane
+// of the wave is past the group: with a mean of 2, two groups instead of 32
+// compares with as many conditions in spilled scalar registers.
 __device__ __forceinline__ int poisson_count(const NeuronArgs &a, int64_t t, int i)
 {
+    static_assert(kMaxPoisson % 4 == 0, "whole groups");
     const uint32_t u = rng32(a.seed, 3, (uint64_t)t, (uint64_t)i);
     int k = 0;
 #pragma unroll
-    for (int q = 0; q < kMaxPoisson; ++q)
-        if (q < a.poisson_len) k += (a.poisson[q] <= u);
-    return k;
+    for (int g = 0; g < kMaxPoisson; g += 4) {
+        if (g > 0 && !ballot64(a.poisson[g - 1] <= u)) break;  // wave-uniform
+#pragma unroll
+        for (int q = g; q < g + 4; ++q) k += (a.poisson[q] <= u);
+    }
+    return min(k, a.poisson_len);
 }
 
 // The dynamics of one neuron at step t (i < n) on its state in registers,
@@ -156,7 +163,9 @@ __device__ __forceinline__ int neuron_dynamics(const NeuronArgs &a, int i, int64
         v = __fadd_rn(st.v, __fmul_rn(x, a.k_m));
     } else {
         float x = 0.f;
-        if (a.poisson_len > 0 && !held) {
+        if (a.poisson_len > 0) {  // uniform
+            // (keeps the branch: without a drive the draw is not computed)
+            asm volatile("");
             x = __fmul_rn(a.j_ext, (float)poisson_count(a, t, i));
         }
         const float b = __fmul_rn(__fsub_rn(a.v_inf, st.v), a.k_m);

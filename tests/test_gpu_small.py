@@ -1,17 +1,19 @@
 """Small networks in one workgroup, at the edges of its rounds, of its history
-folding (every 32 steps) and of its input conversion.
+folding (every 32 steps) and of its input conversion; and the external drive's
+table walk.
 
 The steps of one launch are compared bit for bit with the separate part calls
-of the same library (another kernel for each part).
+of the same library (another kernel for each part), the drive with the oracle.
 """
 
+import numpy as np
 import pytest
 
 import workloads as wl
 from workloads.presets import PLASTIC_NONE
 from paper_2107_04092_amd import snn
 
-from gpu_common import gpu_net, log, same_state
+from gpu_common import gpu_net, to_np, log, same_state
 
 pytestmark = pytest.mark.gpu
 LDS = snn.SNN_DELIVER_LDS_SLICE
@@ -49,3 +51,26 @@ def test_one_workgroup_equals_the_parts(case):
             b.deliver_spikes(LDS)
             b.advance()
         same_state(a, b, "%d steps" % k, weights=False)
+
+
+@pytest.mark.parametrize("table", [
+    [2 ** 31], [0], [2 ** 32 - 1], [1 << 29, 2 << 29, 3 << 29, 4 << 29],
+    [1 << 28, 1 << 29, 1 << 30, 3 << 30, 2 ** 32 - 5],
+    [(q + 1) * (2 ** 32 // 33) for q in range(32)],
+], ids=lambda t: "%d-entries-%x" % (len(t), t[0]))
+def test_drive_table_matches_oracle(table):
+    """Tables of every fill (none, one group, the whole capacity; saturated or
+    not): spikes and potentials of a driven network equal the oracle's."""
+    from oracle import oracle
+    log("drive table of %d entries" % len(table))
+    p = wl.preset("brunel", n=700, n_exc=560, p_or_fanout=0.05, delay=1, j_ext=0.7,
+                  poisson_mu=0.0)
+    net = snn.Network(snn.config_from_preset(p, table))
+    net.build_random(p.graph_kind, p.p_or_fanout, p.w_exc, p.w_inh)
+    o = oracle.Oracle(p, np.asarray(table, np.uint32))
+    o.build_random()
+    net.step(40, LDS)
+    o.step(40)
+    s, n = net.state(), o.neurons()
+    assert np.array_equal(to_np(s["hist"]).view(np.uint64), n["hist"])
+    assert np.array_equal(to_np(s["v"]).view(np.uint32), n["v"].view(np.uint32))
