@@ -92,6 +92,12 @@ __global__ __launch_bounds__(kPbPlanBlock) void k_block_plan(BlockArgs b)
     }
     // (a forced update is the row's last event when no higher bit is set)
     const uint32_t dfm = fm != 0u && (evm >> (__ffs((int)fm))) == 0u ? fm : 0u;
+    if (b.fin_blocks) {  // the forced rows of the call's last step, for the lists after it
+        const uint64_t m = ballot64((fm >> (B - 1)) & 1u);
+        const int word = blockIdx.x * NWV + wave;
+        if (lane == 0 && word * kWave < b.n)
+            b.dmask[(int64_t)D * ((b.n + kWave - 1) / kWave) + word] = m;
+    }
     for (int q = 0; q <= B; ++q) {  // uniform
         const bool ev = q < B ? ((evm & ~dfm) >> q) & 1u : dfm != 0u;
         const uint64_t m = ballot64(ev);
@@ -633,6 +639,25 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
         const int lc = last <= 64 * HW - 16 ? 0 : last >= 64 * HW - 1 ? 15 : last - (64 * HW - 16);
         b.dcode[i] = (uint8_t)(first | (lc << 4));
     }
+    if (b.fin_blocks && wave * kWave < wn) {  // wave-uniform
+        // the call's last block: the masks of its last step, and (b.dmask) the
+        // spikes of the last D steps, which the lists are made from
+        const int word = glo / kWave + wave, nw = (n + kWave - 1) / kWave;
+        const uint64_t h0 = live ? st.h0 : 0ull, h1 = live ? st.h1 : 0ull;
+        const uint64_t txm = ballot64((h0 >> (b.delay - 1)) & 1ull);
+        const uint64_t rcm = ballot64((h0 | h1) != 0ull);
+        uint64_t mine = 0ull;  // lane q: the spikes of step t0 + B - 1 - q
+        for (int q = 0; q < b.delay; ++q) {
+            const uint64_t m = ballot64((h0 >> q) & 1ull);
+            if (lane == q) mine = m;
+        }
+        if (lane < b.delay) b.dmask[(int64_t)lane * nw + word] = mine;
+        if (lane == 0) {
+            b.mask[word] = mine;
+            b.txmask[word] = txm;
+            b.recent[word] = rcm;
+        }
+    }
     events = block_sum_i64_n<kPbBlock>(events, sh);
     w_tx = block_sum_i64_n<kPbBlock>(w_tx, sh);
     w_forced = block_sum_i64_n<kPbBlock>(w_forced, sh);
@@ -645,6 +670,7 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
         if (spikes) add_stat(b.gstats + kGSpikes, spikes);
         if (g == 0) {
             add_stat(b.gstats + kGSteps, B);
+            *b.df_cnt = b.ev_cnt[B];  // the deferred updates' count
             b.clk->t = t0 + B;
             b.clk->input_forced = 0;  // the next input is partial sum 0
             b.clk->n_parts = 1;
@@ -686,6 +712,51 @@ struct DfPart {
     int valid;
 };
 
+// After the last block of a call, the per-step lists of the step-by-step path,
+// from the masks the run and the plan left (b.dmask): role q < D, the spike
+// list of step t-1-q (t = clk->t) in ascending order into its ring slot, with
+// its count and each neuron's position; role D, the forced rows of step t-1.
+// Each also clears a share of the list scans' status words, so that no stale
+// step tag matches a later scan. These workgroups join the last block's
+// deferred launch (neither needs the other): a mask word per thread and one
+// scan over the words, 25,000 neurons and D = 15: about no time of its own beside the
+// deferred updates, against 28.4 us as a launch of its own that read the
+// histories 1,024 neurons at a time (18.0 with eight loads in flight: one CU
+// per list reads 200 KB).
+__device__ __forceinline__ void finish_lists(const BlockArgs &b, int q, long long *sh)
+{
+    const int tid = threadIdx.x;
+    const int n = b.n, D = b.delay;
+    const int nw = (n + kWave - 1) / kWave;
+    static_assert(kPbMaxN / kWave <= kDfBlock, "one mask word per thread");
+    uint64_t m = tid < nw ? b.dmask[(int64_t)q * nw + tid] : 0ull;
+    const int64_t t = load_clock(b.clk).t;
+    for (int64_t x = (int64_t)q * kDfBlock + tid; x < b.status_words;
+         x += (int64_t)(D + 1) * kDfBlock)
+        b.status[x] = 0ull;
+    if (q == 0 && tid < kBatchMax) {  // both blocks' list counts, for the next call's plans
+        b.ev_cnt[tid] = 0;            // (the deferred updates read b.df_cnt)
+        b.ev_cnt_next[tid] = 0;
+    }
+    const bool lists = q < D;
+    const int own = (int)__popcll(m);
+    const int incl = (int)block_incl_scan_i64_n<kDfBlock>(own, sh);
+    const int slot = ring_slot(t - 1 - q, D);
+    int32_t *list = lists ? b.ring + (int64_t)slot * n : b.rows;
+    int32_t *pos = b.spk_pos + (int64_t)slot * n;  // (lists only)
+    for (int r = incl - own; m; m &= m - 1ull, ++r) {  // r < n: one entry per neuron
+        const int i = tid * kWave + __ffsll((long long)m) - 1;
+        list[r] = i;
+        if (lists) pos[i] = r;
+    }
+    if (tid == kDfBlock - 1) {
+        if (lists)
+            b.ring_cnt[slot] = incl;
+        else
+            *b.row_cnt = incl;
+    }
+}
+
 template <int HW>
 __global__ __launch_bounds__(kDfBlock) void k_block_deferred(BlockArgs b)
 {
@@ -698,7 +769,12 @@ __global__ __launch_bounds__(kDfBlock) void k_block_deferred(BlockArgs b)
     __shared__ long long sh[NWV];
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int n = b.n, B = b.steps;
-    const int nd = min(max(b.ev_cnt[B], 0), n);
+    if ((int)blockIdx.x < b.fin_blocks) {  // whole workgroup, before any barrier
+        finish_lists(b, blockIdx.x, sh);
+        return;
+    }
+    const int block = blockIdx.x - b.fin_blocks, blocks = gridDim.x - b.fin_blocks;
+    const int nd = min(max(*b.df_cnt, 0), n);
     const PbEvent *__restrict__ evd = b.ev + (int64_t)B * n;
     const int32_t *__restrict__ col = b.col;
     float *__restrict__ wgt = b.w;
@@ -718,8 +794,8 @@ __global__ __launch_bounds__(kDfBlock) void k_block_deferred(BlockArgs b)
     // holds the record of the row of item (j & ~63) + l, read out for the
     // current item j (no load inside the part stream waits on a record).
     const int P = b.df_parts;
-    const int stride = gridDim.x * NWV;
-    const int w0 = blockIdx.x * NWV + wave;
+    const int stride = blocks * NWV;
+    const int w0 = block * NWV + wave;
     const long long nitems = (long long)nd * P;
     const int nit = w0 < nitems ? (int)((nitems - 1 - w0) / stride + 1) : 0;
     PbEvent le = PbEvent{};
@@ -874,89 +950,7 @@ __global__ __launch_bounds__(kDfBlock) void k_block_deferred(BlockArgs b)
         step(P1);
     }
     written = block_sum_i64_n<kDfBlock>(written, sh);
-    if (tid == 0 && written) add_stat(b.syn_stats + (blockIdx.x % b.syn_slots), written);
-}
-
-// ---------------------------------------------------------------------------
-// After the last block of a call, what the step-by-step path keeps per step,
-// rebuilt from the histories (the run writes none of it): workgroup q < D,
-// the spike list of step t-1-q (bit q of history word 0; t = clk->t) in
-// ascending order into its ring slot, with its count and each neuron's
-// position; workgroup D, the spike, transmit and recency masks of step t-1
-// and its forced rows (plastic, brought up to date at t-1 without
-// transmitting), ascending. Every workgroup clears a share of the list
-// scans' status words, so that no stale step tag matches a later scan.
-
-constexpr int kPbFinishBlock = 1024;
-
-__global__ __launch_bounds__(kPbFinishBlock) void k_block_finish(BlockArgs b)
-{
-    constexpr int NWV = kPbFinishBlock / kWave;
-    __shared__ int s_cnt[NWV];
-    __shared__ int s_base;
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const int q = blockIdx.x;
-    const int n = b.n, hw = b.hw, D = b.delay;
-    const int64_t t = load_clock(b.clk).t;
-    for (int64_t x = (int64_t)q * kPbFinishBlock + tid; x < b.status_words;
-         x += (int64_t)gridDim.x * kPbFinishBlock)
-        b.status[x] = 0ull;
-    if (q == 0 && tid < kBatchMax) {  // both blocks' list counts, for the next call's plans
-        b.ev_cnt[tid] = 0;
-        b.ev_cnt_next[tid] = 0;
-    }
-    if (tid == 0) s_base = 0;
-    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    const bool lists = q < D;
-    const int slot = ring_slot(t - 1 - q, D);
-    int32_t *list = lists ? b.ring + (int64_t)slot * n : b.rows;
-    int32_t *pos = b.spk_pos + (int64_t)slot * n;  // (lists only)
-    for (int i0 = 0; i0 < n; i0 += kPbFinishBlock) {  // uniform
-        const int i = i0 + tid;
-        bool s = false;
-        if (lists) {
-            s = i < n && ((b.hist[(int64_t)i * hw] >> q) & 1ull);
-        } else {
-            uint64_t h0 = 0ull, h1 = 0ull;
-            if (i < n) {
-                h0 = b.hist[(int64_t)i * hw];
-                if (hw == 2) h1 = b.hist[(int64_t)i * hw + 1];
-            }
-            const bool tx = (h0 >> (D - 1)) & 1ull;
-            s = i < b.n_plastic_rows && !tx && (int64_t)b.t_last[i] == t - 1;
-            const uint64_t m = ballot64(i < n && (h0 & 1ull));
-            const uint64_t txm = ballot64(i < n && tx);
-            const uint64_t rcm = ballot64(i < n && (h0 | h1) != 0ull);
-            const int64_t word = (int64_t)(i0 / kWave) + wave;
-            if (lane == 0 && word * kWave < n) {
-                b.mask[word] = m;
-                b.txmask[word] = txm;
-                b.recent[word] = rcm;
-            }
-        }
-        const uint64_t m = ballot64(s);
-        if (lane == 0) s_cnt[wave] = __popcll(m);
-        __syncthreads();  // s_cnt, and s_base of the previous round
-        int p = s_base, tot = 0;
-        for (int w = 0; w < NWV; ++w) {
-            if (w < wave) p += s_cnt[w];
-            tot += s_cnt[w];
-        }
-        if (s) {
-            const int r = p + __popcll(m & below);
-            list[r] = i;
-            if (lists) pos[i] = r;
-        }
-        __syncthreads();  // every read of s_cnt and s_base
-        if (tid == 0) s_base = p + tot;  // (thread 0: p is the round's base)
-    }
-    __syncthreads();
-    if (tid == 0) {
-        if (lists)
-            b.ring_cnt[slot] = s_base;
-        else
-            *b.row_cnt = s_base;
-    }
+    if (tid == 0 && written) add_stat(b.syn_stats + (block % b.syn_slots), written);
 }
 
 template <int HW, bool CT>
@@ -996,21 +990,18 @@ hipError_t launch_block_deferred(hipStream_t s, const BlockArgs &b)
 {
     if (b.steps < 1 || b.steps > kPbMaxSteps || b.n < 1 || b.n > kPbMaxN || b.n_edges < 1 ||
         b.n_edges > INT32_MAX || b.n_cu < 1 || b.syn_slots < 1 || (b.hw != 1 && b.hw != 2) ||
-        b.df_parts < 1 || b.df_parts > (kMaxSortRow + 7 + kDfPart - 1) / kDfPart)
+        b.df_parts < 1 || b.df_parts > (kMaxSortRow + 7 + kDfPart - 1) / kDfPart ||
+        (b.fin_blocks != 0 && b.fin_blocks != b.delay + 1) || b.delay < 2 || b.delay > 64)
         return hipErrorInvalidValue;
-    const int grid = (int)std::min<int64_t>(
-        (int64_t)b.n_cu, ((int64_t)b.n * b.df_parts + kDfBlock / kWave - 1) / (kDfBlock / kWave));
+    // one workgroup per CU, those of the lists among them
+    const int grid =
+        b.fin_blocks + (int)std::min<int64_t>(
+                           std::max(b.n_cu - b.fin_blocks, 1),
+                           ((int64_t)b.n * b.df_parts + kDfBlock / kWave - 1) / (kDfBlock / kWave));
     if (b.hw == 2)
         hipLaunchKernelGGL(k_block_deferred<2>, dim3(grid), dim3(kDfBlock), 0, s, b);
     else
         hipLaunchKernelGGL(k_block_deferred<1>, dim3(grid), dim3(kDfBlock), 0, s, b);
-    return hipGetLastError();
-}
-
-hipError_t launch_block_finish(hipStream_t s, const BlockArgs &b)
-{
-    if (b.delay < 2 || b.delay > 64 || b.n < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_block_finish, dim3(b.delay + 1), dim3(kPbFinishBlock), 0, s, b);
     return hipGetLastError();
 }
 

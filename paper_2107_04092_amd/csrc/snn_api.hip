@@ -128,6 +128,8 @@ struct snn_ctx {
     PbEvent *pev = nullptr;
     int32_t *pev_cnt = nullptr;
     uint8_t *pdcode = nullptr;
+    int32_t *pdf_cnt = nullptr;
+    uint64_t *pdmask = nullptr;
     uint64_t *phq = nullptr;
     BlockClock *bclk = nullptr;
     // source blocks (SourceArgs: Bernoulli sources, D = 1, plastic): most
@@ -450,6 +452,8 @@ void plan_workspace(snn_ctx *c, uint8_t *base)
     c->abatch = p.take<long long>(c->batch_max > 0 ? (int64_t)c->batch_max * c->nacc * n : 1);
     c->pev = p.take<PbEvent>(c->pb_max > 0 ? (int64_t)(c->pb_max + 1) * n : 1);
     c->pev_cnt = p.take<int32_t>(2 * kBatchMax);  // consecutive blocks alternate halves
+    c->pdf_cnt = p.take<int32_t>(1);
+    c->pdmask = p.take<uint64_t>(c->pb_max > 0 ? (int64_t)(c->delay + 1) * c->nw : 1);
     c->pdcode = p.take<uint8_t>(c->pb_max > 0 ? (n + 15) / 16 * 16 : 1);
     c->phq = p.take<uint64_t>(c->pb_max > 0 ? 2 * n * c->hw : 1);
     c->bclk = p.take<BlockClock>(1);
@@ -670,6 +674,8 @@ BlockArgs block_args(snn_ctx *c, int32_t steps, int32_t parity)
     b.ev_cnt = c->pev_cnt + (parity & 1) * kBatchMax;
     b.ev_cnt_next = c->pev_cnt + (~parity & 1) * kBatchMax;
     b.dcode = c->pdcode;
+    b.df_cnt = c->pdf_cnt;
+    b.dmask = c->pdmask;
     b.hq = c->phq;
     b.n_cu = c->n_cu;
     b.df_parts = (int32_t)std::max<int64_t>(1, ((int64_t)c->max_row + 7 + kPbDfPart - 1) /
@@ -1547,14 +1553,15 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
         return SNN_OK;
     }
     // a plastic network with D >= 2 runs in blocks of up to D-1 steps (see
-    // BlockArgs): the plan, then the run of the block, and after the last
-    // block the per-step lists
+    // BlockArgs): the plan, the run and the deferred updates of each block,
+    // the last one's launch with the per-step lists
     const bool pblocks = mode == SNN_DELIVER_LDS_SLICE && c->pb_max > 0 && c->t_used >= c->t_cap;
     if (pblocks && n_steps > 0) {
         const NeuronArgs a = neuron_args(c);
         for (int32_t q = 0, k = 0; q < n_steps; ++k) {
             const int32_t B = std::min<int32_t>(n_steps - q, c->pb_max);
-            const BlockArgs b = block_args(c, B, k);
+            BlockArgs b = block_args(c, B, k);
+            if (q + B == n_steps) b.fin_blocks = c->delay + 1;
             if ((st = check_hip(c, launch_block_plan(c->stream, b), "plastic block plan")))
                 return st;
             if ((st = check_hip(c, launch_block_run(c->stream, a, b), "plastic block run")))
@@ -1564,9 +1571,6 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
             c->t += B;
             q += B;
         }
-        if ((st = check_hip(c, launch_block_finish(c->stream, block_args(c, 1, 0)),
-                            "plastic block lists")))
-            return st;
         c->last_neuron_t = c->last_deliver_t = c->t - 1;
         return SNN_OK;
     }

@@ -350,10 +350,10 @@ constexpr int64_t kBatchBytes = 256ll << 20;  // most workspace for a block's pa
 // (gpiv[k][g] = the row-relative first entry of row k with a target >=
 // g gwidth, g = 0..n_groups; the pivot kernel with gwidth for the slice
 // width). After the last
-// block of a call, k_block_finish rebuilds from the histories what the
-// step-by-step path keeps per step: the delay-ring lists of the last D
-// steps with their positions, the masks and forced-row list of the last
-// step; and clears the list scans' status words.
+// block of a call, the deferred launch also rebuilds what the step-by-step
+// path keeps per step: the delay-ring lists of the last D steps with their
+// positions and the forced-row list of the last step, from masks the run and
+// the plan leave; and clears the list scans' status words.
 struct BlockClock {
     long long t0;          // the block's first step
     int32_t input_forced;  // the input of step t0, as the step clock said
@@ -400,6 +400,12 @@ struct BlockArgs {
                                  // it against a forced window (4-7)
     uint64_t *hq;                // [n][2 hw] run -> deferred: history words at block start,
                                  // then the block's spikes (bit 0: its last step)
+    int32_t *df_cnt;             // run -> deferred: the deferred list's length
+    uint64_t *dmask;             // [D + 1][mask words]: run -> lists, spikes of the last D steps
+                                 // (row q: step t0 + B - 1 - q); plan -> lists, row D: the
+                                 // forced rows of the block's last step
+    int32_t fin_blocks;          // D + 1 after a call's last block: the deferred launch also
+                                 // rebuilds the per-step lists; else 0
     int32_t n_cu;
     int32_t df_parts;            // parts of kDfPart entries of the longest row (deferred)
     BlockClock *bclk;            // written by the plan, read by the run
@@ -424,7 +430,7 @@ struct BlockArgs {
     int64_t *gstats;
     int32_t event;               // 1: replay only the set history bits; 0: every step
     float c_pot, c_dep, mu;
-    // finish
+    // lists after the last block
     int32_t *ring, *ring_cnt, *spk_pos, *rows, *row_cnt;
     uint64_t *mask, *txmask, *recent;
     int32_t status_words;
@@ -468,7 +474,6 @@ constexpr int kSrcMaxSteps = kBatchMax;  // steps per source block (one scan per
 hipError_t launch_block_plan(hipStream_t s, const BlockArgs &b);
 hipError_t launch_block_run(hipStream_t s, const NeuronArgs &a, const BlockArgs &b);
 hipError_t launch_block_deferred(hipStream_t s, const BlockArgs &b);
-hipError_t launch_block_finish(hipStream_t s, const BlockArgs &b);
 
 // Optional events placed by a launch itself around the kernel
 // (hipExtLaunchKernelGGL): its device time without marker or dispatch gaps.
