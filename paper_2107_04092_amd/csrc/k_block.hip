@@ -164,7 +164,7 @@ __global__ __launch_bounds__(kPbPlanBlock) void k_block_plan(BlockArgs b)
                            ((uint32_t)((ri.age_pre >> 8) & 1) << 24)
                      : 0u;
         pe.lenf |= ((uint32_t)tx << 25) | ((uint32_t)(b.nacc == 2 && kr >= b.n_exc) << 26) |
-                   ((uint32_t)q << 27);
+                   ((uint32_t)q << 27) | (q > 0 ? ((r_evm >> (q - 1)) & 1u) << 31 : 0u);
         pe.xp0 = ok ? ri.xp0 : 0.f;
         pe.k = kr;
         const int lq = (r_dfm >> q) & 1u ? B : q;  // the list
@@ -202,10 +202,8 @@ __global__ __launch_bounds__(kPbPlanBlock) void k_block_plan(BlockArgs b)
 //       its state in registers from the first step to the last), with the
 //       input of step t: the state's input at t0, afterwards the LDS
 //       accumulator; the new history words and post traces go to LDS;
-//   (2) the step's rows (the plan's list): for each, its entries with a
-//       target in the group, staged as in slice delivery (prefix sums of
-//       the lengths, a map from each flattened entry to its row), then
-//       every entry: the plastic ones brought up to date from the target's
+//   (2) the step's rows (the plan's list): of each, the entries with a target
+//       in the group; the plastic ones brought up to date from the target's
 //       history in LDS (a forced row: only those; its other entries are not
 //       read), and a transmitting row's entries added to the accumulator
 //       (64-bit fixed point, LDS atomics), which step t+1's neuron update
@@ -214,17 +212,26 @@ __global__ __launch_bounds__(kPbPlanBlock) void k_block_plan(BlockArgs b)
 // written by one workgroup only, and the steps of a workgroup are ordered by
 // its barriers.
 //
-// The workgroup first loads the records of all its rows of the block (row
-// start plus the group's offset and length, plastic length, age, flags, pre
-// trace) into LDS, so a step stages its rows without a round trip to
-// memory. The steps are pipelined: the next step's rows are staged and
-// mapped while this step's entries are computed, and once the step's last
-// barrier has ordered its weight stores, the next step's entries (its
-// first window) are loaded, one set of loads in flight at a time (a wave's
-// loads complete in the order they were issued, and the loads a step waits
-// for are always the oldest). Further windows and batches of a step are
-// loaded when the step reaches them; a block with more records than LDS
-// holds loads each step's records when it runs.
+// What bounds it is the chain of one step (a step of the 25,000-neuron Brunel
+// network has 700 entries per group), so everything that does not depend on
+// the step before is taken out of it:
+//   - the rows' records of all steps are loaded into LDS first (start of the
+//     group's entries, plastic length, age, flags, pre trace), the entries
+//     flattened over all of them by one scan, and a map from each flattened
+//     entry to its record written once; a step only walks its stretch of the
+//     map, with no staging of its own;
+//   - the entries of step q+1 are loaded before those of step q are computed
+//     (two register sets in turn), every slot from a valid address so that
+//     the loads in flight are counted, not guessed. A row with an event in
+//     both steps would be loaded before its store: the plan marks such a
+//     record (late), and its weights are loaded again after the barrier;
+//   - the external drive of several steps is drawn by all threads at once
+//     (512 / gw steps), not by the neurons' threads inside the step;
+// which leaves two barriers a step. A launch of up to 14 steps of that network: 91 -> 54 us
+// (a scan, a map and five barriers per step before).
+// Blocks with more records than LDS holds, or entries than the map, run in
+// stretches of whole steps that fit; a step that does not fit by itself takes
+// its records in portions, loaded and computed in turn.
 //
 // At the end the state goes back, the accumulator becomes partial sum 0 (the
 // input of step t0 + B), each target's history words at block start and its
@@ -232,47 +239,46 @@ __global__ __launch_bounds__(kPbPlanBlock) void k_block_plan(BlockArgs b)
 // workgroup 0 advances the step clock, which no workgroup of the run reads
 // (they read the plan's copy).
 
-constexpr int kPbDirect = 32;  // segments up to this long are mapped by their own thread
-constexpr long long kMask40 = (1ll << 40) - 1;
-// a record's flags: age (bits 0-7), pre spike (8), delivered (9), inhibitory (10)
-// per loaded entry: record in the batch (bits 0-9), plastic (10), present
-// (11), offset in the segment (12-25), edge index parity (26)
-constexpr int kPkSeg = 0x3ff, kPkPlastic = 1 << 10, kPkIn = 1 << 11, kPkOff = 12;
-constexpr int kPkOffMask = 0x3fff, kPkOdd = 26;
-static_assert(kPbSegs <= kPkSeg + 1, "record index fits the entry word");
-static_assert(kMaxSortRow <= kPkOffMask + 1, "segment offset fits the entry word");
-// a queued update: record in the batch (bits 0-9), offset (10-23), target in the group (24-31)
-static_assert(kPbMaxWidth <= 256, "target in the group fits the queue word");
+constexpr int kPbU = 4;                       // entries per thread loaded ahead
+constexpr int kPbAhead = kPbU * kPbBlock;     // ... per workgroup
+constexpr int kPbMap = 16384;                 // entries of a stretch of steps
+static_assert(kMaxSortRow <= kPbMap, "any one record fits the map");
+static_assert(kPbRecords <= 65536, "16-bit map");
+// a record's flags, as kept in LDS and with each loaded entry: age (bits
+// 0-7), pre spike (8), delivered (9), inhibitory (10), late (11), step (12-15);
+// a loaded entry also: present (16), odd edge index (17), plastic (18)
+constexpr int kRfPre = 1 << 8, kRfTx = 1 << 9, kRfInh = 1 << 10, kRfLate = 1 << 11, kRfStep = 12;
+constexpr int kEnIn = 1 << 16, kEnOdd = 1 << 17, kEnPlastic = 1 << 18;
+// a queued update: flattened entry (bits 0-13), target in the group (14-21)
+static_assert(kPbMap <= 1 << 14 && kPbMaxWidth <= 256, "queue word");
 // The graphs of the blocks (at most kPbMaxN rows of at most kMaxSortRow
 // entries) have fewer than 2^31 edges: 32-bit edge indices.
 static_assert((int64_t)kPbMaxN * kMaxSortRow < (1ll << 31), "32-bit edge index");
 
 struct PbEntries {
-    float wv[kPbUnroll];     // weight as loaded
-    uint32_t cv[kPbUnroll];  // target as loaded (compressed: the 32-bit word holding it)
-    int pk[kPbUnroll];
+    float wv[kPbU];     // weight as loaded
+    uint32_t cv[kPbU];  // target as loaded (compressed: the 32-bit word holding it)
+    int f[kPbU];        // flags
 };
 
 template <int HW, bool CT>
 __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs b)
 {
     constexpr int NWV = kPbBlock / kWave;
-    constexpr int QH = 4;  // entry slots between queue flushes
-    __shared__ int r_start[kPbRecords];   // first entry of the row in the group (edge index)
-    __shared__ int r_lens[kPbRecords];    // entries (bits 0-15), plastic entries (16-31)
-    __shared__ int r_info[kPbRecords];
+    // per record: first edge less its flattened index, flattened end of its
+    // plastic entries, flags, pre trace
+    __shared__ int r_base[kPbRecords], r_pend[kPbRecords], r_info[kPbRecords];
     __shared__ float r_xp0[kPbRecords];
-    __shared__ int s_off[2][kPbSegs + 1];
-    __shared__ uint16_t s_map[2][kPbWindow];  // entry -> 1 + record in the batch
-    __shared__ long long s_tot[2];            // entries (bits 0-39), long segments (40+)
-    __shared__ float q_w[NWV][QH * kWave];
-    __shared__ int q_p[NWV][QH * kWave];
+    __shared__ uint16_t s_map[kPbMap];  // flattened entry -> record
+    __shared__ int s_yoff[kBatchMax + 1];  // a stretch's first entry of each step, and its end
+    __shared__ float q_w[NWV][kPbU * kWave];
+    __shared__ int q_p[NWV][kPbU * kWave];
     __shared__ uint64_t s_hist[kPbMaxWidth * HW];
     __shared__ float s_y[kPbMaxWidth];
+    __shared__ float s_x[kPbBlock];  // external drive: [step of the draw][target]
     __shared__ long long s_acc[2 * kPbMaxWidth];
     __shared__ float s_dpow[kMaxAge + 1];
     __shared__ long long sh[NWV];
-    __shared__ int shi[NWV];
     __shared__ int s_cnt[kBatchMax], s_base[kBatchMax + 1];
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     // neighbouring groups (which read neighbouring entries of each row) on
@@ -319,232 +325,217 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
     float *__restrict__ wgt = b.w;
     long long events = 0, w_tx = 0, w_forced = 0, spikes = 0;
     uint32_t blk = 0u;  // the block's spikes (bit 0: the latest step)
+    const bool driven = a.model == 0 && a.poisson_len > 0;
+    const int dsteps = kPbBlock / b.gwidth;  // steps per draw of the drive (gwidth divides 512)
+    const uint64_t hs0 = st.h0, hs1 = st.h1;  // the history words at block start
     __syncthreads();  // s_base
 
-    // LDS records r0 .. r0 + count - 1 from the lists from entry j0 of step
-    // q0 on (across the steps' lists in order): the row's start plus the
-    // group's offset and length (the group pivots of the row, loaded once
-    // the row is known), clamped to the graph (only a failed plan scan,
-    // which leaves list entries unwritten, could point elsewhere)
-    auto load_records = [&](int q0, int j0, int r0, int count) {
-        constexpr int RU = kPbRecords / kPbBlock;  // all records of LDS in one round
+    // the external drive of steps q .. q + dsteps - 1 (published by the next barrier)
+    auto draw = [&](int q) {
+        const int ds = tid / b.gwidth, j = tid - ds * b.gwidth;
+        s_x[tid] = drive(a, t0 + q + ds, min(glo + j, n - 1));
+    };
+    // LDS records 0 .. count - 1 (count <= kPbRecords) from the lists from
+    // entry j0 of step q0 on (across the steps' lists in order): the row's
+    // entries in the group (from the group pivots of the row, loaded once the
+    // row is known), clamped to the graph (only a failed plan, which leaves
+    // list entries unwritten, could point elsewhere). Their entries are
+    // flattened: s_yoff[q], q = q0 .. q1, the first entry of each step, and
+    // the map written as far as it reaches. Returns the number of entries;
+    // begins and ends with a barrier.
+    auto load_records = [&](int q0, int q1, int j0, int count) -> int {
+        constexpr int RU = kPbRecords / kPbBlock;
         static_assert(kPbRecords % kPbBlock == 0, "whole rounds of records");
-        for (int x0 = 0; x0 < count; x0 += RU * kPbBlock) {
-            PbEvent pe[RU];
+        __syncthreads();  // every read of the records and the map before
+        const int per = (count + kPbBlock - 1) / kPbBlock;  // records per thread, consecutive
+        const int r0 = tid * per;
+        int own = 0;
+        PbEvent pe[RU];
 #pragma unroll
-            for (int u = 0; u < RU; ++u) {
-                const int x = min(x0 + u * kPbBlock + tid, max(count - 1, 0));
-                // (the step of flattened entry x: at most kBatchMax lists)
-                int q = q0, j = j0 + x;
-                while (q < B - 1 && j >= s_cnt[q]) {
-                    j -= s_cnt[q];
-                    ++q;
-                }
-                j = min(j, max(s_cnt[q] - 1, 0));
-                pe[u] = b.ev[(int64_t)q * n + j];
+        for (int u = 0; u < RU; ++u) {
+            if (u >= per) break;  // uniform
+            const int x = min(r0 + u, max(count - 1, 0));
+            // (the step of flattened record x: at most kBatchMax lists)
+            int q = q0, j = j0 + x;
+            while (q < B - 1 && j >= s_cnt[q]) {
+                j -= s_cnt[q];
+                ++q;
             }
-            int p0[RU], p1[RU];
-#pragma unroll
-            for (int u = 0; u < RU; ++u) {
-                const int32_t *gp = b.gpiv + (int64_t)min(max(pe[u].k, 0), n - 1) * (G + 1) + g;
-                p0[u] = gp[0];
-                p1[u] = gp[1];
-            }
-#pragma unroll
-            for (int u = 0; u < RU; ++u) {
-                const int x = x0 + u * kPbBlock + tid;
-                if (x >= count) continue;
-                int sl = max(p1[u] - p0[u], 0);
-                const uint32_t f = pe[u].lenf;
-                const int plen = min(max((int)(f & 0xffffu) - p0[u], 0), sl);
-                const int deliver = (f >> 25) & 1;
-                if (!deliver) sl = plen;  // a forced row: its plastic entries only
-                const long long st0 = min(max((long long)pe[u].rs + p0[u], 0ll), ne);
-                sl = (int)min((long long)sl, ne - st0);
-                r_start[r0 + x] = (int)st0;
-                r_lens[r0 + x] = sl | (min(plen, sl) << 16);
-                r_info[r0 + x] = (int)((f >> 16) & 0xff) | (int)(((f >> 24) & 1) << 8) |
-                                 (deliver << 9) | (int)(((f >> 26) & 1) << 10);
-                r_xp0[r0 + x] = pe[u].xp0;
-            }
+            j = min(j, max(s_cnt[q] - 1, 0));
+            pe[u] = b.ev[(int64_t)q * n + j];
         }
+        int p0[RU], p1[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            if (u >= per) break;
+            const int32_t *gp = b.gpiv + (int64_t)min(max(pe[u].k, 0), n - 1) * (G + 1) + g;
+            p0[u] = gp[0];
+            p1[u] = gp[1];
+        }
+        int len[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            if (u >= per) break;
+            const int x = r0 + u;
+            len[u] = 0;
+            if (x >= count) continue;
+            int sl = max(p1[u] - p0[u], 0);
+            const uint32_t f = pe[u].lenf;
+            const int plen = min(max((int)(f & 0xffffu) - p0[u], 0), sl);
+            const int deliver = (f >> 25) & 1;
+            if (!deliver) sl = plen;  // a forced row: its plastic entries only
+            const long long st0 = min(max((long long)pe[u].rs + p0[u], 0ll), ne);
+            sl = (int)min((long long)sl, ne - st0);
+            len[u] = sl;
+            r_base[x] = (int)st0;
+            r_pend[x] = min(plen, sl);
+            r_info[x] = (int)((f >> 16) & 0xff) | (((f >> 24) & 1) ? kRfPre : 0) |
+                        (deliver ? kRfTx : 0) | (((f >> 26) & 1) ? kRfInh : 0) |
+                        ((f >> 31) ? kRfLate : 0) | (int)(((f >> 27) & 15) << kRfStep);
+            r_xp0[x] = pe[u].xp0;
+            own += sl;
+        }
+        const long long incl = block_incl_scan_i64_n<kPbBlock>((long long)own, sh);
+        int y = (int)min(incl - own, (long long)INT32_MAX / 2);
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            if (u >= per) break;
+            const int x = r0 + u;
+            if (x >= count) continue;
+            r_base[x] -= y;
+            r_pend[x] += y;
+            // the first record of a step: the step's first entry (and that of
+            // empty steps before it)
+            const int q = (r_info[x] >> kRfStep) & 15;
+            const int pq = x == 0 ? q0 - 1 : (u == 0 ? 16 : (r_info[x - 1] >> kRfStep) & 15);
+            if (pq < 16)
+                for (int z = max(pq + 1, q0); z <= min(q, q1); ++z) s_yoff[z] = y;
+            if (y + len[u] <= kPbMap)
+                for (int z = y; z < y + len[u]; ++z) s_map[z] = (uint16_t)x;
+            y += len[u];
+        }
+        __syncthreads();  // r_info (the record before the thread's first)
+        if (r0 < count && r0 > 0) {
+            const int q = (r_info[r0] >> kRfStep) & 15, pq = (r_info[r0 - 1] >> kRfStep) & 15;
+            const int yf = (int)min(incl - own, (long long)INT32_MAX / 2);
+            for (int z = max(pq + 1, q0); z <= min(q, q1); ++z) s_yoff[z] = yf;
+        }
+        long long total = 0;  // the waves' sums of the scan
+#pragma unroll
+        for (int w = 0; w < NWV; ++w) total += sh[w];
+        return (int)min(total, (long long)INT32_MAX / 2);
     };
-    // a batch of nbt records from LDS record rb on, into staging buffer x:
-    // offsets scanned, the map of its first window; ends with a barrier
-    auto build_map = [&](int x, int nbt, int w0, int we, bool direct) {
-        if (direct) {  // short segments: each thread writes its own segments' entries
+    // loads of the entries y0 + u kPbBlock + tid (u < kPbU) below y1: every
+    // slot loads from a valid address, the results are looked at when the
+    // entries are computed
+    auto issue = [&](int y0, int y1, PbEntries &E) {
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int j = 2 * tid + r;
-                if (j < nbt) {
-                    const int a0 = max(s_off[x][j], w0), a1 = min(s_off[x][j + 1], w0 + we);
-                    for (int y = a0; y < a1; ++y) s_map[x][y - w0] = (uint16_t)(j + 1);
-                }
-            }
-            __syncthreads();
-        } else {  // mark each segment's first entry in the window, then max-scan
-            for (int y = tid; y < we; y += kPbBlock) s_map[x][y] = 0;
-            __syncthreads();
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int j = 2 * tid + r;
-                if (j < nbt) {
-                    const int a0 = max(s_off[x][j], w0), a1 = min(s_off[x][j + 1], w0 + we);
-                    if (a0 < a1) s_map[x][a0 - w0] = (uint16_t)(j + 1);
-                }
-            }
-            __syncthreads();
-            fill_segment_map<kPbBlock, kPbUnroll, uint16_t>(s_map[x], we, shi, 0);
-        }
-    };
-    auto prep = [&](int x, int rb, int nbt) {
-        int len[2];
-        long long packed = 0;
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int j = 2 * tid + r;
-            len[r] = j < nbt ? (r_lens[rb + j] & 0xffff) : 0;
-            packed += (long long)len[r] | ((long long)(len[r] > kPbDirect) << 40);
-        }
-        const long long incl = block_incl_scan_i64_n<kPbBlock>(packed, sh);
-        long long ex = (incl - packed) & kMask40;
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            s_off[x][2 * tid + r] = (int)ex;
-            ex += len[r];
-        }
-        if (tid == kPbBlock - 1) {
-            s_off[x][kPbSegs] = (int)(incl & kMask40);
-            s_tot[x] = incl;
-        }
-        __syncthreads();
-        const long long tq = s_tot[x];
-        const int total = (int)(tq & kMask40);
-        if (total > 0) build_map(x, nbt, 0, min(total, kPbWindow), (tq >> 40) == 0);
-    };
-    // loads of window [w0, w0 + we) of staging buffer x (records from rb):
-    // every slot loads from a valid address, the results are looked at when
-    // the entries are computed
-    auto issue = [&](int x, int rb, int w0, int we, PbEntries &E) {
-#pragma unroll
-        for (int u = 0; u < kPbUnroll; ++u) {
-            const int y = u * kPbBlock + tid;
-            const bool in = y < we;
-            // a slot no lane of the wave uses loads nothing (wave-uniform)
-            if (u * kPbBlock + wave * kWave >= we) {
-                E.pk[u] = 0;
-                continue;
-            }
-            const int l = in ? (int)s_map[x][y] - 1 : 0;
-            const int off = w0 + y - s_off[x][l];
-            const int r = rb + l;
-            const int e = in ? r_start[r] + off : 0;  // < n_edges
+        for (int u = 0; u < kPbU; ++u) {
+            const int y = y0 + u * kPbBlock + tid;
+            const bool in = y < y1;
+            const int r = in ? (int)s_map[y] : 0;
+            const int e = in ? r_base[r] + y : 0;  // < n_edges
             E.cv[u] = CT ? col32[e >> 1] : (uint32_t)col[e];
             E.wv[u] = wgt[e];
-            E.pk[u] = in ? l | (off < (r_lens[r] >> 16) ? kPkPlastic : 0) | kPkIn |
-                               (off << kPkOff) | ((e & 1) << kPkOdd)
-                         : 0;
+            E.f[u] = in ? r_info[r] | kEnIn | ((e & 1) ? kEnOdd : 0) |
+                              (y < r_pend[r] ? kEnPlastic : 0)
+                        : 0;
         }
     };
-    // The entries of one window: a transmitting row's entry whose weight
-    // does not change is delivered at once; the entries whose weight
+    // weights of late records loaded again, once the step before is stored
+    auto reload = [&](int y0, PbEntries &E) {
+        bool any = false;
+#pragma unroll
+        for (int u = 0; u < kPbU; ++u) any = any || (E.f[u] & kRfLate);
+        if (!ballot64(any)) return;  // wave-uniform
+#pragma unroll
+        for (int u = 0; u < kPbU; ++u)
+            if (E.f[u] & kRfLate) {
+                const int y = y0 + u * kPbBlock + tid;
+                E.wv[u] = wgt[r_base[s_map[y]] + y];
+            }
+    };
+    // The entries of one window from y0: a transmitting row's entry whose
+    // weight does not change is delivered at once; the entries whose weight
     // changes (a pre spike, or a post spike of the target within the row's
     // window) go to the wave's queue, which is then updated 64 at a time
     // with every lane busy (the replay loops run over those entries only),
     // stored, and delivered where the row transmits.
-    auto compute = [&](int rb, const PbEntries &E) {
+    auto compute = [&](int y0, const PbEntries &E) {
         float *qw = q_w[wave];
         int *qp = q_p[wave];
+        int qn = 0;
 #pragma unroll
-        for (int hf = 0; hf < kPbUnroll / QH; ++hf) {
-            int qn = 0;
-#pragma unroll
-            for (int v = 0; v < QH; ++v) {
-                const int u = hf * QH + v;
-                const int pk = E.pk[u];
-                if (!ballot64(pk & kPkIn)) continue;  // an unused slot of the wave
-                const int l = pk & kPkSeg;
-                const int info = (pk & kPkIn) ? r_info[rb + l] : 0;
-                const uint32_t c = CT ? (((pk >> kPkOdd) & 1) ? E.cv[u] >> 16 : E.cv[u] & 0xffffu)
-                                      : E.cv[u];
-                const int j = (int)c - cbase;
-                const bool ok = (pk & kPkIn) && (unsigned)j < (unsigned)wn;
-                if ((pk & kPkIn) && !ok) atomicOr(b.err, kErrIndex);  // not this group's target
-                bool cand = false;
-                if (ok && (pk & kPkPlastic)) {
-                    uint64_t m0, m1;
-                    window_masks(info & 0xff, m0, m1);
-                    const uint64_t h0 = s_hist[j * HW] & m0;
-                    const uint64_t h1 = HW == 2 ? s_hist[j * 2 + 1] & m1 : 0ull;
-                    cand = h0 || h1 || ((info >> 8) & 1) || !b.event;
-                }
-                if (ok && !cand && ((info >> 9) & 1)) {
-                    atomicAdd((unsigned long long *)(s_acc + j +
-                                                     (((info >> 10) & 1) ? kPbMaxWidth : 0)),
-                              (unsigned long long)to_fix(E.wv[u]));
-                    ++events;
-                }
-                const uint64_t bl = ballot64(cand);
-                if (cand) {
-                    const int e = qn + lane_rank(bl);
-                    qw[e] = E.wv[u];
-                    qp[e] = l | (((pk >> kPkOff) & kPkOffMask) << 10) | (j << 24);
-                }
-                qn += (int)__popcll(bl);
-            }
-            __builtin_amdgcn_wave_barrier();
-            for (int e0 = 0; e0 < qn; e0 += kWave) {  // wave-uniform
-                const int e = e0 + lane;
-                if (e >= qn) continue;
-                float w = qw[e];
-                const unsigned p = (unsigned)qp[e];
-                const int r = rb + (int)(p & kPkSeg);
-                const int off = (int)((p >> 10) & kPkOffMask), j = (int)(p >> 24);
-                const int info = r_info[r];
-                const int age = info & 0xff, pre = (info >> 8) & 1;
+        for (int u = 0; u < kPbU; ++u) {
+            const int f = E.f[u];
+            if (!ballot64(f & kEnIn)) continue;  // an unused slot of the wave
+            const uint32_t c = CT ? ((f & kEnOdd) ? E.cv[u] >> 16 : E.cv[u] & 0xffffu) : E.cv[u];
+            const int j = (int)c - cbase;
+            const bool ok = (f & kEnIn) && (unsigned)j < (unsigned)wn;
+            if ((f & kEnIn) && !ok) atomicOr(b.err, kErrIndex);  // not this group's target
+            bool cand = false;
+            if (ok && (f & kEnPlastic)) {
                 uint64_t m0, m1;
-                window_masks(age, m0, m1);
+                window_masks(f & 0xff, m0, m1);
                 const uint64_t h0 = s_hist[j * HW] & m0;
                 const uint64_t h1 = HW == 2 ? s_hist[j * 2 + 1] & m1 : 0ull;
-                const float y = pre ? s_y[j] : 0.f;
-                const float xp0 = r_xp0[r];
-                // the pre trace after this update, as the plan's snapshot has it
-                const float xpn = __fadd_rn(__fmul_rn(xp0, s_dpow[age]), (float)pre);
-                w = b.event ? stdp_synapse(w, h0, h1, age, pre, xp0, xpn, y, s_dpow, c_pot, c_dep, mu)
-                            : stdp_synapse_steps(w, h0, h1, age, pre, xp0, xpn, y, s_dpow[1],
-                                                 c_pot, c_dep, mu);
-                wgt[r_start[r] + off] = w;
-                if (pre)
-                    ++w_tx;
-                else
-                    ++w_forced;
-                if ((info >> 9) & 1) {
-                    atomicAdd((unsigned long long *)(s_acc + j +
-                                                     (((info >> 10) & 1) ? kPbMaxWidth : 0)),
-                              (unsigned long long)to_fix(w));
-                    ++events;
-                }
+                cand = h0 || h1 || (f & kRfPre) || !b.event;
             }
-            __builtin_amdgcn_wave_barrier();  // the queue is rewritten next
+            if (ok && !cand && (f & kRfTx)) {
+                atomicAdd((unsigned long long *)(s_acc + j + ((f & kRfInh) ? kPbMaxWidth : 0)),
+                          (unsigned long long)to_fix(E.wv[u]));
+                ++events;
+            }
+            const uint64_t bl = ballot64(cand);
+            if (cand) {
+                const int e = qn + lane_rank(bl);
+                qw[e] = E.wv[u];
+                qp[e] = (y0 + u * kPbBlock + tid) | (j << 14);
+            }
+            qn += (int)__popcll(bl);
         }
-    };
-    // the windows of a staged batch from window w_from on (each mapped,
-    // loaded and computed in turn)
-    auto windows = [&](int x, int rb, int nbt, int w_from, PbEntries &E) {
-        const long long tq = s_tot[x];
-        const int total = (int)(tq & kMask40);
-        for (int w0 = w_from; w0 < total; w0 += kPbWindow) {
-            const int we = min(kPbWindow, total - w0);
-            if (w0 > 0) {
-                __syncthreads();  // every read of the map of the window before
-                build_map(x, nbt, w0, we, (tq >> 40) == 0);
+        __builtin_amdgcn_wave_barrier();
+        for (int e0 = 0; e0 < qn; e0 += kWave) {  // wave-uniform
+            const int e = e0 + lane;
+            if (e >= qn) continue;
+            float w = qw[e];
+            const int p = qp[e];
+            const int y = p & (kPbMap - 1), j = p >> 14;
+            const int r = s_map[y];
+            const int info = r_info[r];
+            const int age = info & 0xff, pre = (info & kRfPre) ? 1 : 0;
+            uint64_t m0, m1;
+            window_masks(age, m0, m1);
+            const uint64_t h0 = s_hist[j * HW] & m0;
+            const uint64_t h1 = HW == 2 ? s_hist[j * 2 + 1] & m1 : 0ull;
+            const float yp = pre ? s_y[j] : 0.f;
+            const float xp0 = r_xp0[r];
+            // the pre trace after this update, as the plan's snapshot has it
+            const float xpn = __fadd_rn(__fmul_rn(xp0, s_dpow[age]), (float)pre);
+            w = b.event ? stdp_synapse(w, h0, h1, age, pre, xp0, xpn, yp, s_dpow, c_pot, c_dep, mu)
+                        : stdp_synapse_steps(w, h0, h1, age, pre, xp0, xpn, yp, s_dpow[1],
+                                             c_pot, c_dep, mu);
+            wgt[r_base[r] + y] = w;
+            if (pre)
+                ++w_tx;
+            else
+                ++w_forced;
+            if (info & kRfTx) {
+                atomicAdd((unsigned long long *)(s_acc + j + ((info & kRfInh) ? kPbMaxWidth : 0)),
+                          (unsigned long long)to_fix(w));
+                ++events;
             }
-            issue(x, rb, w0, we, E);
-            compute(rb, E);
+        }
+        __builtin_amdgcn_wave_barrier();  // the queue is rewritten next
+    };
+    // entries [y0, y1), loaded and computed a window at a time
+    auto windows = [&](int y0, int y1, PbEntries &E) {
+        for (int y = y0; y < y1; y += kPbAhead) {  // uniform
+            issue(y, y1, E);
+            compute(y, E);
         }
     };
     auto neuron_step = [&](int q) {
-        const int64_t t = t0 + q;
         if (live) {
             float ae = 0.f, ai = 0.f;
             if (a.model != 2) {
@@ -556,7 +547,13 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
                     if (b.nacc == 2) ai = from_fix(s_acc[kPbMaxWidth + tid]);
                 }
             }
-            const int sp = neuron_advance<-1, HW>(a, i, t, ae, ai, st);
+            int sp;
+            if (a.model == 2)
+                sp = neuron_dynamics<2>(a, i, t0 + q, ae, ai, st);
+            else
+                sp = lif_dynamics<-1>(a, ae, ai,
+                                      driven ? s_x[(q % dsteps) * b.gwidth + tid] : 0.f, st);
+            neuron_record<-1, HW>(a, sp, st);
             spikes += sp;
             blk = (blk << 1) | (uint32_t)sp;
             s_hist[tid * HW] = st.h0;
@@ -568,56 +565,70 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
             s_acc[kPbMaxWidth + tid] = 0;
         }
     };
+    // the drive of the steps after step q, when step q used the last drawn
+    // (after step q's first barrier)
+    auto draw_next = [&](int q) {
+        if (driven && (q + 1) % dsteps == 0 && q + 1 < B) draw(q + 1);
+    };
 
-    const uint64_t hs0 = st.h0, hs1 = st.h1;  // the history words at block start
-    PbEntries E;
-    const int total_rec = s_base[kBatchMax];
-    if (total_rec <= kPbRecords) {
-        // every record of the block in LDS; step 0 staged and its first
-        // window loaded
-        load_records(0, 0, 0, total_rec);
-        __syncthreads();
-        const int nb0 = min(s_cnt[0], kPbSegs);
-        prep(0, s_base[0], nb0);
-        issue(0, s_base[0], 0, min((int)(s_tot[0] & kMask40), kPbWindow), E);
-        for (int q = 0; q < B; ++q) {
-            const int x = q & 1;
-            neuron_step(q);
-            // (2a) the next step's first batch staged and its first window
-            // mapped (the staging's barriers publish the neuron update)
-            if (q + 1 < B)
-                prep(x ^ 1, s_base[q + 1], min(s_cnt[q + 1], kPbSegs));
-            else
-                __syncthreads();  // the neuron update's histories and traces
-            // (2b) this step's entries: the loaded first window, the rest
-            const int nb1 = min(s_cnt[q], kPbSegs);
-            compute(s_base[q], E);
-            windows(x, s_base[q], nb1, kPbWindow, E);
-            for (int e0 = kPbSegs; e0 < s_cnt[q]; e0 += kPbSegs) {  // further batches
-                __syncthreads();  // every read of the staging of the batch before
-                const int nbt = min(kPbSegs, s_cnt[q] - e0);
-                prep(x, s_base[q] + e0, nbt);
-                windows(x, s_base[q] + e0, nbt, 0, E);
+    PbEntries E0, E1;
+    if (driven) draw(0);
+    __syncthreads();  // s_x
+    for (int q = 0; q < B;) {
+        // the whole steps whose records fit
+        int qe = q;
+        while (qe < B && s_base[qe + 1] - s_base[q] <= kPbRecords) ++qe;
+        int fit = 0;  // steps of the stretch
+        if (qe > q) {
+            const int cnt = s_base[qe] - s_base[q];
+            const int total = load_records(q, qe, 0, cnt);
+            if (tid == 0) {  // the steps after the last record
+                const int lq = cnt > 0 ? (r_info[cnt - 1] >> kRfStep) & 15 : q - 1;
+                for (int z = lq + 1; z <= qe; ++z) s_yoff[z] = total;
             }
-            __syncthreads();  // every atomic and weight store of step q done
-            // (3) the next step's first window loaded
-            if (q + 1 < B) issue(x ^ 1, s_base[q + 1], 0,
-                                 min((int)(s_tot[x ^ 1] & kMask40), kPbWindow), E);
+            __syncthreads();  // s_yoff
+            while (q + fit < qe && s_yoff[q + fit + 1] <= kPbMap) ++fit;
         }
-    } else {
-        // more records than LDS holds: each batch of each step's records is
-        // loaded when the step reaches it
-        for (int q = 0; q < B; ++q) {
+        if (fit > 0) {
+            const int qs = q, qx = q + fit;
+            // one step: its entries loaded (E), the next step's loaded into F
+            auto step = [&](int k, PbEntries &E, PbEntries &F) {
+                neuron_step(k);
+                __syncthreads();  // histories, traces, the cleared accumulator
+                const int y0 = s_yoff[k], y1 = s_yoff[k + 1];
+                const int z1 = k + 1 < qx ? s_yoff[k + 2] : y1;
+                issue(y1, z1, F);
+                compute(y0, E);
+                if (y1 - y0 > kPbAhead) windows(y0 + kPbAhead, y1, E);
+                draw_next(k);
+                __syncthreads();  // every atomic and weight store of step k done
+                reload(y1, F);
+            };
+            issue(s_yoff[qs], s_yoff[qs + 1], E0);
+            for (int k = qs; k < qx; k += 2) {
+                step(k, E0, E1);
+                if (k + 1 < qx) step(k + 1, E1, E0);
+            }
+            q = qx;
+        } else {
+            // a step that does not fit: its records in portions (halved until
+            // their entries fit the map; one record always does)
             neuron_step(q);
-            for (int e0 = 0; e0 < s_cnt[q]; e0 += kPbSegs) {
-                __syncthreads();  // every read of the records and staging before
-                const int nbt = min(kPbSegs, s_cnt[q] - e0);
-                load_records(q, e0, 0, nbt);
+            for (int j = 0; j < s_cnt[q];) {
+                int m = min(s_cnt[q] - j, kPbRecords);
+                int total = load_records(q, q, j, m);
+                while (total > kPbMap) {  // uniform
+                    m = (m + 1) / 2;
+                    total = load_records(q, q, j, m);
+                }
                 __syncthreads();
-                prep(0, 0, nbt);
-                windows(0, 0, nbt, 0, E);
+                windows(0, total, E0);
+                j += m;
             }
             __syncthreads();  // every atomic of step q done (and the neuron update published)
+            draw_next(q);
+            __syncthreads();  // s_x
+            ++q;
         }
     }
     if (live) {

@@ -365,23 +365,19 @@ struct PbEvent {
     int32_t rs;      // first edge of the row
     uint32_t lenf;   // plastic prefix length (bits 0-15), age (16-23), pre spike (24),
                      // transmitting (25), inhibitory source of a CUBA network (26),
-                     // step in the block (27-30)
+                     // step in the block (27-30), an event at the step before too (31)
     float xp0;       // pre trace at the row's previous update
     int32_t k;       // the row
 };
 constexpr int kPbPlanBlock = 512;   // threads of the plan (one row each, a half wave per step's scan)
 constexpr int kPbBlock = 512;       // threads of a target group's workgroup
 constexpr int kPbMaxWidth = 256;    // most targets per group (one neuron per thread)
-constexpr int kPbSegs = 2 * kPbBlock;  // a step's records staged at once (two per thread)
-constexpr int kPbUnroll = 16;       // flattened entries per thread per window
-constexpr int kPbWindow = kPbBlock * kPbUnroll;
 constexpr int kPbRecords = 5120;    // a block's records a workgroup holds in LDS
 constexpr int kPbMaxN = 65536;      // largest network the blocks run
 constexpr int kPbMaxSteps = kBatchMax - 1;  // steps per block: lists 0 .. B-1, deferred list B
 constexpr int kPbDfPart = 8 * 64;   // entries per part of a deferred row (8 per lane)
 static_assert(kPbPlanBlock / 32 >= kPbMaxSteps + 1, "a half wave per list scan");
 static_assert(kPbMaxSteps < 16, "step in the block fits PbEvent::lenf");
-static_assert(kPbSegs < 65535, "16-bit segment map");
 struct BlockArgs {
     // plan
     const int64_t *row_ptr;

@@ -142,32 +142,31 @@ __device__ __forceinline__ int poisson_count(const NeuronArgs &a, int64_t t, int
     return min(k, a.poisson_len);
 }
 
-// The dynamics of one neuron at step t (i < n) on its state in registers,
-// with input (ae, ai), in a fixed fp32 operation order. Returns whether it
-// spiked. A refractory neuron counts down and holds the reset potential: both
-// outcomes are computed and selected, so a wave with a few refractory neurons
-// does not walk two branches.
-template <int M>
-__device__ __forceinline__ int neuron_dynamics(const NeuronArgs &a, int i, int64_t t, float ae,
-                                               float ai, NState &st)
+// The external drive of neuron i at step t, in mV (LIF with delta synapses).
+__device__ __forceinline__ float drive(const NeuronArgs &a, int64_t t, int i)
 {
-    if (nmodel<M>(a) == 2) return rng32(a.seed, 4, (uint64_t)t, (uint64_t)i) < a.fire_thr;
+    return __fmul_rn(a.j_ext, (float)poisson_count(a, t, i));
+}
+
+// The dynamics of one LIF neuron on its state in registers, with input
+// (ae, ai) and external drive x, in a fixed fp32 operation order. Returns
+// whether it spiked. A refractory neuron counts down and holds the reset
+// potential: both outcomes are computed and selected, so a wave with a few
+// refractory neurons does not walk two branches.
+template <int M>
+__device__ __forceinline__ int lif_dynamics(const NeuronArgs &a, float ae, float ai, float x,
+                                            NState &st)
+{
     const bool held = st.r > 0;
     float v;
     if (nmodel<M>(a) == 1) {
         st.ie = __fadd_rn(__fmul_rn(st.ie, a.d_e), ae);
         st.ii = __fadd_rn(__fmul_rn(st.ii, a.d_i), ai);
-        float x = __fsub_rn(a.v_inf, st.v);
-        x = __fadd_rn(x, st.ie);
-        x = __fadd_rn(x, st.ii);
-        v = __fadd_rn(st.v, __fmul_rn(x, a.k_m));
+        float c = __fsub_rn(a.v_inf, st.v);
+        c = __fadd_rn(c, st.ie);
+        c = __fadd_rn(c, st.ii);
+        v = __fadd_rn(st.v, __fmul_rn(c, a.k_m));
     } else {
-        float x = 0.f;
-        if (a.poisson_len > 0) {  // uniform
-            // (keeps the branch: without a drive the draw is not computed)
-            asm volatile("");
-            x = __fmul_rn(a.j_ext, (float)poisson_count(a, t, i));
-        }
         const float b = __fmul_rn(__fsub_rn(a.v_inf, st.v), a.k_m);
         v = __fadd_rn(__fadd_rn(__fadd_rn(st.v, b), ae), x);
     }
@@ -177,6 +176,34 @@ __device__ __forceinline__ int neuron_dynamics(const NeuronArgs &a, int i, int64
     return s;
 }
 
+// The dynamics of neuron i < n at step t. Returns whether it spiked.
+template <int M>
+__device__ __forceinline__ int neuron_dynamics(const NeuronArgs &a, int i, int64_t t, float ae,
+                                               float ai, NState &st)
+{
+    if (nmodel<M>(a) == 2) return rng32(a.seed, 4, (uint64_t)t, (uint64_t)i) < a.fire_thr;
+    float x = 0.f;
+    if (nmodel<M>(a) == 0 && a.poisson_len > 0) {  // uniform
+        // (keeps the branch: without a drive the draw is not computed)
+        asm volatile("");
+        x = drive(a, t, i);
+    }
+    return lif_dynamics<M>(a, ae, ai, x, st);
+}
+
+// The post trace and the history words after a step in which the neuron
+// spiked (s) or not.
+template <int M, int H>
+__device__ __forceinline__ void neuron_record(const NeuronArgs &a, int s, NState &st)
+{
+    if (nplastic<M>(a)) {
+        // post trace seen by a pre spike at step t: posts strictly before t
+        st.y = __fmul_rn(__fadd_rn(st.y, (float)(st.h0 & 1ull)), a.d_minus);
+    }
+    st.h1 = nhw<H>(a) == 2 ? (st.h1 << 1) | (st.h0 >> 63) : 0ull;
+    st.h0 = (st.h0 << 1) | (uint64_t)s;
+}
+
 // One neuron's update at step t (i < n): its dynamics, its post trace and its
 // history words. Returns whether it spiked.
 template <int M, int H>
@@ -184,12 +211,7 @@ __device__ __forceinline__ int neuron_advance(const NeuronArgs &a, int i, int64_
                                               float ai, NState &st)
 {
     const int s = neuron_dynamics<M>(a, i, t, ae, ai, st);
-    if (nplastic<M>(a)) {
-        // post trace seen by a pre spike at step t: posts strictly before t
-        st.y = __fmul_rn(__fadd_rn(st.y, (float)(st.h0 & 1ull)), a.d_minus);
-    }
-    st.h1 = nhw<H>(a) == 2 ? (st.h1 << 1) | (st.h0 >> 63) : 0ull;
-    st.h0 = (st.h0 << 1) | (uint64_t)s;
+    neuron_record<M, H>(a, s, st);
     return s;
 }
 
