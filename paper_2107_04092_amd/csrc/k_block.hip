@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kPbPlanBlock) void k_block_plan(BlockArgs b)
 //     record (late), and its weights are loaded again after the barrier;
 //   - the external drive of several steps is drawn by all threads at once
 //     (512 / gw steps), not by the neurons' threads inside the step;
-// which leaves two barriers a step. A launch of up to 14 steps of that network: 91 -> 54 us
+// which leaves two barriers a step. A launch of up to 14 steps of that network: 91 -> 49 us
 // (a scan, a map and five barriers per step before).
 // Blocks with more records than LDS holds, or entries than the map, run in
 // stretches of whole steps that fit; a step that does not fit by itself takes
@@ -243,14 +243,13 @@ constexpr int kPbU = 4;                       // entries per thread loaded ahead
 constexpr int kPbAhead = kPbU * kPbBlock;     // ... per workgroup
 constexpr int kPbMap = 16384;                 // entries of a stretch of steps
 static_assert(kMaxSortRow <= kPbMap, "any one record fits the map");
-static_assert(kPbRecords <= 65536, "16-bit map");
+static_assert(kPbRecords < 65536, "16-bit map (1 + record, 0: none)");
+static_assert(kPbMap % (8 * kPbBlock) == 0, "whole 16-byte words per thread");
 // a record's flags, as kept in LDS and with each loaded entry: age (bits
 // 0-7), pre spike (8), delivered (9), inhibitory (10), late (11), step (12-15);
 // a loaded entry also: present (16), odd edge index (17), plastic (18)
 constexpr int kRfPre = 1 << 8, kRfTx = 1 << 9, kRfInh = 1 << 10, kRfLate = 1 << 11, kRfStep = 12;
 constexpr int kEnIn = 1 << 16, kEnOdd = 1 << 17, kEnPlastic = 1 << 18;
-// a queued update: flattened entry (bits 0-13), target in the group (14-21)
-static_assert(kPbMap <= 1 << 14 && kPbMaxWidth <= 256, "queue word");
 // The graphs of the blocks (at most kPbMaxN rows of at most kMaxSortRow
 // entries) have fewer than 2^31 edges: 32-bit edge indices.
 static_assert((int64_t)kPbMaxN * kMaxSortRow < (1ll << 31), "32-bit edge index");
@@ -259,7 +258,12 @@ struct PbEntries {
     float wv[kPbU];     // weight as loaded
     uint32_t cv[kPbU];  // target as loaded (compressed: the 32-bit word holding it)
     int f[kPbU];        // flags
+    int e[kPbU];        // edge
+    float xp0[kPbU];    // pre trace at the row's previous update
 };
+// a queued update: weight, edge, pre trace (as bits), flags with the target in
+// the group in bits 24-31
+static_assert(kEnPlastic < 1 << 24 && kPbMaxWidth <= 256, "queue word");
 
 template <int HW, bool CT>
 __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs b)
@@ -269,16 +273,16 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
     // plastic entries, flags, pre trace
     __shared__ int r_base[kPbRecords], r_pend[kPbRecords], r_info[kPbRecords];
     __shared__ float r_xp0[kPbRecords];
-    __shared__ uint16_t s_map[kPbMap];  // flattened entry -> record
+    __shared__ __align__(16) uint16_t s_map[kPbMap];  // flattened entry -> record
     __shared__ int s_yoff[kBatchMax + 1];  // a stretch's first entry of each step, and its end
-    __shared__ float q_w[NWV][kPbU * kWave];
-    __shared__ int q_p[NWV][kPbU * kWave];
+    __shared__ int4 s_q[NWV][kPbU * kWave];
     __shared__ uint64_t s_hist[kPbMaxWidth * HW];
     __shared__ float s_y[kPbMaxWidth];
     __shared__ float s_x[kPbBlock];  // external drive: [step of the draw][target]
     __shared__ long long s_acc[2 * kPbMaxWidth];
     __shared__ float s_dpow[kMaxAge + 1];
     __shared__ long long sh[NWV];
+    __shared__ int shi[NWV];
     __shared__ int s_cnt[kBatchMax], s_base[kBatchMax + 1];
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     // neighbouring groups (which read neighbouring entries of each row) on
@@ -294,31 +298,33 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
     const bool live = tid < wn;
     const int B = b.steps;
     const long long ne = (long long)b.n_edges;
-    // the neuron state and the input of the first step (both in flight
-    // while the block clock is read)
+    // the lists' lengths, the neuron state, the input of the first step and
+    // the block clock: every load out before any is looked at
+    static_assert(kBatchMax <= kWave, "one list per lane");
+    const int cnt_l = b.ev_cnt[min(lane, kBatchMax - 1)];
+    const int ic = live ? i : glo;
     NState st = {};
     float ae0 = 0.f, ai0 = 0.f;
-    const BlockClock bc = *b.bclk;
-    const int64_t t0 = bc.t0;
-    if (live) {
-        InputLoads in0;
-        nstate_load<-1, HW>(a, i, st);
-        if (a.model != 2) {
-            input_issue(a, i, in0);
-            input_combine(a, in0, bc.input_forced, bc.n_parts, i, ae0, ai0);
-        }
-    }
-    if (tid < kBatchMax) s_cnt[tid] = tid < B ? min(max(b.ev_cnt[tid], 0), n) : 0;
+    InputLoads in0;
+    nstate_load<-1, HW>(a, ic, st);
+    if (a.model != 2) input_issue(a, ic, in0);
+    BlockClock bc;  // (vector loads, as in load_clock)
+    bc.t0 = __hip_atomic_load(&b.bclk->t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bc.input_forced =
+        __hip_atomic_load(&b.bclk->input_forced, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bc.n_parts = __hip_atomic_load(&b.bclk->n_parts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int q = tid; q <= kMaxAge; q += kPbBlock) s_dpow[q] = b.dpow[q];
-    __syncthreads();  // s_cnt
-    if (tid == 0) {
-        int acc = 0;
-        for (int q = 0; q < kBatchMax; ++q) {
-            s_base[q] = acc;
-            acc += s_cnt[q];
+    {
+        const int c = lane < B ? min(max(cnt_l, 0), n) : 0;
+        const int upto = wave_incl_scan(c, 0, AddOp{});
+        if (wave == 0 && lane < kBatchMax) {
+            s_cnt[lane] = c;
+            s_base[lane + 1] = upto;
+            if (lane == 0) s_base[0] = 0;
         }
-        s_base[kBatchMax] = acc;
     }
+    const int64_t t0 = bc.t0;
+    if (a.model != 2) input_combine(a, in0, bc.input_forced, bc.n_parts, ic, ae0, ai0);
     const float c_pot = b.c_pot, c_dep = b.c_dep, mu = b.mu;
     const int32_t *__restrict__ col = b.col;
     const uint32_t *__restrict__ col32 = reinterpret_cast<const uint32_t *>(b.col16);
@@ -326,13 +332,14 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
     long long events = 0, w_tx = 0, w_forced = 0, spikes = 0;
     uint32_t blk = 0u;  // the block's spikes (bit 0: the latest step)
     const bool driven = a.model == 0 && a.poisson_len > 0;
-    const int dsteps = kPbBlock / b.gwidth;  // steps per draw of the drive (gwidth divides 512)
+    const int gsh = 31 - __clz(b.gwidth);  // gwidth is 64, 128 or 256
+    const int dsteps = kPbBlock >> gsh;    // steps per draw of the drive
     const uint64_t hs0 = st.h0, hs1 = st.h1;  // the history words at block start
     __syncthreads();  // s_base
 
     // the external drive of steps q .. q + dsteps - 1 (published by the next barrier)
     auto draw = [&](int q) {
-        const int ds = tid / b.gwidth, j = tid - ds * b.gwidth;
+        const int ds = tid >> gsh, j = tid & (b.gwidth - 1);
         s_x[tid] = drive(a, t0 + q + ds, min(glo + j, n - 1));
     };
     // LDS records 0 .. count - 1 (count <= kPbRecords) from the lists from
@@ -341,8 +348,8 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
     // row is known), clamped to the graph (only a failed plan, which leaves
     // list entries unwritten, could point elsewhere). Their entries are
     // flattened: s_yoff[q], q = q0 .. q1, the first entry of each step, and
-    // the map written as far as it reaches. Returns the number of entries;
-    // begins and ends with a barrier.
+    // the map written as far as it reaches (read after the next barrier).
+    // Returns the number of entries; begins with a barrier.
     auto load_records = [&](int q0, int q1, int j0, int count) -> int {
         constexpr int RU = kPbRecords / kPbBlock;
         static_assert(kPbRecords % kPbBlock == 0, "whole rounds of records");
@@ -350,20 +357,28 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
         const int per = (count + kPbBlock - 1) / kPbBlock;  // records per thread, consecutive
         const int r0 = tid * per;
         int own = 0;
+        int sb[kBatchMax];  // first record of the steps after q0's, from the first one loaded
+#pragma unroll
+        for (int z = 0; z < kBatchMax; ++z) sb[z] = s_base[z + 1] - s_base[q0] - j0;
         PbEvent pe[RU];
 #pragma unroll
         for (int u = 0; u < RU; ++u) {
             if (u >= per) break;  // uniform
             const int x = min(r0 + u, max(count - 1, 0));
-            // (the step of flattened record x: at most kBatchMax lists)
-            int q = q0, j = j0 + x;
-            while (q < B - 1 && j >= s_cnt[q]) {
-                j -= s_cnt[q];
-                ++q;
-            }
-            j = min(j, max(s_cnt[q] - 1, 0));
-            pe[u] = b.ev[(int64_t)q * n + j];
+            // its list: the steps that end at or before it are behind it
+            int q = q0, first = -j0;
+#pragma unroll
+            for (int z = 0; z < kBatchMax; ++z)
+                if (z >= q0 && z < B - 1 && sb[z] <= x) {
+                    q = z + 1;
+                    first = sb[z];
+                }
+            pe[u] = b.ev[(int64_t)q * n + min(max(x - first, 0), n - 1)];
         }
+        constexpr int MW = kPbMap / (8 * kPbBlock);  // 16-byte map words per thread
+        uint4 *mw = reinterpret_cast<uint4 *>(s_map) + tid * MW;  // consecutive
+#pragma unroll
+        for (int v = 0; v < MW; ++v) mw[v] = make_uint4(0u, 0u, 0u, 0u);
         int p0[RU], p1[RU];
 #pragma unroll
         for (int u = 0; u < RU; ++u) {
@@ -396,6 +411,7 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
             own += sl;
         }
         const long long incl = block_incl_scan_i64_n<kPbBlock>((long long)own, sh);
+        // (the map was cleared before the scan's barriers)
         int y = (int)min(incl - own, (long long)INT32_MAX / 2);
 #pragma unroll
         for (int u = 0; u < RU; ++u) {
@@ -410,11 +426,43 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
             const int pq = x == 0 ? q0 - 1 : (u == 0 ? 16 : (r_info[x - 1] >> kRfStep) & 15);
             if (pq < 16)
                 for (int z = max(pq + 1, q0); z <= min(q, q1); ++z) s_yoff[z] = y;
-            if (y + len[u] <= kPbMap)
-                for (int z = y; z < y + len[u]; ++z) s_map[z] = (uint16_t)x;
+            if (len[u] > 0 && y < kPbMap) s_map[y] = (uint16_t)(x + 1);  // marks its first entry
             y += len[u];
         }
-        __syncthreads();  // r_info (the record before the thread's first)
+        __syncthreads();  // the marks, r_info (the record before the thread's first)
+        // the map: each entry's record is the last one marked up to it
+        {
+            uint32_t m[4 * MW];
+            uint32_t top = 0u;
+#pragma unroll
+            for (int v = 0; v < MW; ++v) {
+                const uint4 x = mw[v];
+                m[4 * v] = x.x;
+                m[4 * v + 1] = x.y;
+                m[4 * v + 2] = x.z;
+                m[4 * v + 3] = x.w;
+            }
+#pragma unroll
+            for (int v = 0; v < 4 * MW; ++v) {
+                const uint32_t lo = max(top, m[v] & 0xffffu);
+                top = max(lo, m[v] >> 16);
+                m[v] = lo | (top << 16);
+            }
+            const int inc = wave_incl_scan((int)top, 0, MaxOp{});
+            if (lane == kWave - 1) shi[wave] = inc;
+            __syncthreads();
+            int ex = wave_shr1(inc, 0);
+            for (int w = 0; w < wave; ++w) ex = max(ex, shi[w]);
+            const uint32_t e0 = (uint32_t)ex;
+#pragma unroll
+            for (int v = 0; v < 4 * MW; ++v) {  // record = mark - 1 (before the first mark: 0)
+                const uint32_t lo = max(e0, m[v] & 0xffffu), hi = max(e0, m[v] >> 16);
+                m[v] = (lo ? lo - 1u : 0u) | ((hi ? hi - 1u : 0u) << 16);
+            }
+#pragma unroll
+            for (int v = 0; v < MW; ++v)
+                mw[v] = make_uint4(m[4 * v], m[4 * v + 1], m[4 * v + 2], m[4 * v + 3]);
+        }
         if (r0 < count && r0 > 0) {
             const int q = (r_info[r0] >> kRfStep) & 15, pq = (r_info[r0 - 1] >> kRfStep) & 15;
             const int yf = (int)min(incl - own, (long long)INT32_MAX / 2);
@@ -429,41 +477,48 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
     // slot loads from a valid address, the results are looked at when the
     // entries are computed
     auto issue = [&](int y0, int y1, PbEntries &E) {
+        static_assert(kPbU % 2 == 0, "two halves");
 #pragma unroll
-        for (int u = 0; u < kPbU; ++u) {
-            const int y = y0 + u * kPbBlock + tid;
-            const bool in = y < y1;
-            const int r = in ? (int)s_map[y] : 0;
-            const int e = in ? r_base[r] + y : 0;  // < n_edges
-            E.cv[u] = CT ? col32[e >> 1] : (uint32_t)col[e];
-            E.wv[u] = wgt[e];
-            E.f[u] = in ? r_info[r] | kEnIn | ((e & 1) ? kEnOdd : 0) |
-                              (y < r_pend[r] ? kEnPlastic : 0)
-                        : 0;
+        for (int h = 0; h < 2; ++h) {
+            if (h && y0 + kPbAhead / 2 >= y1) {  // uniform: the second half is empty
+#pragma unroll
+                for (int u = kPbU / 2; u < kPbU; ++u) E.f[u] = 0;
+                break;
+            }
+#pragma unroll
+            for (int u = h * kPbU / 2; u < (h + 1) * kPbU / 2; ++u) {
+                const int y = y0 + u * kPbBlock + tid;
+                const bool in = y < y1;
+                const int r = in ? (int)s_map[y] : 0;
+                const int e = in ? r_base[r] + y : 0;  // < n_edges
+                E.cv[u] = CT ? col32[e >> 1] : (uint32_t)col[e];
+                E.wv[u] = wgt[e];
+                E.e[u] = e;
+                E.xp0[u] = r_xp0[r];
+                E.f[u] = in ? (r_info[r] & ((1 << kRfStep) - 1)) | kEnIn |
+                                  ((e & 1) ? kEnOdd : 0) | (y < r_pend[r] ? kEnPlastic : 0)
+                            : 0;
+            }
         }
     };
     // weights of late records loaded again, once the step before is stored
-    auto reload = [&](int y0, PbEntries &E) {
+    auto reload = [&](PbEntries &E) {
         bool any = false;
 #pragma unroll
         for (int u = 0; u < kPbU; ++u) any = any || (E.f[u] & kRfLate);
         if (!ballot64(any)) return;  // wave-uniform
 #pragma unroll
         for (int u = 0; u < kPbU; ++u)
-            if (E.f[u] & kRfLate) {
-                const int y = y0 + u * kPbBlock + tid;
-                E.wv[u] = wgt[r_base[s_map[y]] + y];
-            }
+            if (E.f[u] & kRfLate) E.wv[u] = wgt[E.e[u]];
     };
-    // The entries of one window from y0: a transmitting row's entry whose
+    // The entries of one window: a transmitting row's entry whose
     // weight does not change is delivered at once; the entries whose weight
     // changes (a pre spike, or a post spike of the target within the row's
     // window) go to the wave's queue, which is then updated 64 at a time
     // with every lane busy (the replay loops run over those entries only),
     // stored, and delivered where the row transmits.
-    auto compute = [&](int y0, const PbEntries &E) {
-        float *qw = q_w[wave];
-        int *qp = q_p[wave];
+    auto compute = [&](const PbEntries &E) {
+        int4 *qq = s_q[wave];
         int qn = 0;
 #pragma unroll
         for (int u = 0; u < kPbU; ++u) {
@@ -488,9 +543,9 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
             }
             const uint64_t bl = ballot64(cand);
             if (cand) {
-                const int e = qn + lane_rank(bl);
-                qw[e] = E.wv[u];
-                qp[e] = (y0 + u * kPbBlock + tid) | (j << 14);
+                qq[qn + lane_rank(bl)] =
+                    make_int4(__float_as_int(E.wv[u]), E.e[u], __float_as_int(E.xp0[u]),
+                              (f & 0xffffff) | (j << 24));
             }
             qn += (int)__popcll(bl);
         }
@@ -498,24 +553,22 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
         for (int e0 = 0; e0 < qn; e0 += kWave) {  // wave-uniform
             const int e = e0 + lane;
             if (e >= qn) continue;
-            float w = qw[e];
-            const int p = qp[e];
-            const int y = p & (kPbMap - 1), j = p >> 14;
-            const int r = s_map[y];
-            const int info = r_info[r];
+            const int4 p = qq[e];
+            float w = __int_as_float(p.x);
+            const int info = p.w, j = (int)((unsigned)p.w >> 24);
             const int age = info & 0xff, pre = (info & kRfPre) ? 1 : 0;
             uint64_t m0, m1;
             window_masks(age, m0, m1);
             const uint64_t h0 = s_hist[j * HW] & m0;
             const uint64_t h1 = HW == 2 ? s_hist[j * 2 + 1] & m1 : 0ull;
             const float yp = pre ? s_y[j] : 0.f;
-            const float xp0 = r_xp0[r];
+            const float xp0 = __int_as_float(p.z);
             // the pre trace after this update, as the plan's snapshot has it
             const float xpn = __fadd_rn(__fmul_rn(xp0, s_dpow[age]), (float)pre);
             w = b.event ? stdp_synapse(w, h0, h1, age, pre, xp0, xpn, yp, s_dpow, c_pot, c_dep, mu)
                         : stdp_synapse_steps(w, h0, h1, age, pre, xp0, xpn, yp, s_dpow[1],
                                              c_pot, c_dep, mu);
-            wgt[r_base[r] + y] = w;
+            wgt[p.y] = w;
             if (pre)
                 ++w_tx;
             else
@@ -532,7 +585,7 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
     auto windows = [&](int y0, int y1, PbEntries &E) {
         for (int y = y0; y < y1; y += kPbAhead) {  // uniform
             issue(y, y1, E);
-            compute(y, E);
+            compute(E);
         }
     };
     auto neuron_step = [&](int q) {
@@ -543,8 +596,15 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
                     ae = ae0;
                     ai = ai0;
                 } else {
-                    ae = from_fix(s_acc[tid]);
-                    if (b.nacc == 2) ai = from_fix(s_acc[kPbMaxWidth + tid]);
+                    const long long se = s_acc[tid];
+                    const long long si = b.nacc == 2 ? s_acc[kPbMaxWidth + tid] : 0;
+                    if (!ballot64(!(fix_small(se) && fix_small(si)))) {  // any input in earnest
+                        ae = from_fix_small(se);
+                        ai = from_fix_small(si);
+                    } else {
+                        ae = from_fix(se);
+                        ai = from_fix(si);
+                    }
                 }
             }
             int sp;
@@ -552,7 +612,7 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
                 sp = neuron_dynamics<2>(a, i, t0 + q, ae, ai, st);
             else
                 sp = lif_dynamics<-1>(a, ae, ai,
-                                      driven ? s_x[(q % dsteps) * b.gwidth + tid] : 0.f, st);
+                                      driven ? s_x[((q & (dsteps - 1)) << gsh) + tid] : 0.f, st);
             neuron_record<-1, HW>(a, sp, st);
             spikes += sp;
             blk = (blk << 1) | (uint32_t)sp;
@@ -568,7 +628,7 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
     // the drive of the steps after step q, when step q used the last drawn
     // (after step q's first barrier)
     auto draw_next = [&](int q) {
-        if (driven && (q + 1) % dsteps == 0 && q + 1 < B) draw(q + 1);
+        if (driven && ((q + 1) & (dsteps - 1)) == 0 && q + 1 < B) draw(q + 1);
     };
 
     PbEntries E0, E1;
@@ -598,11 +658,11 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
                 const int y0 = s_yoff[k], y1 = s_yoff[k + 1];
                 const int z1 = k + 1 < qx ? s_yoff[k + 2] : y1;
                 issue(y1, z1, F);
-                compute(y0, E);
+                compute(E);
                 if (y1 - y0 > kPbAhead) windows(y0 + kPbAhead, y1, E);
                 draw_next(k);
                 __syncthreads();  // every atomic and weight store of step k done
-                reload(y1, F);
+                reload(F);
             };
             issue(s_yoff[qs], s_yoff[qs + 1], E0);
             for (int k = qs; k < qx; k += 2) {

@@ -372,7 +372,7 @@ struct PbEvent {
 constexpr int kPbPlanBlock = 512;   // threads of the plan (one row each, a half wave per step's scan)
 constexpr int kPbBlock = 512;       // threads of a target group's workgroup
 constexpr int kPbMaxWidth = 256;    // most targets per group (one neuron per thread)
-constexpr int kPbRecords = 5120;    // a block's records a workgroup holds in LDS
+constexpr int kPbRecords = 4096;    // a block's records a workgroup holds in LDS
 constexpr int kPbMaxN = 65536;      // largest network the blocks run
 constexpr int kPbMaxSteps = kBatchMax - 1;  // steps per block: lists 0 .. B-1, deferred list B
 constexpr int kPbDfPart = 8 * 64;   // entries per part of a deferred row (8 per lane)

@@ -23,7 +23,7 @@ CASES = [
     # about 3,000 per group and step: blocks of a few stretches
     ("stress", dict(n=300, p_or_fanout=1000, p_fire=0.05, delay=12), 64,
      dict(history_bits=128)),
-    # more than 5,120 records in a block, and in a step
+    # more than 4,096 records in a block, and in a step
     ("stress", dict(n=20000, p_or_fanout=8, p_fire=0.04, delay=16), 64, dict()),
     ("stress", dict(n=20000, p_or_fanout=8, p_fire=0.4, delay=3), 256, dict()),
     # consecutive events of a row at every distance, 32-bit targets
