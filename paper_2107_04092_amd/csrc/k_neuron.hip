@@ -696,7 +696,8 @@ __global__ __launch_bounds__(kStepsBlock) void k_source_steps(NeuronArgs a, Comp
     int tl = tl0;
     for (int k = 0; k < B; ++k) {
         const int64_t t = t0 + k;
-        const int s = live ? neuron_advance<-1, H>(a, ic, t, 0.f, 0.f, st) : 0;
+        const int s = live ? neuron_dynamics<2>(a, ic, t, 0.f, 0.f, st) : 0;  // (a source)
+        neuron_record<-1, H>(a, s, st);
         const int f = live && prow && !s && t - (int64_t)tl >= 64 * H;
         if (live && prow && (s || f) && t > (int64_t)tl) tl = (int)t;
         fired |= (uint32_t)s << k;
