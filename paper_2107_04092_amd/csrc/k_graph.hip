@@ -4,6 +4,8 @@
 // pivots with plastic prefixes.
 #include "snn_device.h"
 
+#include <algorithm>
+
 namespace snn {
 namespace {
 
@@ -171,6 +173,108 @@ __global__ __launch_bounds__(kBlock) void k_edges_scatter(GraphArgs a, const int
     }
 }
 
+// Edge lists by buckets of rows (BucketArgs). One global atomic per edge, to
+// count and again to place it, is executed at the memory (about 20 per ns for
+// the whole device), and a bitonic network sorts a row of 266 in 45 rounds of
+// barriers; here a workgroup counts its stretch of the list per bucket of
+// consecutive rows in LDS, reserves room for the whole stretch with one atomic
+// per bucket, and drops the edges there (row in the bucket and target in one
+// word, weight in another, in the arrays of the graph itself); then one
+// workgroup per bucket sorts it in LDS. 8M edges of 30,011 rows: counting 391
+// -> 18 us, placing 721 -> 197 us (bound by its scattered words), sorting 750 -> 108 us.
+constexpr int kGroupBlock = 1024;
+constexpr int kGroupU = 8;  // edges a thread loads at once
+
+__device__ __forceinline__ bool edge_ok(const GraphArgs &a, int s, int d)
+{
+    return s >= 0 && s < a.n && d >= 0 && d < a.n;
+}
+
+__global__ __launch_bounds__(kGroupBlock) void k_bucket_count(GraphArgs a, BucketArgs b)
+{
+    extern __shared__ int s_n[];  // nb
+    for (int x = threadIdx.x; x < b.nb; x += kGroupBlock) s_n[x] = 0;
+    __syncthreads();
+    const int64_t e0 = blockIdx.x * b.stretch, e1 = min(e0 + b.stretch, b.e);
+    bool bad = false;
+    for (int64_t i0 = e0 + threadIdx.x; i0 < e1; i0 += kGroupBlock * kGroupU) {
+        int s[kGroupU], d[kGroupU];
+#pragma unroll
+        for (int u = 0; u < kGroupU; ++u) {
+            const int64_t i = min(i0 + u * kGroupBlock, e1 - 1);
+            s[u] = b.src[i];
+            d[u] = b.dst[i];
+        }
+#pragma unroll
+        for (int u = 0; u < kGroupU; ++u) {
+            if (i0 + u * kGroupBlock >= e1) break;
+            if (edge_ok(a, s[u], d[u]))
+                atomicAdd(&s_n[s[u] >> b.shift], 1);
+            else
+                bad = true;
+        }
+    }
+    if (bad) atomicOr(a.err, kErrIndex);
+    __syncthreads();
+    for (int x = threadIdx.x; x < b.nb; x += kGroupBlock)
+        if (s_n[x]) atomicAdd((unsigned long long *)(b.start + x + 1), (unsigned long long)s_n[x]);
+}
+
+__global__ __launch_bounds__(kGroupBlock) void k_bucket_place(GraphArgs a, BucketArgs b)
+{
+    // per bucket: the stretch's count, then the next free place less the
+    // bucket's start (a bucket holds fewer than 2^31 edges)
+    extern __shared__ int s_n[];  // nb
+    for (int x = threadIdx.x; x < b.nb; x += kGroupBlock) s_n[x] = 0;
+    __syncthreads();
+    const int64_t e0 = blockIdx.x * b.stretch, e1 = min(e0 + b.stretch, b.e);
+    for (int64_t i0 = e0 + threadIdx.x; i0 < e1; i0 += kGroupBlock * kGroupU) {
+        int s[kGroupU], d[kGroupU];
+#pragma unroll
+        for (int u = 0; u < kGroupU; ++u) {
+            const int64_t i = min(i0 + u * kGroupBlock, e1 - 1);
+            s[u] = b.src[i];
+            d[u] = b.dst[i];
+        }
+#pragma unroll
+        for (int u = 0; u < kGroupU; ++u)
+            if (i0 + u * kGroupBlock < e1 && edge_ok(a, s[u], d[u]))
+                atomicAdd(&s_n[s[u] >> b.shift], 1);
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x < b.nb; x += kGroupBlock)
+        if (s_n[x])
+            s_n[x] = (int)(atomicAdd((unsigned long long *)(b.cursor + x),
+                                     (unsigned long long)s_n[x]) -
+                           (unsigned long long)b.start[x]);
+    __syncthreads();
+    for (int64_t i0 = e0 + threadIdx.x; i0 < e1; i0 += kGroupBlock * kGroupU) {
+        int s[kGroupU], d[kGroupU];
+        float w[kGroupU];
+        int64_t at[kGroupU];
+#pragma unroll
+        for (int u = 0; u < kGroupU; ++u) {
+            const int64_t i = min(i0 + u * kGroupBlock, e1 - 1);
+            s[u] = b.src[i];
+            d[u] = b.dst[i];
+            w[u] = b.w[i];
+        }
+#pragma unroll
+        for (int u = 0; u < kGroupU; ++u) {
+            const bool ok = edge_ok(a, s[u], d[u]);
+            at[u] = b.start[ok ? s[u] >> b.shift : 0];
+        }
+#pragma unroll
+        for (int u = 0; u < kGroupU; ++u) {
+            if (i0 + u * kGroupBlock >= e1 || !edge_ok(a, s[u], d[u])) continue;
+            const int k = s[u] >> b.shift;
+            const int64_t pos = at[u] + atomicAdd(&s_n[k], 1);
+            a.col[pos] = (int32_t)(((uint32_t)(s[u] - (k << b.shift)) << 24) | (uint32_t)d[u]);
+            a.w[pos] = w[u];
+        }
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_row_maxlen(GraphArgs a)
 {
     const int k = blockIdx.x * kBlock + threadIdx.x;
@@ -234,6 +338,130 @@ __global__ __launch_bounds__(kSortBlock) void k_row_sort(GraphArgs a)
         const unsigned long long key = keys[x];
         a.col[rs + x] = (int32_t)(key >> 32);
         a.w[rs + x] = ord2f((uint32_t)key);
+    }
+}
+
+// Sorts the entries of one bucket of rows by (row, target, weight) in LDS,
+// writes them back (targets alone, and the compressed ones) and its rows'
+// pointers. Every row is cut into `sub` ranges of targets; an entry's place is
+// its range's start (one scan over all ranges of the bucket) plus the order
+// in which it arrived there, and the few entries of a range (about one: ranges
+// are as many as LDS holds counters) are then put in order by one thread. A
+// bucket with a range of more than kSubMax entries (targets far from evenly
+// spread) is sorted row by row with a bitonic network instead.
+constexpr int kSortU = kBucketCap / kSortBlock;  // entries per thread
+constexpr int kSubU = kBucketSubs / kSortBlock;  // ranges per thread
+constexpr int kSubMax = 48;
+static_assert(kBucketCap % kSortBlock == 0 && kBucketSubs % kSortBlock == 0, "whole rounds");
+
+__global__ __launch_bounds__(kSortBlock) void k_bucket_sort(GraphArgs a, BucketArgs b)
+{
+    extern __shared__ unsigned long long s_e[];  // kBucketCap entries, then the ranges' starts
+    int *s_off = reinterpret_cast<int *>(s_e + kBucketCap);  // kBucketSubs + 1
+    __shared__ long long sh[kSortBlock / kWave];
+    __shared__ int s_max;
+    const int tid = threadIdx.x, k = blockIdx.x;
+    const int r0 = k << b.shift, nr = min(1 << b.shift, a.n - r0);
+    const int64_t e0 = b.fanout ? (int64_t)r0 * b.fanout : b.start[k];
+    const int cnt = b.fanout ? nr * b.fanout : (int)(b.start[k + 1] - e0);  // <= kBucketCap
+    if (cnt > kBucketCap) {  // (the host checks it)
+        if (tid == 0) atomicOr(a.err, kErrRowTooLong);
+        return;
+    }
+    const int sub = kBucketSubs >> b.shift;  // ranges per row
+    const uint32_t f = b.scale;
+    for (int x = tid; x <= kBucketSubs; x += kSortBlock) s_off[x] = 0;
+    if (tid == 0) s_max = 0;
+    __syncthreads();
+    uint32_t key[kSortU], wk[kSortU];
+    int at[kSortU];  // range (bits 0-15), order of arrival (16-31)
+#pragma unroll
+    for (int u = 0; u < kSortU; ++u) {
+        const int x = u * kSortBlock + tid;
+        const int64_t e = e0 + min(x, max(cnt - 1, 0));
+        key[u] = cnt > 0 ? (uint32_t)a.col[e] : 0u;
+        wk[u] = cnt > 0 ? f2ord(a.w[e]) : 0u;
+        if (b.fanout) key[u] |= (uint32_t)(min(x, max(cnt - 1, 0)) / b.fanout) << 24;
+    }
+#pragma unroll
+    for (int u = 0; u < kSortU; ++u) {
+        at[u] = 0;
+        if (u * kSortBlock + tid >= cnt) continue;
+        const int q = (int)(key[u] >> 24) * sub + (int)__umulhi(key[u] & 0xffffffu, f);
+        at[u] = q | (atomicAdd(&s_off[q], 1) << 16);
+    }
+    __syncthreads();
+    {  // counts to starts
+        int n[kSubU], sum = 0, top = 0;
+#pragma unroll
+        for (int v = 0; v < kSubU; ++v) {
+            n[v] = s_off[kSubU * tid + v];
+            sum += n[v];
+            top = max(top, n[v]);
+        }
+        int at0 = (int)block_incl_scan_i64_n<kSortBlock>(sum, sh) - sum;
+#pragma unroll
+        for (int v = 0; v < kSubU; ++v) {
+            s_off[kSubU * tid + v] = at0;
+            at0 += n[v];
+        }
+        if (tid == kSortBlock - 1) s_off[kBucketSubs] = at0;
+        if (top > kSubMax) atomicMax(&s_max, top);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kSortU; ++u)
+        if (u * kSortBlock + tid < cnt)
+            s_e[s_off[at[u] & 0xffff] + (at[u] >> 16)] =
+                ((unsigned long long)key[u] << 32) | wk[u];
+    for (int r = tid; r < nr; r += kSortBlock) a.row_ptr[r0 + r] = e0 + s_off[r * sub];
+    if (tid == 0 && r0 + nr == a.n) a.row_ptr[a.n] = e0 + cnt;
+    __syncthreads();
+    if (s_max == 0) {  // workgroup-uniform
+        for (int q = tid; q < kBucketSubs; q += kSortBlock) {
+            const int lo = s_off[q], hi = s_off[q + 1];
+            for (int i = lo + 1; i < hi; ++i) {
+                const unsigned long long v = s_e[i];
+                int j = i;
+                for (; j > lo && s_e[j - 1] > v; --j) s_e[j] = s_e[j - 1];
+                s_e[j] = v;
+            }
+        }
+    } else {
+        // a bitonic network per row, with every comparator ascending (the
+        // first round of a merge pairs mirrored entries), so that the entries
+        // beyond the row stand for the largest key and are left out
+        for (int r = 0; r < nr; ++r) {
+            const int lo = s_off[r * sub], len = s_off[(r + 1) * sub] - lo;
+            int p2 = 1;
+            while (p2 < len) p2 <<= 1;
+            for (int size = 2; size <= p2; size <<= 1) {
+                for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                    const bool mirror = stride == size >> 1;
+                    for (int x = tid; x < (p2 >> 1); x += kSortBlock) {
+                        const int blk = x / stride, in = x - blk * stride;
+                        const int i = 2 * stride * blk + in;
+                        const int j = mirror ? 2 * stride * (blk + 1) - 1 - in : i + stride;
+                        if (j < len) {
+                            const unsigned long long u = s_e[lo + i], v = s_e[lo + j];
+                            if (u > v) {
+                                s_e[lo + i] = v;
+                                s_e[lo + j] = u;
+                            }
+                        }
+                    }
+                    __syncthreads();
+                }
+            }
+        }
+    }
+    __syncthreads();
+    for (int x = tid; x < cnt; x += kSortBlock) {
+        const unsigned long long v = s_e[x];
+        const int32_t d = (int32_t)((v >> 32) & 0xffffffu);
+        a.col[e0 + x] = d;
+        a.w[e0 + x] = ord2f((uint32_t)v);
+        if (a.col16) a.col16[e0 + x] = (uint16_t)(d % a.width);
     }
 }
 
@@ -334,6 +562,63 @@ hipError_t launch_edges_scatter(hipStream_t s, const GraphArgs &a, const int32_t
     if (e <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_edges_scatter, dim3(blocks_for(e, kBlock, 1 << 16)), dim3(kBlock), 0,
                        s, a, src, dst, w, e, cursor);
+    return hipGetLastError();
+}
+
+bool choose_buckets(BucketArgs &b, int32_t n, int64_t e, int64_t max_row)
+{
+    // rows per bucket: about kBucketAim edges, but no fewer than 512 buckets
+    // where there are rows for them, and as many as LDS can count
+    int shift = 0;
+    while (shift < kBucketShift && ((int64_t)n >> (shift + 1)) >= 512 &&
+           e * (2ll << shift) / n <= kBucketAim)
+        ++shift;
+    while (shift < kBucketShift && (((int64_t)n - 1) >> shift) + 1 > kBucketMax) ++shift;
+    b.shift = shift;
+    b.nb = (int32_t)((((int64_t)n - 1) >> shift) + 1);
+    const int sub = kBucketSubs >> shift;
+    b.scale = (uint32_t)std::min<uint64_t>(((uint64_t)sub << 32) / (uint64_t)n, 0xFFFFFFFFull);
+    b.e = e;
+    const int64_t stretches =
+        std::max<int64_t>(1, std::min<int64_t>(256, (e + kGroupU * kGroupBlock - 1) / (kGroupU * kGroupBlock)));
+    b.stretch = (e + stretches - 1) / stretches;
+    b.grid = (int32_t)stretches;
+    return b.nb <= kBucketMax && max_row <= kBucketCap &&
+           (double)e / n * (double)(1 << shift) <= kBucketCap;
+}
+
+hipError_t launch_bucket_count(hipStream_t s, const GraphArgs &a, const BucketArgs &b)
+{
+    static std::mutex mu;
+    static int granted = 48 * 1024;
+    const int lds = b.nb * (int)sizeof(int);
+    const hipError_t e = allow_dynamic_lds((const void *)k_bucket_count, lds, mu, granted);
+    if (e != hipSuccess) return e;
+    if (b.e > 0)
+        hipLaunchKernelGGL(k_bucket_count, dim3(b.grid), dim3(kGroupBlock), lds, s, a, b);
+    return hipGetLastError();
+}
+
+hipError_t launch_bucket_place(hipStream_t s, const GraphArgs &a, const BucketArgs &b)
+{
+    static std::mutex mu;
+    static int granted = 48 * 1024;
+    const int lds = b.nb * (int)sizeof(int);
+    const hipError_t e = allow_dynamic_lds((const void *)k_bucket_place, lds, mu, granted);
+    if (e != hipSuccess) return e;
+    if (b.e > 0)
+        hipLaunchKernelGGL(k_bucket_place, dim3(b.grid), dim3(kGroupBlock), lds, s, a, b);
+    return hipGetLastError();
+}
+
+hipError_t launch_bucket_sort(hipStream_t s, const GraphArgs &a, const BucketArgs &b)
+{
+    static std::mutex mu;
+    static int granted = 48 * 1024;
+    const int lds = kBucketCap * (int)sizeof(unsigned long long) + (kBucketSubs + 1) * (int)sizeof(int);
+    const hipError_t e = allow_dynamic_lds((const void *)k_bucket_sort, lds, mu, granted);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_bucket_sort, dim3(b.nb), dim3(kSortBlock), lds, s, a, b);
     return hipGetLastError();
 }
 

@@ -526,7 +526,8 @@ snn_status zero_stats(snn_ctx *c)
 }
 
 // Finish a graph build: pivots, plastic prefixes, error check, group size.
-snn_status finish_graph(snn_ctx *c)
+// encoded: the compressed targets are already written.
+snn_status finish_graph(snn_ctx *c, bool encoded = false)
 {
     GraphArgs a = graph_args(c);
     snn_status st = check_hip(c, launch_pivots(c->stream, a), "pivot kernel");
@@ -539,7 +540,7 @@ snn_status finish_graph(snn_ctx *c)
         st = check_hip(c, launch_pivots(c->stream, ga), "group pivot kernel");
         if (st) return st;
     }
-    if (c->ct) {
+    if (c->ct && !encoded) {
         st = check_hip(c, launch_encode_targets(c->stream, a, c->n_edges), "target compression");
         if (st) return st;
     }
@@ -1338,6 +1339,7 @@ snn_status snn_build_graph_random(snn_ctx *c, float w_exc, float w_inh)
     GraphArgs a = graph_args(c);
     a.w_exc = w_exc;
     a.w_inh = w_inh;
+    bool encoded = false;
     hipError_t e = launch_fill_i32(c->stream, c->err_flag, 1, 0);
     if (c->counted_kind == SNN_GRAPH_BERNOULLI) {
         const double thr = std::floor(c->counted_p * 4294967296.0);
@@ -1350,12 +1352,19 @@ snn_status snn_build_graph_random(snn_ctx *c, float w_exc, float w_inh)
             int p2 = 2;
             while (p2 < a.fanout) p2 <<= 1;
             if (a.fanout > kMaxSortRow) return fail(c, SNN_EINVAL, "fan-out above %d", kMaxSortRow);
-            e = launch_row_sort(c->stream, a, p2);
+            BucketArgs b{};
+            b.fanout = a.fanout;
+            if (choose_buckets(b, c->n, c->n_edges, a.fanout)) {
+                e = launch_bucket_sort(c->stream, a, b);
+                encoded = true;
+            } else {
+                e = launch_row_sort(c->stream, a, p2);
+            }
         }
     }
     st = check_hip(c, e, "graph fill");
     if (st) return st;
-    return finish_graph(c);
+    return finish_graph(c, encoded);
 }
 
 snn_status snn_build_graph_edges(snn_ctx *c, const int32_t *src, const int32_t *dst,
@@ -1369,6 +1378,44 @@ snn_status snn_build_graph_edges(snn_ctx *c, const int32_t *src, const int32_t *
     if (e > 0 && (!src || !dst || !w)) return fail(c, SNN_EINVAL, "edge arrays are NULL");
     GraphArgs a = graph_args(c);
     hipError_t he = launch_fill_i32(c->stream, c->err_flag, 1, 0);
+    // by buckets of rows, if the largest fits the sort's LDS (known after the
+    // count; the scan's space holds their starts, the row pointers' the
+    // cursors)
+    BucketArgs b{};
+    b.src = src;
+    b.dst = dst;
+    b.w = w;
+    b.start = c->scratch;
+    b.cursor = c->row_ptr;
+    if (choose_buckets(b, c->n, e, 0)) {
+        GraphArgs ba = a;  // the buckets in the place of the rows
+        ba.row_ptr = b.start;
+        ba.n = b.nb;
+        if (he == hipSuccess) he = launch_fill_i32(c->stream, c->maxlen, 1, 0);
+        if (he == hipSuccess) he = launch_fill_i64(c->stream, b.start, (int64_t)b.nb + 1, 0);
+        if (he == hipSuccess) he = launch_bucket_count(c->stream, a, b);
+        if (he == hipSuccess) he = launch_scan_i64(c->stream, b.start + 1, b.nb, c->bsum);
+        if (he == hipSuccess) he = launch_row_maxlen(c->stream, ba);
+        if (he == hipSuccess)
+            he = launch_copy_bytes(c->stream, b.cursor, b.start, (int64_t)b.nb * 8);
+        if (he == hipSuccess) he = launch_bucket_place(c->stream, a, b);
+        st = check_hip(c, he, "edge grouping");
+        if (st) return st;
+        int32_t largest = 0, err = 0;
+        st = check_hip(c, hipMemcpyAsync(&largest, c->maxlen, 4, hipMemcpyDeviceToHost, c->stream),
+                       "read bucket size");
+        if (!st)
+            st = check_hip(c, hipMemcpyAsync(&err, c->err_flag, 4, hipMemcpyDeviceToHost,
+                                             c->stream), "read error flag");
+        if (!st) st = check_hip(c, hipStreamSynchronize(c->stream), "edge grouping");
+        if (st) return st;
+        if (err & kErrIndex) return fail(c, SNN_EINVAL, "edge index outside [0, n)");
+        if (largest <= kBucketCap) {
+            st = check_hip(c, launch_bucket_sort(c->stream, a, b), "bucket sort");
+            if (st) return st;
+            return finish_graph(c, true);
+        }
+    }
     if (he == hipSuccess) he = launch_fill_i32(c->stream, c->maxlen, 1, 0);
     if (he == hipSuccess) he = launch_fill_i64(c->stream, c->row_ptr, (int64_t)c->n + 1, 0);
     if (he == hipSuccess) he = launch_edges_count(c->stream, a, src, dst, e);

@@ -275,6 +275,32 @@ struct GraphArgs {
     float w_exc, w_inh;
 };
 
+// Building the rows by buckets of 2^shift consecutive rows (k_bucket_count,
+// k_bucket_place, k_bucket_sort): of an edge list, or (fanout > 0) of rows of
+// that many targets already in place, which are only sorted.
+struct BucketArgs {
+    const int32_t *src, *dst;
+    const float *w;
+    int64_t e;
+    int64_t *start;   // [nb + 1]: first edge of each bucket (counted into start + 1, then scanned)
+    int64_t *cursor;  // [nb]: next free place of each bucket
+    int64_t stretch;  // edges per workgroup of the counting and placing kernels
+    int32_t grid;     // their workgroups
+    int32_t nb, shift, fanout;
+    uint32_t scale;   // target range of a row: mulhi(target, scale)
+};
+constexpr int kBucketShift = 8;     // most rows per bucket: 2^8 (row in the top byte of a word)
+constexpr int kBucketAim = 5120;    // edges per bucket aimed at
+constexpr int kBucketCap = 12288;   // most edges a bucket can have (LDS: 8 B each)
+constexpr int kBucketSubs = 8192;   // target ranges per bucket (LDS: 4 B each)
+constexpr int kBucketMax = 32768;   // most buckets (LDS: 4 B each)
+// The buckets for n rows and e edges, the longest row max_row if known (else
+// 0); false where they do not fit (then: launch_edges_count and so on).
+bool choose_buckets(BucketArgs &b, int32_t n, int64_t e, int64_t max_row);
+hipError_t launch_bucket_count(hipStream_t s, const GraphArgs &a, const BucketArgs &b);
+hipError_t launch_bucket_place(hipStream_t s, const GraphArgs &a, const BucketArgs &b);
+hipError_t launch_bucket_sort(hipStream_t s, const GraphArgs &a, const BucketArgs &b);
+
 // Several whole steps of a small network without plasticity in one launch of
 // one workgroup (k_small_steps): neuron update, spike list into the delay
 // ring, and delivery into an LDS accumulator that the next step's neuron
