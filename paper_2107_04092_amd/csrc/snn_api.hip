@@ -117,6 +117,9 @@ struct snn_ctx {
     int32_t dlv_slots = 0;
     // delay blocks (no plasticity, D >= 2): steps per block, partial inputs
     int32_t batch_max = 0;
+    // one launch per step (StepOneArgs): targets per workgroup (0: off), masks
+    int32_t one_gw = 0;
+    uint64_t *one_mask = nullptr;
     bool fuse = false;  // plastic: parts (2) and (3) of snn_step in one launch
     int32_t fuse_slots = 0;  // workgroups of the fused pass resident at once
     int32_t fuse_chunks = 1;  // workgroups per slice in the fused pass (<= chunks)
@@ -372,6 +375,13 @@ void derive(snn_ctx *c)
         const int64_t bb = (c->batch_max * c->n_slices + 7) / 8 * 8;
         if (bb > c->dlv_slots) c->dlv_slots = (int32_t)bb;
     }
+    // One launch per step (StepOneArgs): no plasticity, D = 1, more neurons than
+    // one workgroup runs; groups of whole slices, about kSmallBlock targets
+    // (one per thread).
+    c->one_gw = 0;
+    if (k.plastic == SNN_PLASTIC_NONE && c->delay == 1 && k.n <= kOneMaxN &&
+        k.slice_width <= kOneMaxW)
+        c->one_gw = std::max(1, kSmallBlock / k.slice_width) * k.slice_width;
     c->info_blocks = c->nblk;  // statistics slots of the neuron-kernel / flush snapshots
     // Plastic blocks (BlockArgs) of up to D-1 steps (at most kPbMaxSteps): lazy
     // plasticity, D >= 2, up to kPbMaxN neurons. Target groups of 64, 128
@@ -458,6 +468,7 @@ void plan_workspace(snn_ctx *c, uint8_t *base)
     c->pdcode = p.take<uint8_t>(c->pb_max > 0 ? (n + 15) / 16 * 16 : 1);
     c->phq = p.take<uint64_t>(c->pb_max > 0 ? 2 * n * c->hw : 1);
     c->bclk = p.take<BlockClock>(1);
+    c->one_mask = p.take<uint64_t>(c->one_gw > 0 ? 2 * (int64_t)c->nw : 1);
     {
         const int64_t v = c->sb_max > 1 ? c->sb_max - 1 : 0;  // versions
         const int64_t npl = std::max<int32_t>(c->n_plastic_rows, 1);
@@ -1566,6 +1577,44 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
         q += B;
     }
     if (blocks) return SNN_OK;
+    // a network without plasticity and D = 1 takes one launch per step (and one
+    // more per call; see StepOneArgs)
+    const bool ones = mode == SNN_DELIVER_LDS_SLICE && c->one_gw > 0 && c->t_used >= c->t_cap;
+    if (ones && n_steps > 0) {
+        const NeuronArgs a = neuron_args(c);
+        StepOneArgs b{};
+        b.gw = c->one_gw;
+        b.mult = c->one_gw / c->cfg.slice_width;
+        b.n_slices = c->n_slices;
+        // lanes per row: its entries per workgroup on average, 4 to 64
+        const double seg = (double)c->n_edges / c->n * c->one_gw / c->n;
+        b.lg_team = 2;
+        while (b.lg_team < 6 && (1 << b.lg_team) < seg) ++b.lg_team;
+        b.row_ptr = c->row_ptr;
+        b.col = c->col;
+        b.w = c->w;
+        b.piv = c->piv;
+        b.ring = c->ring;
+        b.ring_cnt = c->ring_cnt;
+        b.tx_cnt = c->tx_cnt;
+        b.apart = c->apart;
+        b.gstats = c->gstats;
+        b.dlv_stats = c->dlv_stats;
+        b.dlv_slots = c->dlv_slots;
+        b.status = c->status;
+        b.status_words = c->status_words;
+        for (int32_t k = 0; k <= n_steps; ++k) {
+            b.deliver = k > 0;
+            b.last = k == n_steps;
+            b.step = k;
+            b.mask_in = c->one_mask + (int64_t)(~k & 1) * c->nw;
+            b.mask_out = c->one_mask + (int64_t)(k & 1) * c->nw;
+            if ((st = check_hip(c, launch_step_one(c->stream, a, b), "one-launch step"))) return st;
+        }
+        c->t += n_steps;
+        c->last_neuron_t = c->last_deliver_t = c->t - 1;
+        return SNN_OK;
+    }
     // a plastic network of Bernoulli sources with D = 1 runs in source
     // blocks (see SourceArgs): one launch for the neuron updates and lists
     // of up to sb_max steps, then the synapse pass of each step on its
@@ -1574,7 +1623,10 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
     // shape left can match a step tag. With kernel timing on, the block's
     // launch is timed as the neuron part of its first step and each pass as
     // the delivery part of its step.
-    const bool sblocks = mode == SNN_DELIVER_LDS_SLICE && c->sb_max > 0;
+    // (timed as configured: a pass with fewer workgroups per slice than asked
+    // for runs as its parts while kernel times are being recorded)
+    const bool whole = c->fuse_chunks == c->chunks || c->t_used >= c->t_cap;
+    const bool sblocks = mode == SNN_DELIVER_LDS_SLICE && c->sb_max > 0 && whole;
     if (sblocks && n_steps > 0) {
         if ((st = check_hip(c, clear_status(c), "clear the list scans"))) return st;
         NeuronArgs a = neuron_args(c);
@@ -1637,7 +1689,7 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
     }
     // parts (2) and (3) of plastic networks in one launch where it fits
     // (kernel timing records it as the delivery part)
-    const bool fuse = mode == SNN_DELIVER_LDS_SLICE && c->fuse;
+    const bool fuse = mode == SNN_DELIVER_LDS_SLICE && c->fuse && whole;
     for (int32_t q = 0; q < n_steps; ++q) {
         if ((st = launch_step_neurons(c))) return st;
         if (fuse) {

@@ -329,6 +329,31 @@ constexpr int kSmallRounds = 4;     // neurons per thread: n <= 4096
 constexpr int kSmallMaxAcc = 8192;  // nacc * n accumulators (64 KiB of LDS)
 constexpr int kSmallChunk = 4096;   // steps per launch
 
+// One launch per step of a network without plasticity and D = 1
+// (k_step_one): deliver the spikes of the step before, update the neurons.
+struct StepOneArgs {
+    const uint64_t *mask_in;  // spikes of the step to deliver (deliver != 0)
+    uint64_t *mask_out;       // spikes of the step updated (last == 0)
+    int32_t deliver, last;    // last: deliver only, and leave the state as after snn_step
+    int32_t step;             // the step updated is clk->t + step; last: the call's steps
+    int32_t gw, mult;         // targets per workgroup: mult slices
+    int32_t n_slices;
+    int32_t lg_team;          // log2 of the lanes that share one row
+    const int64_t *row_ptr;
+    const int32_t *col;
+    const float *w;
+    const int32_t *piv;       // [n][n_slices + 1]
+    int32_t *ring, *ring_cnt, *tx_cnt;
+    long long *apart;         // part 0: the pending input after the last step
+    int64_t *gstats, *dlv_stats;
+    int32_t dlv_slots;
+    unsigned long long *status;
+    int32_t status_words;
+};
+constexpr int kOneMaxN = 65536;  // a mask word per thread
+constexpr int kOneMaxW = 4096;   // targets per workgroup
+hipError_t launch_step_one(hipStream_t s, const NeuronArgs &a, const StepOneArgs &b);
+
 // Delay-blocked steps of a network without plasticity and delay D >= 2
 // (k_neuron_steps after a batched k_deliver_lds). The input of step t comes
 // from the spikes of step t-D only, so the inputs of steps t0+1 .. t0+B
