@@ -583,11 +583,20 @@ __global__ __launch_bounds__(kSmallBlock) void k_step_one(NeuronArgs a, StepOneA
                 if (pos >= 0 && pos < kOneList) s_list[pos] = tid * kWave + __ffsll((long long)x) - 1;
             __syncthreads();  // the list (and the cleared accumulators)
             const int cnt = min(total - c0, kOneList);
+            // a team's next row is looked up while its row is added
+            int kn = cnt > 0 ? s_list[min(team, cnt - 1)] : 0;
+            int64_t rsn = b.row_ptr[kn];
+            int p0n = b.piv[(int64_t)kn * (b.n_slices + 1) + s0];
+            int p1n = b.piv[(int64_t)kn * (b.n_slices + 1) + s1];
             for (int q = team; q < cnt; q += teams) {
-                const int k = s_list[q];
-                const int32_t *pv = b.piv + (int64_t)k * (b.n_slices + 1);
-                const int64_t rs = b.row_ptr[k];
-                const int p0 = pv[s0], p1 = pv[s1];
+                const int k = kn, p0 = p0n, p1 = p1n;
+                const int64_t rs = rsn;
+                if (q + teams < cnt) {
+                    kn = s_list[q + teams];
+                    rsn = b.row_ptr[kn];
+                    p0n = b.piv[(int64_t)kn * (b.n_slices + 1) + s0];
+                    p1n = b.piv[(int64_t)kn * (b.n_slices + 1) + s1];
+                }
                 const int half = (M == 1 && k >= a.n_exc) ? NP : 0;
                 for (int p = p0 + tl; p < p1; p += 2 * ts) {
                     const int64_t e0 = rs + p;
