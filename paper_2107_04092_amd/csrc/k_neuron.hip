@@ -823,18 +823,17 @@ __global__ __launch_bounds__(kStepsBlock) void k_neuron_steps(NeuronArgs a, Batc
 // workgroup (a half wave per step's list scan). A row transmits at the step
 // its neuron fires; a plastic row is forced at a step where it neither
 // transmits nor was updated in the last 64 hw steps, as in k_neuron. The
-// walk through the steps records the spike and forced bits and the state of
-// each step; after the scans a second walk over the row's updates makes
-// their snapshots, each starting from the t_last and pre trace the one
-// before left (what the passes commit in between, step by step).
+// walk through the steps records the spike and forced bits; after the scans a
+// second walk over the row's updates makes their snapshots, each starting from
+// the t_last and pre trace the one before left.
 template <int H>
 __global__ __launch_bounds__(kStepsBlock) void k_source_steps(NeuronArgs a, CompactArgs lst,
                                                               SourceArgs b)
 {
     constexpr int NWV = kStepsBlock / kWave;
     static_assert(kStepsBlock / 32 >= kSrcMaxSteps, "a half wave per step's list scan");
-    __shared__ uint64_t s_m[kSrcMaxSteps][NWV];  // transmitted rows of step k, per wave
-    __shared__ uint64_t s_f[kSrcMaxSteps][NWV];  // forced rows
+    __shared__ uint64_t s_m[kSrcMaxSteps][NWV];  // listed rows of step k, per wave
+    __shared__ uint64_t s_f[2][NWV];             // forced rows: the last step's; the block's others
     __shared__ int s_lb[2 * kBatchMax];
     __shared__ unsigned long long s_st[4];
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
@@ -854,7 +853,7 @@ __global__ __launch_bounds__(kStepsBlock) void k_source_steps(NeuronArgs a, Comp
     const float xp0 = lst.xpre[ip];
     const StepClock ck = load_clock(a.clk);
     const int64_t t0 = ck.t;
-    const int64_t nh = (int64_t)n * H;
+    const uint64_t hs0 = st.h0, hs1 = st.h1;
     uint32_t fired = 0, forced = 0;
     int tl = tl0;
     for (int k = 0; k < B; ++k) {
@@ -865,58 +864,84 @@ __global__ __launch_bounds__(kStepsBlock) void k_source_steps(NeuronArgs a, Comp
         if (live && prow && (s || f) && t > (int64_t)tl) tl = (int)t;
         fired |= (uint32_t)s << k;
         forced |= (uint32_t)f << k;
-        const uint64_t m = ballot64(s), fm = ballot64(f);
-        const uint64_t rcm = ballot64(live && (st.h0 | st.h1) != 0ull);
-        if (lane == 0) {
-            s_m[k][wave] = m;
-            s_f[k][wave] = fm;
+        if (k == 0 && B > 1 && live) {
+            uint64_t *hp = b.hist0 + (int64_t)i * H;
+            hp[0] = st.h0;
+            if (H == 2) hp[1] = st.h1;
+            b.y0[i] = st.y;
         }
-        if (k < B - 1) {  // the step's versions (the last step's go to the state arrays)
-            if (live) {
-                uint64_t *hp = b.hist + k * nh + (int64_t)i * H;
-                hp[0] = st.h0;
-                if (H == 2) hp[1] = st.h1;
-                b.ypost[(int64_t)k * n + i] = st.y;
-                b.code[(int64_t)k * b.code_stride + i] = hist_code(st.h0, st.h1);
-            }
-            const int64_t word = (int64_t)blockIdx.x * NWV + wave;
-            if (lane == 0 && word * kWave < n) b.recent[(int64_t)k * lst.nw + word] = rcm;
-        } else {
-            const int64_t word = (int64_t)blockIdx.x * NWV + wave;
-            if (lane == 0 && word * kWave < n) {
+    }
+    // a forced update is deferred when no later event of the block follows (a
+    // row is forced at most once per block: 64 hw > B steps apart); the last
+    // step's always is, and keeps its own list
+    const uint32_t ev = fired | forced;
+    const uint32_t late = forced && (ev >> __ffs((int)forced)) == 0u ? forced : 0u;
+    const uint32_t lastbit = 1u << (B - 1);
+    const uint32_t listed = fired | (forced & ~late);
+    for (int k = 0; k < B; ++k) {
+        const uint64_t m = ballot64((listed >> k) & 1u);
+        if (lane == 0) s_m[k][wave] = m;
+    }
+    {
+        const uint64_t fm = ballot64(late & lastbit), dm = ballot64(late & ~lastbit);
+        const uint64_t m = ballot64(fired & lastbit);
+        const uint64_t rcm = ballot64(live && (st.h0 | st.h1) != 0ull);
+        const uint64_t rcb = ballot64(live && ((hs0 | hs1) != 0ull || fired));
+        const int64_t word = (int64_t)blockIdx.x * NWV + wave;
+        if (lane == 0) {
+            s_f[0][wave] = fm;
+            s_f[1][wave] = dm;
+            if (word * kWave < n) {
                 a.mask[word] = m;
                 a.txmask[word] = m;  // D = 1: the spikes of the step transmit
                 a.recent[word] = rcm;
+                b.recent[word] = rcb;
             }
         }
     }
-    if (live) neuron_commit(a, i, st);
-    __syncthreads();  // every step's ballots, s_st
-    // the workgroup's transmitted and forced counts of step `tid`, published
-    // for the scans
+    if (live) {
+        neuron_commit(a, i, st);
+        const uint64_t blk = (uint64_t)(__brev(fired) >> (32 - B));
+        uint64_t *q = b.hq + (int64_t)i * (2 * H);
+        q[0] = hs0;
+        if (H == 2) q[1] = hs1;
+        q[H] = blk;
+    }
+    __syncthreads();  // every ballot, s_st
+    // the workgroup's counts of step `tid`, published for the scans: its
+    // listed rows, and (in the last step's scan) that step's forced rows or
+    // (in the first step's, if another) the block's other forced rows
     int own_s = 0, own_f = 0;
     if (tid < B) {
         for (int w = 0; w < NWV; ++w) {
             own_s += __popcll(s_m[tid][w]);
-            own_f += __popcll(s_f[tid][w]);
+            own_f += tid == B - 1 ? __popcll(s_f[0][w]) : tid == 0 ? __popcll(s_f[1][w]) : 0;
         }
         publish_status(b.status + (int64_t)tid * b.status_stride + blockIdx.x,
                        status_word(own_s, own_f, t0 + tid,
                                    blockIdx.x == 0 ? kStatusInc : kStatusAgg));
     }
     lookback32<kStepsBlock>(b.status, b.status_stride, B, (int)blockIdx.x, t0, s_lb, lst.err);
-    if (tid < B && blockIdx.x > 0)
-        publish_status(b.status + (int64_t)tid * b.status_stride + blockIdx.x,
-                       status_word(s_lb[2 * tid] + own_s, s_lb[2 * tid + 1] + own_f, t0 + tid,
-                                   kStatusInc));
-    // the row's updates in step order, each at its place in its step's list:
-    // the earlier workgroups, then the earlier waves, then the earlier lanes
+    if (tid < B) {
+        if (blockIdx.x > 0)
+            publish_status(b.status + (int64_t)tid * b.status_stride + blockIdx.x,
+                           status_word(s_lb[2 * tid] + own_s, s_lb[2 * tid + 1] + own_f, t0 + tid,
+                                       kStatusInc));
+        // the chunks' places in the step's list (chunk c: from workgroup
+        // c grid / chunks on)
+        int32_t *sp = b.split + tid * (b.chunks + 1);
+        for (int c = 0; c < b.chunks; ++c)
+            if ((int)((int64_t)c * gridDim.x / b.chunks) == (int)blockIdx.x) sp[c] = s_lb[2 * tid];
+        if (blockIdx.x == gridDim.x - 1) sp[b.chunks] = s_lb[2 * tid] + own_s;
+    }
+    // the row's updates in step order, each at its place in its list: the
+    // earlier workgroups, then the earlier waves, then the earlier lanes
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     int tlw = tl0;
     float xp = xp0;
     long long n_rows = 0, n_forced = 0, n_syn = 0, n_fsyn = 0;
-    for (uint32_t ev = fired | forced; ev; ev &= ev - 1u) {
-        const int k = __ffs((int)ev) - 1;
+    for (uint32_t e = ev; e; e &= e - 1u) {
+        const int k = __ffs((int)e) - 1;
         const int64_t t = t0 + k;
         const int tx = (int)((fired >> k) & 1u);
         const bool last = k == B - 1;
@@ -936,31 +961,37 @@ __global__ __launch_bounds__(kStepsBlock) void k_source_steps(NeuronArgs a, Comp
                 }
             }
         }
-        if (tx) {
-            if (!ok) {  // nothing to bring up to date: the row is only delivered
-                ri = RowInfo{};
-                ri.k = i;
-                ri.rs = rs;
-            }
+        if (!ok) {  // nothing to bring up to date: the row is only delivered
+            ri = RowInfo{};
+            ri.k = i;
+            ri.rs = rs;
+        }
+        ri.pad = k | (tx ? kSrcTx : 0);
+        if ((listed >> k) & 1u) {
             int pos = s_lb[2 * k] + __popcll(s_m[k][wave] & below);
             for (int w = 0; w < wave; ++w) pos += __popcll(s_m[k][w]);
             // (only a failed scan puts a position out of range)
             if (pos < n) {
-                (last ? lst.ring : b.tx + (int64_t)k * n)[pos] = i;
+                if (last) lst.ring[pos] = i;
                 (last ? lst.txinfo : b.txinfo + (int64_t)k * n)[pos] = ri;
             } else {
                 atomicOr(lst.err, kErrRing);
             }
         } else {
-            int pos = s_lb[2 * k + 1] + __popcll(s_f[k][wave] & below);
-            for (int w = 0; w < wave; ++w) pos += __popcll(s_f[k][w]);
+            const int d = last ? 0 : 1;
+            int pos = s_lb[(last ? 2 * (B - 1) : 0) + 1] + __popcll(s_f[d][wave] & below);
+            for (int w = 0; w < wave; ++w) pos += __popcll(s_f[d][w]);
             if (pos < npl) {
-                (last ? lst.row_list : b.rows + (int64_t)k * npl)[pos] = i;
-                (last ? lst.info : b.info + (int64_t)k * npl)[pos] = ri;
+                if (last) lst.row_list[pos] = i;
+                (last ? lst.info : b.dinfo)[pos] = ri;
             } else {
                 atomicOr(lst.err, kErrRing);
             }
         }
+    }
+    if (prow && tlw != tl0) {
+        b.t_last[i] = tlw;
+        b.xpre[i] = xp;
     }
     if (lst.info_stats) {
         n_rows = wave_sum_i64(n_rows);
@@ -981,27 +1012,16 @@ __global__ __launch_bounds__(kStepsBlock) void k_source_steps(NeuronArgs a, Comp
             add_stat(sl + f, (long long)s_st[tid]);
         }
     }
-    // copies of the clock as the passes before the last expect it
-    if (blockIdx.x == 0 && tid < B - 1) {
-        StepClock c = ck;
-        c.t = t0 + tid + 1;
-        b.clk[tid] = c;
-    }
     if (blockIdx.x == gridDim.x - 1) {
         // every workgroup has read the clock: the scans saw all of them
-        if (tid < B) {
-            const int cs = s_lb[2 * tid] + own_s, cf = s_lb[2 * tid + 1] + own_f;
-            if (tid == B - 1) {
-                lst.ring_cnt[0] = cs;
-                *lst.tx_cnt = cs;
-                *lst.row_cnt = cf;
-            } else {
-                b.cnt[2 * tid] = cs;
-                b.cnt[2 * tid + 1] = cf;
-            }
-            add_stat(lst.gstats + kGSpikes, cs);
+        if (tid == B - 1) {
+            const int cs = s_lb[2 * tid] + own_s;
+            lst.ring_cnt[0] = cs;
+            *lst.tx_cnt = cs;
+            *lst.row_cnt = s_lb[2 * tid + 1] + own_f;
         }
         if (tid == 0) {
+            *b.dcnt = B > 1 ? s_lb[1] + own_f : 0;
             add_stat(lst.gstats + kGSteps, B);
             a.clk->t = t0 + B;
         }
@@ -1215,7 +1235,8 @@ hipError_t launch_source_steps(hipStream_t s, const NeuronArgs &a, const Compact
 {
     if (b.steps < 1 || b.steps > kSrcMaxSteps || a.model != 2 || c.delay != 1 ||
         c.n_plastic_rows < 1 || c.n_plastic_rows > a.n || (a.hw != 1 && a.hw != 2) ||
-        b.info_slots < 1 || b.status_stride < source_steps_grid(a.n) || c.segb)
+        b.info_slots < 1 || b.status_stride < source_steps_grid(a.n) || c.segb ||
+        b.chunks < 1 || b.chunks > kSrcMaxChunks)
         return hipErrorInvalidValue;
     if (a.hw == 2)
         launch_kernel(k_source_steps<2>, dim3(source_steps_grid(a.n)), dim3(kStepsBlock), 0, s,

@@ -137,15 +137,15 @@ struct snn_ctx {
     uint64_t *phq = nullptr;
     BlockClock *bclk = nullptr;
     // source blocks (SourceArgs: Bernoulli sources, D = 1, plastic): most
-    // steps per block (0: off) and the per-step versions of the arrays the
-    // synapse pass reads, for the steps before a block's last
-    int32_t sb_max = 0, sv_code_stride = 0;
-    uint64_t *sv_hist = nullptr, *sv_recent = nullptr;
-    float *sv_ypost = nullptr;
-    uint8_t *sv_code = nullptr;
-    int32_t *sv_tx = nullptr, *sv_rows = nullptr, *sv_cnt = nullptr;
-    RowInfo *sv_txinfo = nullptr, *sv_info = nullptr;
-    StepClock *sv_clk = nullptr;
+    // steps per block (0: off), row chunks per slice, delivery workgroups and
+    // resident workgroups of k_source_run, its LDS
+    int32_t sb_max = 0, sb_chunks = 1, sb_nd = 0, sb_slots = 0;
+    size_t sb_lds = 0;
+    int32_t parts = 1;  // partial inputs: the chunks of whichever delivery has more
+    uint64_t *sb_hist0 = nullptr, *sb_hq = nullptr, *sb_recent = nullptr;
+    float *sb_y0 = nullptr;
+    RowInfo *sb_txinfo = nullptr, *sb_dinfo = nullptr;
+    int32_t *sb_dcnt = nullptr, *sb_split = nullptr;
 
     // graph
     uint8_t *g = nullptr;
@@ -431,7 +431,7 @@ void plan_workspace(snn_ctx *c, uint8_t *base)
     c->ypost = p.take<float>(n);
     c->t_last = p.take<int32_t>(n);
     c->xpre = p.take<float>(n);
-    c->apart = p.take<long long>((int64_t)c->chunks * c->nacc * n);
+    c->apart = p.take<long long>((int64_t)c->parts * c->nacc * n);
     c->ain = p.take<float>((int64_t)c->nacc * n);
     c->mask = p.take<uint64_t>(c->nw);
     c->txmask = p.take<uint64_t>(c->nw);
@@ -470,19 +470,16 @@ void plan_workspace(snn_ctx *c, uint8_t *base)
     c->bclk = p.take<BlockClock>(1);
     c->one_mask = p.take<uint64_t>(c->one_gw > 0 ? 2 * (int64_t)c->nw : 1);
     {
-        const int64_t v = c->sb_max > 1 ? c->sb_max - 1 : 0;  // versions
-        const int64_t npl = std::max<int32_t>(c->n_plastic_rows, 1);
-        c->sv_code_stride = (int32_t)((n + 16 + 15) / 16 * 16);
-        c->sv_hist = p.take<uint64_t>(v ? v * n * c->hw : 1);
-        c->sv_ypost = p.take<float>(v ? v * n : 1);
-        c->sv_code = p.take<uint8_t>(v ? v * c->sv_code_stride : 1);
-        c->sv_recent = p.take<uint64_t>(v ? v * c->nw : 1);
-        c->sv_tx = p.take<int32_t>(v ? v * n : 1);
-        c->sv_txinfo = p.take<RowInfo>(v ? v * n : 1);
-        c->sv_rows = p.take<int32_t>(v ? v * npl : 1);
-        c->sv_info = p.take<RowInfo>(v ? v * npl : 1);
-        c->sv_cnt = p.take<int32_t>(v ? 2 * v : 1);
-        c->sv_clk = p.take<StepClock>(v ? v : 1);
+        const bool on = c->sb_max > 0;
+        const int64_t v = c->sb_max > 1 ? c->sb_max - 1 : 0;  // steps before a block's last
+        c->sb_hist0 = p.take<uint64_t>(v ? n * c->hw : 1);
+        c->sb_y0 = p.take<float>(v ? n : 1);
+        c->sb_hq = p.take<uint64_t>(on ? 2 * n * c->hw : 1);
+        c->sb_recent = p.take<uint64_t>(on ? c->nw : 1);
+        c->sb_txinfo = p.take<RowInfo>(v ? v * n : 1);
+        c->sb_dinfo = p.take<RowInfo>(v ? std::max<int32_t>(c->n_plastic_rows, 1) : 1);
+        c->sb_dcnt = p.take<int32_t>(1);
+        c->sb_split = p.take<int32_t>(on ? kSrcMaxSteps * (c->sb_chunks + 1) : 1);
     }
     c->ws_need = p.off;
 }
@@ -642,7 +639,7 @@ NeuronArgs neuron_args(snn_ctx *c)
     a.apart = c->apart;
     a.ain = c->ain;
     a.part_stride = (int64_t)c->nacc * c->n;
-    a.max_parts = c->chunks;
+    a.max_parts = c->parts;
     a.clk = c->clk;
     a.mask = c->mask;
     a.txmask = c->txmask;
@@ -790,7 +787,7 @@ size_t dlv_lds_bytes(const snn_ctx *c)
 }
 
 // Arguments of the synapse pass over the forced rows (flush: all rows).
-StdpArgs stdp_args(snn_ctx *c, bool flush, int64_t waves = 0)
+StdpArgs stdp_args(snn_ctx *c, bool flush, int64_t waves = 0, int32_t steps = 1)
 {
     if (waves <= 0) waves = (int64_t)c->n_cu * (kStdpRowsBlock / kWave);
     StdpArgs a{};
@@ -846,8 +843,8 @@ StdpArgs stdp_args(snn_ctx *c, bool flush, int64_t waves = 0)
     // one in 64 hw per step); ties keep the smaller P (fewer snapshot loads).
     const int part = (c->hw == 2 ? kStdpRowsUnroll2 : kStdpRowsUnroll) * kWave;
     const int64_t parts = std::max(1, (c->max_row + kStoreLine - 1 + part - 1) / part);
-    const int64_t rows = std::max<int64_t>(1, flush ? c->n_plastic_rows
-                                                    : c->n_plastic_rows / (64 * c->hw));
+    const int64_t rows = std::max<int64_t>(
+        1, flush ? c->n_plastic_rows : (int64_t)steps * c->n_plastic_rows / (64 * c->hw));
     int64_t best = -1;
     a.parts = 1;
     for (int pp = 1; pp <= kStdpRowsSplit && pp <= parts; ++pp) {
@@ -965,10 +962,8 @@ DeliverArgs deliver_args(snn_ctx *c)
 }
 
 // Parts (2) and (3) of a step in one launch (k_synapse_pass): delivery on
-// its usual work items, the forced rows on the CU slots left over. ver >= 0:
-// the step of a source block whose lists, histories, post traces, history
-// summaries, counts and clock are the block's version ver (SourceArgs).
-snn_status launch_step_synapse_pass(snn_ctx *c, KernelEvents ev, int ver = -1)
+// its work items, the forced rows on the CU slots left over.
+snn_status launch_step_synapse_pass(snn_ctx *c, KernelEvents ev)
 {
     DeliverArgs d = deliver_args(c);
     d.chunks = c->fuse_chunks;
@@ -976,23 +971,6 @@ snn_status launch_step_synapse_pass(snn_ctx *c, KernelEvents ev, int ver = -1)
     const int nd = (d.n_work + 7) / 8 * 8;
     const int ns = std::max(8, c->fuse_slots - nd);
     StdpArgs a = stdp_args(c, false, (int64_t)ns * (kDlvBlock / kWave));
-    if (ver >= 0) {
-        const int64_t n = c->n, npl = c->n_plastic_rows;
-        d.ring = c->sv_tx + ver * n;
-        d.ring_cnt = d.tx_cnt = c->sv_cnt + 2 * ver;
-        d.clk = c->sv_clk + ver;
-        d.txinfo = c->sv_txinfo + ver * n;
-        d.hist = c->sv_hist + ver * n * c->hw;
-        d.ypost = c->sv_ypost + ver * n;
-        a.info = c->sv_info + ver * npl;
-        a.row_cnt = c->sv_cnt + 2 * ver + 1;
-        a.tx_cnt = c->sv_cnt + 2 * ver;
-        a.clk = c->sv_clk + ver;
-        a.hist = d.hist;
-        a.ypost = d.ypost;
-        if (a.code) a.code = c->sv_code + ver * (int64_t)c->sv_code_stride;
-        if (a.recent) a.recent = c->sv_recent + ver * (int64_t)c->nw;
-    }
     const size_t table = a.xcd      ? (a.code ? (size_t)c->xcd_table : 0)
                          : a.code   ? (((size_t)c->n + 15) / 16) * 16
                          : a.recent ? (size_t)c->nw * sizeof(uint64_t)
@@ -1201,12 +1179,29 @@ snn_status snn_create(const snn_config *cfg, void *hip_stream, snn_ctx **out)
     // Source blocks (SourceArgs): plastic networks of Bernoulli sources with
     // D = 1, lazy plasticity, whose step runs the fused synapse pass on whole
     // forced rows; at most kSrcMaxSteps steps (or plastic_blocks) per block.
+    // The run's delivery workgroups (a slice and a chunk of the rows each)
+    // take half of the resident ones, the forced rows the rest.
     c->sb_max = 0;
+    c->parts = c->chunks;
     if (c->n_plastic_rows > 0 && c->algo != 2 && c->delay == 1 &&
         cfg->neuron_model == SNN_BERNOULLI_SOURCE && c->fuse && !c->xcd &&
-        cfg->plastic_blocks >= 0)
-        c->sb_max = cfg->plastic_blocks > 0 ? std::min<int32_t>(cfg->plastic_blocks, kSrcMaxSteps)
-                                            : kSrcMaxSteps;
+        cfg->plastic_blocks >= 0 && cfg->slice_width <= kSrcMaxW && c->nw <= kRecentMaxWords) {
+        const int rstat = source_run_static_bytes();
+        if (rstat < 0) return fail(c, SNN_EDEVICE, "cannot query the kernels");
+        c->sb_lds = std::max(source_run_lds(cfg->slice_width, c->hw),
+                             (size_t)c->nw * sizeof(uint64_t) + (size_t)fused_queue_bytes(c->hw));
+        const int per_cu = std::min<int>(2, (int)(lds_max / (int64_t)(c->sb_lds + rstat)));
+        c->sb_slots = c->n_cu * per_cu;
+        c->sb_chunks = std::max(1, std::min(c->sb_slots / 2 / c->n_slices, kSrcMaxChunks));
+        c->sb_nd = (c->n_slices * c->sb_chunks + 7) / 8 * 8;
+        if (per_cu >= 1 && c->sb_slots - c->sb_nd >= c->n_cu / 2) {
+            c->sb_max = cfg->plastic_blocks > 0
+                            ? std::min<int32_t>(cfg->plastic_blocks, kSrcMaxSteps)
+                            : kSrcMaxSteps;
+            c->parts = std::max(c->chunks, c->sb_chunks);
+            c->syn_slots = std::max(c->syn_slots, c->sb_slots);
+        }
+    }
     plan_workspace(c, nullptr);
     return SNN_OK;
 }
@@ -1234,7 +1229,7 @@ snn_status snn_bind_workspace(snn_ctx *c, void *device_ptr, size_t bytes)
     hipError_t e = launch_init_state(c->stream, c->v, c->ref, c->ie, c->ii, c->hist, c->ypost,
                                      c->t_last, c->xpre, c->n, c->hw);
     if (e == hipSuccess)
-        e = launch_fill_ll(c->stream, c->apart, (int64_t)c->chunks * c->nacc * c->n, 0);
+        e = launch_fill_ll(c->stream, c->apart, (int64_t)c->parts * c->nacc * c->n, 0);
     if (e == hipSuccess) e = launch_fill_f32(c->stream, c->ain, (int64_t)c->nacc * c->n, 0.f);
     if (e == hipSuccess) e = launch_fill_i32(c->stream, c->ring_cnt, c->delay, 0);
     if (e == hipSuccess) e = launch_fill_i32(c->stream, c->row_cnt, 1, 0);
@@ -1615,22 +1610,61 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
         c->last_neuron_t = c->last_deliver_t = c->t - 1;
         return SNN_OK;
     }
-    // a plastic network of Bernoulli sources with D = 1 runs in source
-    // blocks (see SourceArgs): one launch for the neuron updates and lists
-    // of up to sb_max steps, then the synapse pass of each step on its
-    // versions (the last step's are the state arrays). The scans' status
-    // words are cleared before and after, so that no word a different launch
-    // shape left can match a step tag. With kernel timing on, the block's
-    // launch is timed as the neuron part of its first step and each pass as
-    // the delivery part of its step.
     // (timed as configured: a pass with fewer workgroups per slice than asked
     // for runs as its parts while kernel times are being recorded)
     const bool whole = c->fuse_chunks == c->chunks || c->t_used >= c->t_cap;
-    const bool sblocks = mode == SNN_DELIVER_LDS_SLICE && c->sb_max > 0 && whole;
+    // a plastic network of Bernoulli sources with D = 1 runs in source
+    // blocks (see SourceArgs): one launch for the neuron updates and lists
+    // of up to sb_max steps, then one for the synapse part of all of them. The
+    // scans' status words are cleared before and after, so that no word a
+    // different launch shape left can match a step tag. With kernel timing
+    // on, the block's launches are timed as the neuron and delivery parts of
+    // its first step.
+    const bool sblocks = mode == SNN_DELIVER_LDS_SLICE && c->sb_max > 0 && whole &&
+                         c->n_edges > 0 && c->n_edges <= 0xFFFFFFFFll;
     if (sblocks && n_steps > 0) {
         if ((st = check_hip(c, clear_status(c), "clear the list scans"))) return st;
         NeuronArgs a = neuron_args(c);
         CompactArgs l = compact_args(c);
+        c->last_neuron_t = c->t;  // the history summaries are current below
+        const int ns = c->sb_slots - c->sb_nd;
+        StdpArgs r = stdp_args(c, false, (int64_t)ns * (kDlvBlock / kWave), c->sb_max);
+        r.row_cnt = c->sb_dcnt;
+        r.info = c->sb_dinfo;
+        r.info2 = c->info;
+        r.row_cnt2 = c->row_cnt;
+        r.hq = c->sb_hq;
+        r.code = nullptr;
+        r.recent = c->algo == 0 && c->cfg.stdp_filter != 3 ? c->sb_recent : nullptr;
+        SourceRunArgs d{};
+        d.n = c->n;
+        d.n_slices = c->n_slices;
+        d.width = c->cfg.slice_width;
+        d.chunks = c->sb_chunks;
+        d.n_work = c->n_slices * c->sb_chunks;
+        d.event = c->algo == 0;
+        d.n_edges = c->n_edges;
+        d.col = c->col;
+        d.col16 = c->col16;
+        d.w = c->w;
+        d.piv = c->piv;
+        d.hq = c->sb_hq;
+        d.txinfo = c->sb_txinfo;
+        d.txlast = c->txinfo;
+        d.split = c->sb_split;
+        d.apart = c->apart;
+        d.ain = c->ain;
+        d.clk = c->clk;
+        d.stats = c->dlv_stats;
+        d.stat_slots = c->dlv_slots;
+        d.syn_stats = c->syn_stats;
+        d.syn_slots = c->syn_slots;
+        d.gstats = c->gstats;
+        d.c_pot = c->c_pot;
+        d.c_dep = c->c_dep;
+        d.mu = c->mu;
+        d.d_minus = c->d_minus;
+        for (int q = 0; q <= kMaxAge; ++q) d.dpow[q] = c->dpow[q];
         for (int32_t q = 0; q < n_steps;) {
             const int32_t B = std::min<int32_t>(n_steps - q, c->sb_max);
             SourceArgs b{};
@@ -1638,27 +1672,29 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
             b.status_stride = c->status_stride;
             b.steps = B;
             b.info_slots = c->info_blocks;
-            b.code_stride = c->sv_code_stride;
-            b.hist = c->sv_hist;
-            b.ypost = c->sv_ypost;
-            b.code = c->sv_code;
-            b.recent = c->sv_recent;
-            b.tx = c->sv_tx;
-            b.txinfo = c->sv_txinfo;
-            b.rows = c->sv_rows;
-            b.info = c->sv_info;
-            b.cnt = c->sv_cnt;
-            b.clk = c->sv_clk;
+            b.chunks = c->sb_chunks;
+            b.hist0 = c->sb_hist0;
+            b.y0 = c->sb_y0;
+            b.hq = c->sb_hq;
+            b.recent = c->sb_recent;
+            b.txinfo = c->sb_txinfo;
+            b.dinfo = c->sb_dinfo;
+            b.dcnt = c->sb_dcnt;
+            b.split = c->sb_split;
+            b.t_last = c->t_last;
+            b.xpre = c->xpre;
             if ((st = check_hip(c, launch_source_steps(c->stream, a, l, b, part_events(c, 0)),
                                 "source block")))
                 return st;
-            c->last_neuron_t = c->t;  // the history summaries are current
-            for (int32_t k = 0; k < B; ++k) {
-                if ((st = launch_step_synapse_pass(c, part_events(c, 2), k < B - 1 ? k : -1)))
-                    return st;
-                if (c->t_used < c->t_cap) c->t_used += 1;
-                c->t += 1;
-            }
+            d.steps = r.steps = B;
+            d.hist0 = B > 1 ? c->sb_hist0 : c->hist;
+            d.y0 = B > 1 ? c->sb_y0 : c->ypost;
+            if ((st = check_hip(c, launch_source_run(c->stream, d, r, c->hw, c->sb_nd, ns,
+                                                     c->sb_lds, part_events(c, 2)),
+                                "source block run")))
+                return st;
+            c->t_used = std::min(c->t_used + B, c->t_cap);
+            c->t += B;
             q += B;
         }
         if ((st = check_hip(c, clear_status(c), "clear the list scans"))) return st;

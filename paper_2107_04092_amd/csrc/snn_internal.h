@@ -207,6 +207,13 @@ struct StdpArgs {
     int32_t xcd, xparts;
     const int32_t *segb;
     int32_t xlo[kXcds + 1];
+    // the forced rows of a source block (SourceArgs): info holds row_cnt of
+    // them, info2 the last step's (row_cnt2); histories from hq by the step
+    // of each (RowInfo::pad) of the block's `steps`; nothing is committed
+    const RowInfo *info2;
+    const int32_t *row_cnt2;
+    const uint64_t *hq;
+    int32_t steps;
     float dpow[kMaxAge + 1];
 };
 
@@ -484,40 +491,78 @@ struct BlockArgs {
     float dpow[kMaxAge + 1];
 };
 // Blocks of steps of a plastic network of Bernoulli sources with D = 1
-// (k_source_steps, then one synapse pass per step). A source fires on a
-// counter-based draw that no input changes, so one launch runs the neuron
-// update of B steps: each thread walks its neuron through them (spike,
-// history, post trace) and its row through the updates of each step
-// (transmitting, or forced by the history window), with t_last and x_pre
-// carried in registers from one update to the next exactly as the synapse
-// passes will commit them. For every step it writes what that step's pass
-// reads: the histories, post traces and history summaries after the step,
-// its transmitted and forced lists, ascending (one decoupled look-back per
-// step, the B scans together), their snapshots, their counts and a copy of
-// the clock. The last step of the block writes to the state arrays
-// themselves (ring slot, lists, counts, masks, clock), so after the block
-// the state is that of the step-by-step path; the steps before it write to
-// versions of those arrays in the workspace (step k at k times the stride
-// of each). The passes then run one per step, in order.
+// (k_source_steps, then k_source_run). A source fires on a counter-based draw
+// that no input changes, so one launch runs the neuron update of B steps:
+// each thread walks its neuron through them (spike, history, post trace) and
+// its row through the updates of each step (transmitting, or forced by the
+// history window), with t_last and x_pre carried in registers from one update
+// to the next, and commits them after the block. It writes
+//   - per step the rows to deliver or, forced and with a later event in the
+//     block, to bring up to date only (ascending, with their snapshots; the
+//     place of each chunk of rows in the list: `split`);
+//   - the other forced rows of the block (all but the last step's) in one
+//     list: no later event of the block reads their weights, so they can be
+//     brought up to date at any time during it;
+//   - each neuron's history words before the block with its spikes in it
+//     (hq), and who fired at all in either (recent);
+//   - the histories and post traces after the block's first step.
+// The last step's lists, snapshots, counts, masks and the clock are those of
+// the state, so after the block the state is that of the step-by-step path.
+// k_source_run then runs the synapse part of all B steps: a workgroup owns a
+// slice and a chunk of the rows through the block, so no workgroup waits for
+// another.
 struct SourceArgs {
     unsigned long long *status;  // [kBatchMax][status_stride]: step k's scan in row k
     int32_t status_stride;
     int32_t steps;               // B: 1 .. kSrcMaxSteps
     int32_t info_slots;          // statistics slots of CompactArgs::info_stats
-    int32_t code_stride;         // bytes per version of `code`
-    uint64_t *hist;              // versions: [B-1][n][hw]
-    float *ypost;                // [B-1][n]
-    uint8_t *code;               // [B-1][code_stride]
-    uint64_t *recent;            // [B-1][nw]
-    int32_t *tx;                 // [B-1][n]: the transmitted (= spike) list of the step
-    RowInfo *txinfo;             // [B-1][n]
-    int32_t *rows;               // [B-1][n_plastic_rows]: the forced rows
-    RowInfo *info;               // [B-1][n_plastic_rows]
-    int32_t *cnt;                // [B-1][2]: transmitted and forced counts
-    StepClock *clk;              // [B-1]: t = t0 + k + 1, as after the step's neuron update
+    int32_t chunks;              // row chunks (of whole workgroups of k_source_steps)
+    uint64_t *hist0;             // [n][hw], post traces [n]: after step 0 (B > 1)
+    float *y0;
+    uint64_t *hq;                // [n][2 hw]: history words before the block, then its spikes
+                                 // (bit 0: the last step)
+    uint64_t *recent;            // [nw]: fired in the block or in the history before it
+    RowInfo *txinfo;             // [B-1][n]: the steps' lists; RowInfo::pad: step | kSrcTx
+    RowInfo *dinfo;              // [n_plastic_rows]: forced rows without a later event
+    int32_t *dcnt;               // their number
+    int32_t *split;              // [kSrcMaxSteps][chunks + 1]
+    int32_t *t_last;
+    float *xpre;
 };
+constexpr int kSrcMaxChunks = 64;
+constexpr int kSrcTx = 1 << 8;  // RowInfo::pad of a list entry: delivered (step: bits 0-7)
 constexpr int kSrcMaxSteps = kBatchMax;  // steps per source block (one scan per half wave)
 
+// The synapse part of a source block (k_source_run): delivery of work items
+// (slice, chunk) on workgroups [0, nd), the listed forced rows on the others.
+constexpr int kSrcRecs = 704;   // rows staged at once
+constexpr int kSrcU = 11;       // entries per thread and window
+constexpr int kSrcMaxW = 4096;  // targets per slice
+struct SourceRunArgs {
+    int32_t n, n_slices, width, chunks, n_work, steps, event;
+    int64_t n_edges;
+    const int32_t *col;
+    const uint16_t *col16;
+    float *w;
+    const int32_t *piv;
+    const uint64_t *hist0, *hq;
+    const float *y0;
+    const RowInfo *txinfo, *txlast;  // steps before the last; the last
+    const int32_t *split;
+    long long *apart;
+    float *ain;
+    StepClock *clk;
+    int64_t *stats, *syn_stats, *gstats;
+    int32_t stat_slots, syn_slots;
+    float c_pot, c_dep, mu, d_minus;
+    float dpow[kMaxAge + 1];
+};
+// LDS of a delivery workgroup
+inline size_t source_run_lds(int width, int hw)
+{
+    return (size_t)kSrcRecs * 16 + (size_t)width * (8 + 8 * hw + 4) +
+           (size_t)kSrcU * 512 * sizeof(uint16_t) + 512;
+}
 hipError_t launch_block_plan(hipStream_t s, const BlockArgs &b);
 hipError_t launch_block_run(hipStream_t s, const NeuronArgs &a, const BlockArgs &b);
 hipError_t launch_block_deferred(hipStream_t s, const BlockArgs &b);
@@ -639,6 +684,10 @@ hipError_t launch_deliver_lds(hipStream_t s, const DeliverArgs &a, int blocks, s
 // forced-row STDP on ns more, kDlvBlock threads each; lds covers both
 hipError_t launch_synapse_pass(hipStream_t s, const DeliverArgs &d, const StdpArgs &a, int nd,
                                int ns, size_t lds, KernelEvents ev = {});
+// k_source_run: nd delivery workgroups (a multiple of 8), ns for the forced rows
+hipError_t launch_source_run(hipStream_t s, const SourceRunArgs &d, const StdpArgs &a, int hw,
+                             int nd, int ns, size_t lds, KernelEvents ev = {});
+int source_run_static_bytes();  // static LDS of k_source_run (-1 on error)
 hipError_t launch_deliver_global(hipStream_t s, const DeliverArgs &a, int blocks, KernelEvents ev = {});
 int deliver_lds_static_bytes();  // static LDS of the slice kernel (-1 on error)
 int synapse_pass_static_bytes();  // static LDS of the fused synapse pass (-1 on error)

@@ -1,0 +1,52 @@
+"""The synapse part of a source block in one launch, where it can go wrong:
+many chunks and one, chunks without rows, more rows than are staged at once,
+more entries than a window, segments longer than the direct map's, rows forced
+and delivered in the same block, rows that are only delivered (exc -> exc
+plasticity), the widest slices, blocks of one step and blocks cut short. Equal
+to the step-by-step path bit for bit."""
+
+import pytest
+
+import workloads as wl
+from workloads.presets import PLASTIC_EXC_EXC
+from paper_2107_04092_amd import snn
+
+from gpu_common import gpu_net, log, same_state
+
+pytestmark = pytest.mark.gpu
+LDS = snn.SNN_DELIVER_LDS_SLICE
+
+CASES = [
+    # preset overrides, slice width, chunks, extra config
+    (dict(n=64, p_or_fanout=50, p_fire=0.05), 64, 1, dict()),
+    (dict(n=513, p_or_fanout=300, p_fire=0.02), 512, 2, dict(history_bits=128)),
+    (dict(n=2000, p_or_fanout=900, p_fire=0.01), 4096, 3, dict()),
+    (dict(n=30000, p_or_fanout=40, p_fire=0.3), 2048, 1, dict()),
+    (dict(n=6000, p_or_fanout=3000, p_fire=0.05), 2048, 2, dict(compressed_targets=0)),
+    (dict(n=9001, n_exc=4001, p_or_fanout=200, p_fire=0.02, plastic=PLASTIC_EXC_EXC), 1024, 1,
+     dict(history_bits=128)),
+    # one in seven rows of a block both forced and delivered in it
+    (dict(n=20011, p_or_fanout=100, p_fire=0.008), 1024, 4, dict()),
+    (dict(n=20011, p_or_fanout=100, p_fire=0.008), 640, 1, dict(plastic_blocks=1)),
+    (dict(n=20011, p_or_fanout=64, p_fire=0.004), 2048, 2,
+     dict(plastic_blocks=2, history_bits=128)),
+    (dict(n=100003, p_or_fanout=20, p_fire=0.005), 2048, 2, dict(stdp_filter=3)),
+    (dict(n=5000, p_or_fanout=100, p_fire=0.02), 512, 1, dict(plasticity_algorithm=1)),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%d-w%d-c%d" % (c[0]["n"], c[1], c[2]))
+def test_run_equals_step_by_step(case):
+    kw, width, chunks, cfg = case
+    p = wl.preset("stress", **kw)
+    log("source run: %s width %d %s" % (kw, width, cfg))
+    a = gpu_net(p, slice_width=width, spike_chunks=chunks, **cfg)
+    b = gpu_net(p, slice_width=width, spike_chunks=chunks, **dict(cfg, plastic_blocks=-1))
+    assert a.graph()["block_steps"] > 0
+    for k in (1, 2, 70, 17, 131):
+        a.step(k, LDS)
+        b.step(k, LDS)
+        same_state(a, b, "%d steps" % k)
+    a.flush_plasticity()
+    b.flush_plasticity()
+    same_state(a, b, "flush")
