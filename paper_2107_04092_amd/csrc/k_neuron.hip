@@ -906,6 +906,7 @@ __global__ __launch_bounds__(kStepsBlock) void k_source_steps(NeuronArgs a, Comp
         q[0] = hs0;
         if (H == 2) q[1] = hs1;
         q[H] = blk;
+        b.code[i] = src_code(hs0, hs1, (uint32_t)blk);
     }
     __syncthreads();  // every ballot, s_st
     // the workgroup's counts of step `tid`, published for the scans: its
@@ -1236,7 +1237,8 @@ hipError_t launch_source_steps(hipStream_t s, const NeuronArgs &a, const Compact
     if (b.steps < 1 || b.steps > kSrcMaxSteps || a.model != 2 || c.delay != 1 ||
         c.n_plastic_rows < 1 || c.n_plastic_rows > a.n || (a.hw != 1 && a.hw != 2) ||
         b.info_slots < 1 || b.status_stride < source_steps_grid(a.n) || c.segb ||
-        b.chunks < 1 || b.chunks > kSrcMaxChunks)
+        b.chunks < 1 || b.chunks > kSrcMaxChunks || !b.hist0 || !b.y0 || !b.hq || !b.code ||
+        !b.recent || !b.txinfo || !b.dinfo || !b.dcnt || !b.split || !b.t_last || !b.xpre)
         return hipErrorInvalidValue;
     if (a.hw == 2)
         launch_kernel(k_source_steps<2>, dim3(source_steps_grid(a.n)), dim3(kStepsBlock), 0, s,

@@ -264,8 +264,13 @@ __device__ __forceinline__ void rows_issue(RowPart<U> &p, const int32_t *col, co
 }
 
 // BLK: the forced rows of a source block (StdpArgs::hq): two lists of rows,
-// each target's history at the row's step from its words before the block
-// under the block's spikes (as k_block_deferred), nothing committed.
+// each target's spikes up to the row's step from one word per neuron
+// (src_code; beyond its capacity from the history words before the block under
+// the block's spikes), nothing committed. The word is why the gathers hit the
+// L2: 250,000 neurons' words are 2 MB, their histories with the block's spikes
+// 8 MB, and the half of a row's synapses that are looked up drew 64 bytes of
+// those each from beyond it (run launches of the
+// stress network: 323 -> 283 us).
 template <int NT, int U, int HW, bool BLK = false>
 __device__ __forceinline__ void stdp_rows_body(const StdpArgs &a, int bid, int nblocks,
                                                unsigned char *s_sum)
@@ -400,14 +405,12 @@ __device__ __forceinline__ void stdp_rows_body(const StdpArgs &a, int bid, int n
             constexpr int H = U / 2;
             if (half * H * kWave >= qn) break;  // wave-uniform
             uint64_t h[H], g[H];
-            uint32_t bk[H];
             float y[H], qw[H];
             int cd[H];
 #pragma unroll
             for (int q = 0; q < H; ++q) {
                 const int e0 = (half * H + q) * kWave;
                 h[q] = g[q] = 0ull;
-                bk[q] = 0u;
                 y[q] = qw[q] = 0.f;
                 cd[q] = 0;
                 if (e0 < qn) {  // wave-uniform
@@ -417,11 +420,9 @@ __device__ __forceinline__ void stdp_rows_body(const StdpArgs &a, int bid, int n
                     if (!pre && a.code) {
                         cd[q] = s_code[j];
                         gather_hist<HW>(hist, cd[q] == kCodeMulti ? j : 0, h[q], g[q]);
-                    } else if (BLK) {  // the words before the block; its spikes
-                        const uint64_t *hp = a.hq + (int64_t)j * (2 * HW);
-                        h[q] = hp[0];
-                        if (HW == 2) g[q] = hp[1];
-                        bk[q] = (uint32_t)hp[HW];
+                    } else if (BLK) {
+                        h[q] = a.hcode[j];
+                        cd[q] = j;
                     } else {
                         gather_hist<HW>(hist, j, h[q], g[q]);
                     }
@@ -433,10 +434,22 @@ __device__ __forceinline__ void stdp_rows_body(const StdpArgs &a, int bid, int n
                 const int e = (half * H + q) * kWave + lane;
                 if (e < qn) {
                     uint64_t h0 = h[q], h1 = g[q];
-                    if (BLK) {  // shifted to the row's step qs, under the spikes up to it
+                    if (BLK) {
                         const int qs = ri.pad & 0xff;
-                        if (HW == 2) h1 = (h1 << (qs + 1)) | (h0 >> (63 - qs));
-                        h0 = (h0 << (qs + 1)) | (uint64_t)(bk[q] >> (a.steps - 1 - qs));
+                        if (a.event && (int)(h0 >> 35 & 7) != kSrcOver) {
+                            bool chg;
+                            q_w[e] = stdp_synapse_code(qw[q], h0, qs, a.steps, age, ri.xp0,
+                                                       ri.xp_now, s_dpow, c_pot, mu, chg);
+                            q_j[e] = chg ? 1 : 0;
+                            written += chg;
+                            continue;
+                        }
+                        // the history words before the block, shifted to the
+                        // row's step under the block's spikes up to it
+                        const uint64_t *hp = a.hq + (int64_t)cd[q] * (2 * HW);
+                        const uint64_t s0 = hp[0], bk = h0 >> 48;
+                        if (HW == 2) h1 = (hp[1] << (qs + 1)) | (s0 >> (63 - qs));
+                        h0 = (s0 << (qs + 1)) | (bk >> (a.steps - 1 - qs));
                     }
                     if (!pre && a.code && cd[q] != kCodeMulti) {
                         const int ps = (cd[q] - 1) & 127;  // single spike: ps steps ago
@@ -1666,7 +1679,7 @@ hipError_t launch_source_run(hipStream_t s, const SourceRunArgs &d, const StdpAr
         d.chunks < 1 || d.chunks > kSrcMaxChunks || d.n_work != d.n_slices * d.chunks ||
         nd % 8 != 0 || nd < d.n_work || ns < 1 || d.n_edges < 1 || d.n_edges > 0xFFFFFFFFll ||
         d.stat_slots < 1 || d.syn_slots < nd + ns || (hw != 1 && hw != 2) || !a.hq || a.code ||
-        a.n_info < 1 || lds < source_run_lds(d.width, hw))
+        !a.hcode || a.n_info < 1 || lds < source_run_lds(d.width, hw))
         return hipErrorInvalidValue;
     const bool ct = d.col16 != nullptr;
     if (hw == 2)

@@ -142,7 +142,7 @@ struct snn_ctx {
     int32_t sb_max = 0, sb_chunks = 1, sb_nd = 0, sb_slots = 0;
     size_t sb_lds = 0;
     int32_t parts = 1;  // partial inputs: the chunks of whichever delivery has more
-    uint64_t *sb_hist0 = nullptr, *sb_hq = nullptr, *sb_recent = nullptr;
+    uint64_t *sb_hist0 = nullptr, *sb_hq = nullptr, *sb_code = nullptr, *sb_recent = nullptr;
     float *sb_y0 = nullptr;
     RowInfo *sb_txinfo = nullptr, *sb_dinfo = nullptr;
     int32_t *sb_dcnt = nullptr, *sb_split = nullptr;
@@ -475,6 +475,7 @@ void plan_workspace(snn_ctx *c, uint8_t *base)
         c->sb_hist0 = p.take<uint64_t>(v ? n * c->hw : 1);
         c->sb_y0 = p.take<float>(v ? n : 1);
         c->sb_hq = p.take<uint64_t>(on ? 2 * n * c->hw : 1);
+        c->sb_code = p.take<uint64_t>(on ? n : 1);
         c->sb_recent = p.take<uint64_t>(on ? c->nw : 1);
         c->sb_txinfo = p.take<RowInfo>(v ? v * n : 1);
         c->sb_dinfo = p.take<RowInfo>(v ? std::max<int32_t>(c->n_plastic_rows, 1) : 1);
@@ -1634,6 +1635,7 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
         r.info2 = c->info;
         r.row_cnt2 = c->row_cnt;
         r.hq = c->sb_hq;
+        r.hcode = c->sb_code;
         r.code = nullptr;
         r.recent = c->algo == 0 && c->cfg.stdp_filter != 3 ? c->sb_recent : nullptr;
         SourceRunArgs d{};
@@ -1676,6 +1678,7 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
             b.hist0 = c->sb_hist0;
             b.y0 = c->sb_y0;
             b.hq = c->sb_hq;
+            b.code = c->sb_code;
             b.recent = c->sb_recent;
             b.txinfo = c->sb_txinfo;
             b.dinfo = c->sb_dinfo;

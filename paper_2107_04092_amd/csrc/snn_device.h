@@ -376,6 +376,57 @@ __device__ __forceinline__ float stdp_synapse_steps(float w, uint64_t h0, uint64
     return w;
 }
 
+// A neuron's spikes before and in a source block in one word: the steps before
+// the block that the newest kSrcPos spikes of its history happened (7 bits
+// each from bit 0 on, 0 = the step before the block), their number (bits
+// 35-37; kSrcOver: there are more, see the history words) and the spikes in
+// the block (bits 48-63, bit 48: the last step).
+constexpr int kSrcPos = 5, kSrcOver = 7;
+__device__ __forceinline__ uint64_t src_code(uint64_t h0, uint64_t h1, uint32_t blk)
+{
+    const int np = __popcll(h0) + __popcll(h1);
+    uint64_t c = (uint64_t)(np > kSrcPos ? kSrcOver : np) << 35 | (uint64_t)blk << 48;
+    for (int k = 0; k < kSrcPos && (h0 | h1); ++k) {
+        const int p = h0 ? __ffsll((long long)h0) - 1 : 63 + __ffsll((long long)h1);
+        if (h0)
+            h0 &= h0 - 1ull;
+        else
+            h1 &= h1 - 1ull;
+        c |= (uint64_t)p << (7 * k);
+    }
+    return c;
+}
+
+// stdp_synapse without a pre spike for a row of step qs of a block of `steps`
+// steps, from the target's src_code (at most kSrcPos spikes before the block):
+// the same updates in the same order. Returns the new weight; changed: whether
+// a post spike lay in the window.
+__device__ __forceinline__ float stdp_synapse_code(float w, uint64_t code, int qs, int steps,
+                                                   int age, float xp0, float xp_now,
+                                                   const float *dpow, float c_pot, float mu,
+                                                   bool &changed)
+{
+    changed = false;
+    for (int k = (int)(code >> 35 & 7) - 1; k >= 0; --k) {  // before the block, oldest first
+        const int back = (int)(code >> (7 * k) & 127) + qs + 1;  // steps before step qs
+        if (back < age) {
+            w = w + c_pot * pow_mu(w, mu) * __fmul_rn(xp0, dpow[age - back]);
+            changed = true;
+        }
+    }
+    uint32_t b = (uint32_t)(code >> 48) >> (steps - 1 - qs);  // in the block, up to step qs
+    if (age < 16) b &= (1u << age) - 1u;
+    if (b) changed = true;
+    uint32_t older = b & ~1u;
+    while (older) {
+        const int bit = 31 - __clz((int)older);
+        older ^= 1u << bit;
+        w = w + c_pot * pow_mu(w, mu) * __fmul_rn(xp0, dpow[age - bit]);
+    }
+    if (b & 1u) w = w + c_pot * pow_mu(w, mu) * xp_now;  // post at the row's step
+    return w;
+}
+
 // Delay-ring slot of a step (steps before 0 wrap like the ring).
 __device__ __forceinline__ int ring_slot(int64_t step, int d)
 {

@@ -212,7 +212,7 @@ struct StdpArgs {
     // of each (RowInfo::pad) of the block's `steps`; nothing is committed
     const RowInfo *info2;
     const int32_t *row_cnt2;
-    const uint64_t *hq;
+    const uint64_t *hq, *hcode;
     int32_t steps;
     float dpow[kMaxAge + 1];
 };
@@ -521,6 +521,7 @@ struct SourceArgs {
     float *y0;
     uint64_t *hq;                // [n][2 hw]: history words before the block, then its spikes
                                  // (bit 0: the last step)
+    uint64_t *code;              // [n]: the same in one word (src_code)
     uint64_t *recent;            // [nw]: fired in the block or in the history before it
     RowInfo *txinfo;             // [B-1][n]: the steps' lists; RowInfo::pad: step | kSrcTx
     RowInfo *dinfo;              // [n_plastic_rows]: forced rows without a later event
