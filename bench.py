@@ -16,8 +16,9 @@ itself on the library's stream, which gives per-kernel device times (the
 events widen the gaps between kernels, so the timed region runs without
 them).
 
-The roofline figure of the dominant kernel (the fused synapse pass, or the
-forced-row STDP where the step runs it alone) divides the method's
+The roofline figure of the dominant kernel (the synapse part of a source
+block, the fused synapse pass, or the forced-row STDP where the step runs it
+alone) divides the method's
 algorithmic bytes per step by the kernel's device time. Those bytes follow
 the survey's per-step count (targets and weights read and changed weights
 written per STDP synapse update, row state per triggered row, the gathered
@@ -151,7 +152,8 @@ def write_traffic(fetch_db, write_db, workload_key, copy_mib):
     path = os.path.join(ROOT, "profiles", "traffic.json")
     d = json.load(open(path)) if os.path.exists(path) else {}
     out = {}
-    for k in ("k_neuron", "k_source_steps", "k_synapse_pass", "k_deliver_lds", "k_stdp_rows"):
+    for k in ("k_neuron", "k_source_steps", "k_source_run", "k_synapse_pass", "k_deliver_lds",
+              "k_stdp_rows"):
         f, w = vals[k]["FETCH_SIZE"], vals[k]["WRITE_SIZE"]
         if not f or not w:
             continue
@@ -416,18 +418,22 @@ def main():
         b_dlv = delivery_bytes(st2, p.n, n_slices, chunks, nacc, args.steps,
                                args.mode, tb, hbits // 64) / args.steps
         t_neu, t_stdp, t_dlv = kt["neuron"], kt["plasticity"], kt["delivery"]
-        # a plastic network of Bernoulli sources with D = 1 runs its neuron
-        # updates in source blocks: one launch per block of steps
-        nsteps = (net.graph()["block_steps"] or 1) if (
+        # a plastic network of Bernoulli sources with D = 1 runs in source
+        # blocks: one launch for the neuron updates and one for the synapse
+        # part of up to block_steps steps; the times are per launch
+        block = (net.graph()["block_steps"] or 1) if (
             p.model == snn.SNN_BERNOULLI_SOURCE and p.delay == 1 and p.plastic != 0
             and args.mode == "lds") else 1
+        nsteps = args.steps / -(-args.steps // block)  # steps per launch, on average
+        t_dlv_launch, t_dlv = t_dlv, t_dlv / nsteps
         kernels = {
             "steps_timed": nrec,
             "neuron_us": round(t_neu * 1e3, 3),
-            "neuron_steps_per_launch": nsteps,
+            "neuron_steps_per_launch": round(nsteps, 3),
             "neuron_us_per_step": round(t_neu * 1e3 / nsteps, 3),
             "plasticity_us": round(t_stdp * 1e3, 3),
-            "delivery_us": round(t_dlv * 1e3, 3),
+            "delivery_us": round(t_dlv_launch * 1e3, 3),
+            "delivery_us_per_step": round(t_dlv * 1e3, 3),
             "fused_synapse_pass": bool(p.plastic != 0 and t_stdp == 0 and t_dlv > 0),
             "plasticity_bytes_per_launch": int(b_stdp),
             "delivery_bytes_per_launch": int(b_dlv),
@@ -446,7 +452,7 @@ def main():
         sb = survey_bytes(st2, args.steps, p.n, n_slices, chunks, nacc,
                           fused or (args.mode == "lds" and p.plastic != 0))
         if fused:
-            kname = "k_synapse_pass"
+            kname = "k_source_run" if block > 1 else "k_synapse_pass"
             t_k = t_dlv
             alg = sb["algorithmic"]
             written = sb["as_written"]
@@ -465,12 +471,13 @@ def main():
             roofline = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
                         "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
                         "traffic": traffic, "kernel": kname,
-                        "kernel_us": round(t_k * 1e3, 3),
-                        "bytes_per_launch": int(alg),
-                        "bytes_as_written": int(written),
+                        "kernel_us": round(t_k * 1e3 * nsteps, 3),
+                        "steps_per_launch": round(nsteps, 3),
+                        "bytes_per_launch": int(alg * nsteps),
+                        "bytes_as_written": int(written * nsteps),
                         "frac_as_written": round(written / (t_k * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                        "implementation_bytes_per_launch": int(impl),
-                        "traffic_over_algorithmic": (round(traffic / alg, 3)
+                        "implementation_bytes_per_launch": int(impl * nsteps),
+                        "traffic_over_algorithmic": (round(traffic / (alg * nsteps), 3)
                                                      if traffic else None)}
             comb = sb["algorithmic"] / ((t_stdp + t_dlv) * 1e-3) / 1e9
             combined = {"achieved_GBs": round(comb, 1), "frac": round(comb / HBM_PEAK_GBS, 4),
@@ -478,7 +485,7 @@ def main():
                         "survey_bytes_per_step": {k: int(v) for k, v in sb.items()}}
 
     ceiling = None
-    if roofline is not None and kname in ("k_stdp_rows", "k_synapse_pass") and \
+    if roofline is not None and kname in ("k_stdp_rows", "k_synapse_pass", "k_source_run") and \
             not args.no_row_probe:
         # the forced-row access pattern without its arithmetic, at the same
         # row count: targets and weights streamed (8 B per synapse), then
