@@ -337,6 +337,7 @@ class Network:
         snn_bind_workspace(self.ctx, self.ws.data_ptr() + self._ws_off, nbytes)
         self.g = None
         self.n_edges = None
+        self._views = {}
 
     def close(self):
         if getattr(self, "ctx", None):
@@ -353,6 +354,7 @@ class Network:
     def _bind_graph(self, n_edges):
         torch = self._torch
         nbytes = snn_graph_size(self.ctx, n_edges)
+        self._views.clear()
         with torch.cuda.stream(self.stream):
             self.g = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
         self._g_off = (-self.g.data_ptr()) % 256
@@ -427,14 +429,20 @@ class Network:
 
     # views ---------------------------------------------------------------
     def _view(self, buf, ptr, count, dtype):
-        torch = self._torch
+        # A view of the workspace or graph buffer, made once per place: state()
+        # makes twenty, 2-3 us each, beside a step of a few microseconds. Kept
+        # with the buffer it looks into (dropped when a graph is bound).
         if not ptr or count == 0:
-            return torch.empty(0, dtype=dtype, device=self.device)
-        off = ptr - buf.data_ptr()
-        nbytes = count * torch.empty(0, dtype=dtype).element_size()
-        if off < 0 or off + nbytes > buf.numel():
-            raise RuntimeError("view outside its buffer")
-        return buf[off:off + nbytes].view(dtype)
+            return self._torch.empty(0, dtype=dtype, device=self.device)
+        key = (ptr, count, dtype)
+        made = self._views.get(key)
+        if made is None or made[0] is not buf:
+            off = ptr - buf.data_ptr()
+            nbytes = count * dtype.itemsize
+            if off < 0 or off + nbytes > buf.numel():
+                raise RuntimeError("view outside its buffer")
+            made = self._views[key] = (buf, buf[off:off + nbytes].view(dtype))
+        return made[1].detach()  # a tensor object of the caller's own
 
     def state(self):
         """Zero-copy torch views of the device state (see snn_state_view)."""
