@@ -550,7 +550,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_step_one(NeuronArgs a, StepOneA
     extern __shared__ long long acc[];  // NACC * NP
     __shared__ int s_list[kOneList];
     __shared__ long long sh[NWV];
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const int tid = threadIdx.x, lane = tid % kWave;
     const int n = a.n, nw = (n + kWave - 1) / kWave;  // nw <= kSmallBlock
     const int g = blockIdx.x;
     const int glo = g * b.gw, ghi = min(glo + b.gw, n);

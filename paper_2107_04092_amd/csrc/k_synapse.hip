@@ -853,10 +853,6 @@ __global__ __launch_bounds__(kNaiveBlock) void k_stdp_naive(NaiveArgs a)
 // and then delivered, so the row's targets and weights are read once. The
 // workgroups of slice 0 commit t_last and the pre traces of their spikes.
 //
-// In a delay block (networks without plasticity) the grid also spans the
-// block's steps: item (b, slice) takes ring slot (t_emit0 + b) mod D and
-// writes the fixed-point input of its step to abatch, one chunk per item.
-//
 // The spike count is read first and only the spikes below it are read
 // (a network with few spikes per step would otherwise read a whole batch of
 // snapshots per workgroup), and the workgroup's statistics are reduced
@@ -888,33 +884,20 @@ __device__ __forceinline__ void deliver_lds_body(const DeliverArgs &a, int bid, 
     unsigned long long &s_written = S.written;
     int &s_nlong = S.nlong;
     const int tid = threadIdx.x;
-    const int qa = (bid & 7) * (nb >> 3) + (bid >> 3);
-    if (qa >= a.n_work) return;  // whole workgroup, before any barrier
-    // a delay block's item (b, slice, chunk) takes step b's ring list and
-    // writes partial sums of step b (b varies slowest: an XCD's range of
-    // items covers neighbouring slices)
-    // step t = clk->t - 1 delivers the spikes of step t - D + 1; a delay
-    // block starting at step t0 = clk->t delivers those of t0 + 1 - D + b
+    const int q = (bid & 7) * (nb >> 3) + (bid >> 3);
+    if (q >= a.n_work) return;  // whole workgroup, before any barrier
+    // step t = clk->t - 1 delivers the spikes of step t - D + 1
     const int64_t t = a.clk->t - 1;
-    int slot = ring_slot(t - (a.delay - 1), a.delay);
-    long long *parts = a.apart;
-    int q = qa;
-    if (a.batch > 0) {
-        const int per = a.n_slices * a.chunks;
-        const int bb = qa / per;
-        q = qa - bb * per;
-        slot = ring_slot(t + 2 - a.delay + bb, a.delay);
-        parts = a.abatch + (int64_t)bb * a.chunks * a.part_stride;
-    } else if (qa == 0 && threadIdx.x == 0) {
+    const int slot = ring_slot(t - (a.delay - 1), a.delay);
+    if (q == 0 && threadIdx.x == 0) {
         // the next neuron update reads this delivery's output: the fp32
         // input with one chunk, else the C partial sums
         a.clk->input_forced = a.chunks == 1 ? 1 : 0;
         a.clk->n_parts = a.chunks;
     }
-    // (the count of a single step's transmitted list is at a fixed address:
-    // loading it does not wait for the clock)
+    // (the transmitted list's count is at a fixed address: loading it does not
+    // wait for the clock)
     const int32_t *list = a.ring + (int64_t)slot * a.n;
-    const int32_t *cntp = a.batch > 0 ? a.ring_cnt + slot : a.tx_cnt;
     const int s = q / a.chunks, c = q - s * a.chunks;
     const int C = a.chunks;
     const int base = s * a.width;
@@ -922,7 +905,7 @@ __device__ __forceinline__ void deliver_lds_body(const DeliverArgs &a, int bid, 
     // the count first (one scalar load), then the first batch's snapshots
     // (or list entries) below it, before the staging loads, so the two
     // round trips overlap: spikes j = rr kDlvBlock + tid
-    const int cnt = *cntp;
+    const int cnt = *a.tx_cnt;
     RowInfo ri0[kDlvRounds];
     int k0[kDlvRounds];
 #pragma unroll
@@ -1140,7 +1123,7 @@ __device__ __forceinline__ void deliver_lds_body(const DeliverArgs &a, int bid, 
         add_stat(a.stats + 2 * (int64_t)bid, ev);
         add_stat(a.stats + 2 * (int64_t)bid + 1, (long long)s_written);
     }
-    if (a.chunks == 1 && a.batch == 0) {
+    if (a.chunks == 1) {
         for (int x = tid; x < a.width; x += kDlvBlock) {
             const int j = base + x;
             if (j < a.n) {
@@ -1149,7 +1132,7 @@ __device__ __forceinline__ void deliver_lds_body(const DeliverArgs &a, int bid, 
             }
         }
     } else {
-        long long *out = parts + (int64_t)c * a.part_stride;
+        long long *out = a.apart + (int64_t)c * a.part_stride;
         for (int x = tid; x < a.width; x += kDlvBlock) {
             const int j = base + x;
             if (j < a.n) {
@@ -1168,7 +1151,105 @@ __global__ __launch_bounds__(kDlvBlock, 4) void k_deliver_lds(DeliverArgs a)
     deliver_lds_body<CT, int>(a, blockIdx.x, gridDim.x, reinterpret_cast<unsigned char *>(dyn_dlv));
 }
 
-// Fused synapse pass of one step: the forced rows' plasticity and slice
+// Delivery of a delay block (networks without plasticity, D >= 2): the inputs
+// of all its steps, before its neuron launch. Work item (b, slice) adds the
+// rows of the spikes emitted at step t0 + 1 - D + b (t0 = clk->t, the block's
+// first step) onto the slice's targets, in LDS as above, and writes the
+// fixed-point input of step t0 + 1 + b. The steps are the parallelism, so
+// there is one item per slice and step, and what bounds it is how many loads
+// of row segments are in flight: nothing is updated, so no entry needs to
+// know its place in its row, and a team of lanes takes RU whole segments at a
+// time (U entries of each per lane; a longer segment's rest after them),
+// without the flattened entries' scan, map and barriers of
+// deliver_lds_body, in 64 registers, so that a CU holds 32 waves instead of
+// 16. 14 steps of 62,500 neurons (868 items, 100 segments of 102 entries
+// each): 42 -> 20 us, 57 MB at 2.8 TB/s.
+constexpr int kBdRows = 1024;  // segments looked up at once
+
+template <bool CT, int RU, int U>
+__global__ __launch_bounds__(kBdBlockMax, 8) void k_deliver_block(DeliverArgs a, int lg_team)
+{
+    extern __shared__ uint4 dyn_bd[];
+    int64_t *s_start = reinterpret_cast<int64_t *>(dyn_bd);   // kBdRows
+    int *s_len = reinterpret_cast<int *>(s_start + kBdRows);  // kBdRows: entries, bit 30: inhibitory
+    long long *acc = reinterpret_cast<long long *>(s_len + kBdRows);  // nacc * W
+    __shared__ unsigned long long s_ev;
+    const int tid = threadIdx.x, nt = blockDim.x, nb = gridDim.x;
+    const int q = (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);
+    if (q >= a.n_work) return;  // whole workgroup, before any barrier
+    // (b varies slowest: an XCD's range of items covers neighbouring slices)
+    const int b = q / a.n_slices, s = q - b * a.n_slices;
+    const int slot = ring_slot(a.clk->t + 1 - a.delay + b, a.delay);
+    const int32_t *list = a.ring + (int64_t)slot * a.n;
+    const int cnt = min(a.ring_cnt[slot], a.n);
+    const int base = s * a.width, span = a.nacc * a.width;
+    const int ts = 1 << lg_team, tl = tid & (ts - 1);
+    const int team = tid >> lg_team, teams = nt >> lg_team;
+    if (tid == 0) s_ev = 0ull;
+    for (int x = tid; x < span; x += nt) acc[x] = 0;
+    __syncthreads();
+    for (int b0 = 0; b0 < cnt; b0 += kBdRows) {  // uniform
+        const int m = min(kBdRows, cnt - b0);
+        long long own = 0;
+        for (int j = tid; j < m; j += nt) {
+            const int k = min(max(list[b0 + j], 0), a.n - 1);
+            const int32_t *pv = a.piv + (int64_t)k * (a.n_slices + 1) + s;
+            const int p0 = pv[0], p1 = pv[1];
+            s_start[j] = a.row_ptr[k] + p0;
+            s_len[j] = (p1 - p0) | ((a.nacc == 2 && k >= a.n_exc) ? 1 << 30 : 0);
+            own += p1 - p0;
+        }
+        own = wave_sum_i64(own);
+        if (tid % kWave == 0 && own) atomicAdd(&s_ev, (unsigned long long)own);
+        __syncthreads();
+        // (with entries so far, edge 0 exists: the slots past a segment's end read it)
+        for (int j0 = s_ev ? team : m; j0 < m; j0 += RU * teams) {
+            int64_t g[RU];
+            int len[RU], half[RU], cv[RU][U];
+            float wv[RU][U];
+#pragma unroll
+            for (int r = 0; r < RU; ++r) {
+                const int j = j0 + r * teams, jc = j < m ? j : j0;
+                const int l = s_len[jc];
+                g[r] = s_start[jc];
+                len[r] = j < m ? l & ((1 << 30) - 1) : 0;
+                half[r] = l >> 30 ? a.width : 0;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int p = u * ts + tl;
+                    const int64_t e = p < len[r] ? g[r] + p : 0;
+                    cv[r][u] = CT ? (int)a.col16[e] : a.col[e] - base;
+                    wv[r][u] = a.w[e];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < RU; ++r) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (u * ts + tl < len[r])
+                        atomicAdd((unsigned long long *)(acc + cv[r][u] + half[r]),
+                                  (unsigned long long)to_fix(wv[r][u]));
+                for (int p = U * ts + tl; p < len[r]; p += ts) {
+                    const int c = CT ? (int)a.col16[g[r] + p] : a.col[g[r] + p] - base;
+                    atomicAdd((unsigned long long *)(acc + c + half[r]),
+                              (unsigned long long)to_fix(a.w[g[r] + p]));
+                }
+            }
+        }
+        __syncthreads();  // every atomic done, the segments read
+    }
+    if (tid == 0) add_stat(a.stats + 2 * (int64_t)blockIdx.x, (long long)s_ev);
+    long long *out = a.abatch + (int64_t)b * a.part_stride;
+    for (int x = tid; x < a.width; x += nt) {
+        const int j = base + x;
+        if (j < a.n) {
+            out[j] = acc[x];
+            if (a.nacc == 2) out[a.n + j] = acc[a.width + x];
+        }
+    }
+}
+
+// Fused synapse pass of one step: the forced rows plasticity and slice
 // delivery (with the transmitting rows' plasticity) in one launch. A forced
 // row does not transmit at t, so the two parts touch disjoint rows, and
 // neither reads what the other writes (targets' histories, post traces and
@@ -1620,6 +1701,43 @@ hipError_t launch_deliver_lds(hipStream_t s, const DeliverArgs &a, int blocks, s
     else
         launch_kernel(k_deliver_lds<false>, dim3(blocks), dim3(kDlvBlock), lds, s, ev, a);
     return hipGetLastError();
+}
+
+template <bool CT>
+static hipError_t launch_deliver_block_ct(hipStream_t s, const DeliverArgs &a, double seg, int nt,
+                                          int blocks, int lds)
+{
+    static std::mutex mu;
+    static int granted[3] = {48 * 1024, 48 * 1024, 48 * 1024};
+    // Lanes per segment and segments in flight for `seg` entries on average:
+    // eight entries per lane in flight, of as many segments as fill them.
+    const double want = seg * 1.2;
+    const int form = want <= 2 * kWave ? 0 : want <= 4 * kWave ? 1 : 2;
+    int lg = 2;
+    while (lg < 6 && (2 << lg) < want) ++lg;
+    const void *kern = form == 0   ? (const void *)k_deliver_block<CT, 4, 2>
+                       : form == 1 ? (const void *)k_deliver_block<CT, 2, 4>
+                                   : (const void *)k_deliver_block<CT, 1, 8>;
+    const hipError_t e = allow_dynamic_lds(kern, lds, mu, granted[form]);
+    if (e != hipSuccess) return e;
+    if (form == 0)
+        hipLaunchKernelGGL((k_deliver_block<CT, 4, 2>), dim3(blocks), dim3(nt), lds, s, a, lg);
+    else if (form == 1)
+        hipLaunchKernelGGL((k_deliver_block<CT, 2, 4>), dim3(blocks), dim3(nt), lds, s, a, lg);
+    else
+        hipLaunchKernelGGL((k_deliver_block<CT, 1, 8>), dim3(blocks), dim3(nt), lds, s, a, lg);
+    return hipGetLastError();
+}
+
+hipError_t launch_deliver_block(hipStream_t s, const DeliverArgs &a, int64_t n_edges)
+{
+    const int blocks = (a.n_work + 7) / 8 * 8;
+    const int lds = kBdRows * 12 + a.nacc * a.width * (int)sizeof(long long);
+    const double seg = (double)n_edges / a.n * a.width / a.n;
+    // few items (wide slices): twice the waves each
+    const int nt = a.n_work <= 512 ? kBdBlockMax : kDlvBlock;
+    return a.col16 ? launch_deliver_block_ct<true>(s, a, seg, nt, blocks, lds)
+                   : launch_deliver_block_ct<false>(s, a, seg, nt, blocks, lds);
 }
 
 hipError_t launch_probe_rows(hipStream_t s, int blocks, const int64_t *row_ptr,

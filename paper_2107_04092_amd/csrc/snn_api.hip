@@ -123,7 +123,7 @@ struct snn_ctx {
     bool fuse = false;  // plastic: parts (2) and (3) of snn_step in one launch
     int32_t fuse_slots = 0;  // workgroups of the fused pass resident at once
     int32_t fuse_chunks = 1;  // workgroups per slice in the fused pass (<= chunks)
-    long long *abatch = nullptr;  // [batch_max][C][nacc][n]
+    long long *abatch = nullptr;  // [batch_max][nacc][n]
     // plastic blocks (BlockArgs): most steps per block (0: off), targets per
     // group and groups; the group pivots (graph buffer), the plan's lists
     // and counts and the block clock (workspace)
@@ -1546,12 +1546,9 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
     for (int32_t q = 0; blocks && q < n_steps;) {
         const int32_t B = std::min<int32_t>(n_steps - q, c->batch_max);
         DeliverArgs d = deliver_args(c);
-        d.batch = B;
         d.abatch = c->abatch;
-        d.chunks = 1;
         d.n_work = B * c->n_slices;
-        const int grid = (d.n_work + 7) / 8 * 8;
-        if ((st = check_hip(c, launch_deliver_lds(c->stream, d, grid, dlv_lds_bytes(c)),
+        if ((st = check_hip(c, launch_deliver_block(c->stream, d, c->n_edges),
                             "delay-block delivery")))
             return st;
         NeuronArgs a = neuron_args(c);

@@ -223,7 +223,7 @@ struct DeliverArgs {
     float *w;
     const int32_t *piv;      // [n][S+1]
     // the transmitted spikes of step t = clk->t - 1: delay-ring slot
-    // (t - D + 1) mod D (a delay block: slots of its steps, below)
+    // (t - D + 1) mod D (a delay block: slots of its steps)
     const int32_t *ring, *ring_cnt;
     const int32_t *tx_cnt;   // the transmitted spikes' count of the step (see CompactArgs)
     StepClock *clk;
@@ -233,13 +233,10 @@ struct DeliverArgs {
     int32_t n, n_exc, width, n_slices, chunks, nacc, n_work, hw;
     const uint16_t *col16;   // compressed targets: slice-local indices (nullptr: read `col`)
     int64_t *stats;          // [gridDim.x][2]: events delivered, weights written
-    // delay block (no plasticity): batch > 0 delivers, before the block's
-    // neuron launch, the spikes emitted at steps t0 + 1 - D .. t0 + batch - D
-    // (t0 = clk->t, the block's first step), work item (b, slice, chunk)
-    // writing fixed-point partial c of step b to abatch (the host passes one
-    // chunk, so each item writes the whole sum); n_work counts all batch items
-    int32_t batch, delay;
-    long long *abatch;       // [batch][chunks][nacc][n]
+    int32_t delay;
+    // delay block (k_deliver_block): the inputs of its steps; n_work counts
+    // the items (step, slice)
+    long long *abatch;       // [steps][nacc][n]
     // plasticity of the transmitting rows, fused into slice delivery
     int32_t plastic;         // 0: no plastic rows
     int32_t event;           // as in StdpArgs
@@ -362,7 +359,7 @@ constexpr int kOneMaxW = 4096;   // targets per workgroup
 hipError_t launch_step_one(hipStream_t s, const NeuronArgs &a, const StepOneArgs &b);
 
 // Delay-blocked steps of a network without plasticity and delay D >= 2
-// (k_neuron_steps after a batched k_deliver_lds). The input of step t comes
+// (k_neuron_steps after k_deliver_block). The input of step t comes
 // from the spikes of step t-D only, so the inputs of steps t0+1 .. t0+B
 // (B <= D-1) depend on spikes already in the delay ring when step t0
 // starts: one delivery launch computes all B of them, then one neuron
@@ -680,6 +677,9 @@ constexpr int fused_queue_bytes(int hw)
 constexpr int kRecentMaxWords = kCodeMax / 8;  // words of the spike-recency bitmap
 constexpr uint8_t kCodeMulti = 255;    // history code: two or more spikes in the window
 int stdp_static_bytes();  // static LDS of the slice STDP kernel (-1 on error)
+// k_deliver_block: workgroups of kDlvBlock threads, kBdBlockMax for few items
+constexpr int kBdBlockMax = 1024;
+hipError_t launch_deliver_block(hipStream_t s, const DeliverArgs &a, int64_t n_edges);
 hipError_t launch_deliver_lds(hipStream_t s, const DeliverArgs &a, int blocks, size_t lds, KernelEvents ev = {});
 // k_synapse_pass: slice delivery on workgroups [0, nd) (nd a multiple of 8),
 // forced-row STDP on ns more, kDlvBlock threads each; lds covers both
