@@ -25,6 +25,7 @@ static __device__ __align__(256) unsigned long long scratch[kScratchWords];
 
 namespace {
 constexpr int kMaxDevices = 64;
+constexpr int kFuseChunks = 8;  // most workgroups per slice that the fused pass takes by itself
 std::mutex g_scratch_mu;
 unsigned long long *g_scratch[kMaxDevices] = {};  // device address of `scratch`, per device
 
@@ -122,7 +123,7 @@ struct snn_ctx {
     uint64_t *one_mask = nullptr;
     bool fuse = false;  // plastic: parts (2) and (3) of snn_step in one launch
     int32_t fuse_slots = 0;  // workgroups of the fused pass resident at once
-    int32_t fuse_chunks = 1;  // workgroups per slice in the fused pass (<= chunks)
+    int32_t fuse_chunks = 1;  // workgroups per slice in the fused pass
     long long *abatch = nullptr;  // [batch_max][nacc][n]
     // plastic blocks (BlockArgs): most steps per block (0: off), targets per
     // group and groups; the group pivots (graph buffer), the plan's lists
@@ -1167,12 +1168,21 @@ snn_status snn_create(const snn_config *cfg, void *hip_stream, snn_ctx **out)
         // half of the slots (the sums of the parts do not depend on their
         // number): 100,000 neurons in 98 slices run their step in 25.1 us
         // with two per slice in the pass (25.4 with three, 25.1 with one),
-        // against 32.4 with the configured four in separate launches.
+        // against 32.4 with the configured four in separate launches. Few
+        // wide slices get more than configured (up to kFuseChunks), until
+        // they fill about a fifth of the CUs: a step of 12,345 plastic
+        // neurons in 13 slices takes 20.2, 17.5, 16.5 and 16.7 us with one,
+        // two, four and eight per slice, in 7 slices 26.6, 20.7, 17.8 and
+        // 16.9; 60,000 in 30 slices 27.7, 22.0 and 23.5 with one, two and
+        // four, in 59 slices 21.7 with one and 23.5 with two.
         c->fuse_chunks = c->chunks;
         auto items = [&](int64_t ch) { return (c->n_slices * ch + 7) / 8 * 8; };
         if (c->fuse_slots - items(c->fuse_chunks) < c->n_cu / 2)
             while (c->fuse_chunks > 1 && items(c->fuse_chunks) > c->fuse_slots / 2)
                 c->fuse_chunks -= 1;
+        while (c->fuse_chunks < kFuseChunks && (int64_t)c->n_slices * c->fuse_chunks < c->n_cu / 5 &&
+               c->fuse_slots - items(c->fuse_chunks + 1) >= c->n_cu / 2)
+            c->fuse_chunks += 1;
         c->fuse = per_cu >= 1 && c->fuse_slots - items(c->fuse_chunks) >= c->n_cu / 2;
         // the forced-row workgroups of the pass keep a statistics slot each
         if (c->fuse && c->syn_slots < c->fuse_slots) c->syn_slots = c->fuse_slots;
@@ -1183,7 +1193,7 @@ snn_status snn_create(const snn_config *cfg, void *hip_stream, snn_ctx **out)
     // The run's delivery workgroups (a slice and a chunk of the rows each)
     // take half of the resident ones, the forced rows the rest.
     c->sb_max = 0;
-    c->parts = c->chunks;
+    c->parts = c->fuse ? std::max(c->chunks, c->fuse_chunks) : c->chunks;
     if (c->n_plastic_rows > 0 && c->algo != 2 && c->delay == 1 &&
         cfg->neuron_model == SNN_BERNOULLI_SOURCE && c->fuse && !c->xcd &&
         cfg->plastic_blocks >= 0 && cfg->slice_width <= kSrcMaxW && c->nw <= kRecentMaxWords) {
@@ -1199,7 +1209,7 @@ snn_status snn_create(const snn_config *cfg, void *hip_stream, snn_ctx **out)
             c->sb_max = cfg->plastic_blocks > 0
                             ? std::min<int32_t>(cfg->plastic_blocks, kSrcMaxSteps)
                             : kSrcMaxSteps;
-            c->parts = std::max(c->chunks, c->sb_chunks);
+            c->parts = std::max(c->parts, c->sb_chunks);
             c->syn_slots = std::max(c->syn_slots, c->sb_slots);
         }
     }
@@ -1610,7 +1620,7 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
     }
     // (timed as configured: a pass with fewer workgroups per slice than asked
     // for runs as its parts while kernel times are being recorded)
-    const bool whole = c->fuse_chunks == c->chunks || c->t_used >= c->t_cap;
+    const bool whole = c->fuse_chunks >= c->chunks || c->t_used >= c->t_cap;
     // a plastic network of Bernoulli sources with D = 1 runs in source
     // blocks (see SourceArgs): one launch for the neuron updates and lists
     // of up to sb_max steps, then one for the synapse part of all of them. The

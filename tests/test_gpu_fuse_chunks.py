@@ -1,5 +1,5 @@
 """The fused synapse pass with fewer workgroups per slice than configured
-(more slices than its slots hold): the same states, inputs and weights as the
+(more slices than its slots hold) or more (few slices): the same states, inputs and weights as the
 separate part calls with the configured number, bit for bit."""
 
 import pytest
@@ -28,6 +28,30 @@ def test_fewer_workgroups_per_slice(name, case):
         kw["n_exc"] = n * 4 // 5
     p = wl.preset(name, **kw)
     a = gpu_net(p, slice_width=64, spike_chunks=chunks)
+    b = gpu_net(p, slice_width=64, spike_chunks=chunks, plastic_blocks=-1)
+    for k in (1, 40, 69):
+        a.step(k, LDS)
+        for _ in range(k):
+            b.update_neurons()
+            b.update_plasticity()
+            b.deliver_spikes(LDS)
+            b.advance()
+        same_state(a, b, "%d steps" % k)
+
+
+@pytest.mark.parametrize("case", [
+    # slices, configured workgroups per slice
+    (1, 1), (7, 1), (13, 3), (50, 1), (51, 1),
+], ids=lambda c: "%d-slices-%d" % c)
+@pytest.mark.parametrize("name", ["brunel_plus", "stress"])
+def test_more_workgroups_per_slice(name, case):
+    slices, chunks = case
+    n = 64 * slices - 13
+    log("fused pass: %s, %d slices, %d workgroups each" % (name, slices, chunks))
+    kw = dict(n=n, delay=1, p_or_fanout=0.1, n_exc=n * 4 // 5) if name == "brunel_plus" else dict(
+        n=n, p_or_fanout=20, p_fire=0.02, delay=1)
+    p = wl.preset(name, **kw)
+    a = gpu_net(p, slice_width=64, spike_chunks=chunks, plastic_blocks=-1)
     b = gpu_net(p, slice_width=64, spike_chunks=chunks, plastic_blocks=-1)
     for k in (1, 40, 69):
         a.step(k, LDS)
