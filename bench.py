@@ -420,19 +420,18 @@ def main():
         t_neu, t_stdp, t_dlv = kt["neuron"], kt["plasticity"], kt["delivery"]
         # a plastic network of Bernoulli sources with D = 1 runs in source
         # blocks: one launch for the neuron updates and one for the synapse
-        # part of up to block_steps steps; the times are per launch
+        # part of up to block_steps steps (the times are per step)
         block = (net.graph()["block_steps"] or 1) if (
             p.model == snn.SNN_BERNOULLI_SOURCE and p.delay == 1 and p.plastic != 0
             and args.mode == "lds") else 1
         nsteps = args.steps / -(-args.steps // block)  # steps per launch, on average
-        t_dlv_launch, t_dlv = t_dlv, t_dlv / nsteps
         kernels = {
             "steps_timed": nrec,
-            "neuron_us": round(t_neu * 1e3, 3),
+            "neuron_us": round(t_neu * 1e3 * nsteps, 3),
             "neuron_steps_per_launch": round(nsteps, 3),
-            "neuron_us_per_step": round(t_neu * 1e3 / nsteps, 3),
+            "neuron_us_per_step": round(t_neu * 1e3, 3),
             "plasticity_us": round(t_stdp * 1e3, 3),
-            "delivery_us": round(t_dlv_launch * 1e3, 3),
+            "delivery_us": round(t_dlv * 1e3 * nsteps, 3),
             "delivery_us_per_step": round(t_dlv * 1e3, 3),
             "fused_synapse_pass": bool(p.plastic != 0 and t_stdp == 0 and t_dlv > 0),
             "plasticity_bytes_per_launch": int(b_stdp),

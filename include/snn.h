@@ -428,14 +428,17 @@ snn_status snn_step_static(snn_ctx *ctx, int32_t n_steps, int32_t mode);
  * parts: [0] neuron update with its spike / row lists, [1] plasticity,
  * [2] delivery (for the global-atomic mode from the start of the
  * transmitting rows' plasticity to the end of delivery; where snn_step runs
- * parts (2) and (3) in one launch, that launch, with [1] not recorded). Each launch places its own events around the kernel
- * (no extra stream work). 0 stops recording and frees the events. Calls the
- * stream's synchronisation first. */
+ * parts (2) and (3) in one launch, that launch, with [1] not recorded). A
+ * launch that covers several steps (the two of a block of Bernoulli sources)
+ * is recorded once for all of them; no such launch reaches past the recorded
+ * steps. Each launch places its own events around the kernel (no extra
+ * stream work). 0 stops recording and frees the events. Calls the stream's
+ * synchronisation first. */
 snn_status snn_record_kernel_times(snn_ctx *ctx, int32_t max_steps);
 
 /* Mean device time per recorded step of each part in milliseconds
- * (mean_ms: 3 doubles, host; 0 for a part that launched nothing) and the
- * number of steps recorded.
+ * (mean_ms: 3 doubles, host; a launch of several steps counts for as many;
+ * 0 for a part that launched nothing) and the number of steps recorded.
  * Synchronises the stream. */
 snn_status snn_get_kernel_times(snn_ctx *ctx, double *mean_ms, int32_t *steps);
 

@@ -68,8 +68,8 @@ struct snn_ctx {
     int32_t max_row = 0;  // longest row of the built graph
     float *sx_pre = nullptr, *sx_post = nullptr;  // per-synapse traces (naive)
     // kernel timing: events [step][part][start, stop] for the first t_cap
-    // steps run by snn_step after snn_record_kernel_times; t_rec marks parts
-    // that launched a kernel
+    // steps run by snn_step after snn_record_kernel_times; t_rec: the steps
+    // that the launch recorded there covers (0: the part launched nothing)
     std::vector<hipEvent_t> tev;
     std::vector<uint8_t> t_rec;
     int32_t t_cap = 0, t_used = 0;
@@ -614,15 +614,16 @@ snn_status sync_clock(snn_ctx *c, int64_t *dev_t)
 }
 
 // Events of part `part` (0 neurons and lists, 1 plasticity, 2 delivery)
-// of the current step when timing is on; marks the part as timed.
-KernelEvents part_events(snn_ctx *c, int part)
+// of the current step when timing is on; marks the part as timed, by a launch
+// that covers `steps` steps from this one on.
+KernelEvents part_events(snn_ctx *c, int part, int32_t steps = 1)
 {
     KernelEvents ev;
     if (c->t_used < c->t_cap) {
         const size_t q = (size_t)c->t_used * kTimedParts + part;
         ev.start = c->tev[2 * q];
         ev.stop = c->tev[2 * q + 1];
-        c->t_rec[q] = 1;
+        c->t_rec[q] = (uint8_t)steps;  // (at most kSrcMaxSteps)
     }
     return ev;
 }
@@ -1627,7 +1628,7 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
     // scans' status words are cleared before and after, so that no word a
     // different launch shape left can match a step tag. With kernel timing
     // on, the block's launches are timed as the neuron and delivery parts of
-    // its first step.
+    // its steps.
     const bool sblocks = mode == SNN_DELIVER_LDS_SLICE && c->sb_max > 0 && whole &&
                          c->n_edges > 0 && c->n_edges <= 0xFFFFFFFFll;
     if (sblocks && n_steps > 0) {
@@ -1675,7 +1676,9 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
         d.d_minus = c->d_minus;
         for (int q = 0; q <= kMaxAge; ++q) d.dpow[q] = c->dpow[q];
         for (int32_t q = 0; q < n_steps;) {
-            const int32_t B = std::min<int32_t>(n_steps - q, c->sb_max);
+            int32_t B = std::min<int32_t>(n_steps - q, c->sb_max);
+            // (a recording ends with a block: its events cover no other steps)
+            if (c->t_used < c->t_cap) B = std::min(B, c->t_cap - c->t_used);
             SourceArgs b{};
             b.status = c->status;
             b.status_stride = c->status_stride;
@@ -1693,17 +1696,17 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
             b.split = c->sb_split;
             b.t_last = c->t_last;
             b.xpre = c->xpre;
-            if ((st = check_hip(c, launch_source_steps(c->stream, a, l, b, part_events(c, 0)),
+            if ((st = check_hip(c, launch_source_steps(c->stream, a, l, b, part_events(c, 0, B)),
                                 "source block")))
                 return st;
             d.steps = r.steps = B;
             d.hist0 = B > 1 ? c->sb_hist0 : c->hist;
             d.y0 = B > 1 ? c->sb_y0 : c->ypost;
             if ((st = check_hip(c, launch_source_run(c->stream, d, r, c->hw, c->sb_nd, ns,
-                                                     c->sb_lds, part_events(c, 2)),
+                                                     c->sb_lds, part_events(c, 2, B)),
                                 "source block run")))
                 return st;
-            c->t_used = std::min(c->t_used + B, c->t_cap);
+            if (c->t_used < c->t_cap) c->t_used += B;
             c->t += B;
             q += B;
         }
@@ -1808,7 +1811,7 @@ snn_status snn_get_kernel_times(snn_ctx *c, double *mean_ms, int32_t *steps)
     if (st) return st;
     for (int part = 0; part < kTimedParts; ++part) {
         double sum = 0;
-        int cnt = 0;
+        int cnt = 0;  // steps that the recorded launches cover
         for (int q = 0; q < c->t_used; ++q) {
             const size_t k = (size_t)q * kTimedParts + part;
             if (!c->t_rec[k]) continue;
@@ -1817,7 +1820,7 @@ snn_status snn_get_kernel_times(snn_ctx *c, double *mean_ms, int32_t *steps)
                            "kernel timing");
             if (st) return st;
             sum += ms;
-            ++cnt;
+            cnt += c->t_rec[k];
         }
         mean_ms[part] = cnt ? sum / cnt : 0.0;
     }
