@@ -26,6 +26,7 @@ static __device__ __align__(256) unsigned long long scratch[kScratchWords];
 namespace {
 constexpr int kMaxDevices = 64;
 constexpr int kFuseChunks = 8;  // most workgroups per slice that the fused pass takes by itself
+constexpr int kFuseFewer = 16;  // most configured that it replaces by fewer
 std::mutex g_scratch_mu;
 unsigned long long *g_scratch[kMaxDevices] = {};  // device address of `scratch`, per device
 
@@ -1169,8 +1170,13 @@ snn_status snn_create(const snn_config *cfg, void *hip_stream, snn_ctx **out)
         // half of the slots (the sums of the parts do not depend on their
         // number): 100,000 neurons in 98 slices run their step in 25.1 us
         // with two per slice in the pass (25.4 with three, 25.1 with one),
-        // against 32.4 with the configured four in separate launches. Few
-        // wide slices get more than configured (up to kFuseChunks), until
+        // against 32.4 with the configured four in separate launches. More
+        // than kFuseFewer per slice stay what the caller asked for, in
+        // separate launches: that is the slower choice in quiet networks
+        // (30,000 neurons in 30 slices, 17 each: 26.4 us against 16.4; 16,384
+        // in 32, 17 each: 29.1 against 16.5) but keeps the partial sums and
+        // the three timed parts of a configuration tuned for bursts (30% of
+        // the 30,000 firing in a step: 35.9 against 41.3). Few wide slices get more than configured (up to kFuseChunks), until
         // they fill about a fifth of the CUs: a step of 12,345 plastic
         // neurons in 13 slices takes 20.2, 17.5, 16.5 and 16.7 us with one,
         // two, four and eight per slice, in 7 slices 26.6, 20.7, 17.8 and
@@ -1178,7 +1184,7 @@ snn_status snn_create(const snn_config *cfg, void *hip_stream, snn_ctx **out)
         // four, in 59 slices 21.7 with one and 23.5 with two.
         c->fuse_chunks = c->chunks;
         auto items = [&](int64_t ch) { return (c->n_slices * ch + 7) / 8 * 8; };
-        if (c->fuse_slots - items(c->fuse_chunks) < c->n_cu / 2)
+        if (c->chunks <= kFuseFewer && c->fuse_slots - items(c->fuse_chunks) < c->n_cu / 2)
             while (c->fuse_chunks > 1 && items(c->fuse_chunks) > c->fuse_slots / 2)
                 c->fuse_chunks -= 1;
         while (c->fuse_chunks < kFuseChunks && (int64_t)c->n_slices * c->fuse_chunks < c->n_cu / 5 &&
@@ -1619,9 +1625,6 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
         c->last_neuron_t = c->last_deliver_t = c->t - 1;
         return SNN_OK;
     }
-    // (timed as configured: a pass with fewer workgroups per slice than asked
-    // for runs as its parts while kernel times are being recorded)
-    const bool whole = c->fuse_chunks >= c->chunks || c->t_used >= c->t_cap;
     // a plastic network of Bernoulli sources with D = 1 runs in source
     // blocks (see SourceArgs): one launch for the neuron updates and lists
     // of up to sb_max steps, then one for the synapse part of all of them. The
@@ -1629,7 +1632,7 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
     // different launch shape left can match a step tag. With kernel timing
     // on, the block's launches are timed as the neuron and delivery parts of
     // its steps.
-    const bool sblocks = mode == SNN_DELIVER_LDS_SLICE && c->sb_max > 0 && whole &&
+    const bool sblocks = mode == SNN_DELIVER_LDS_SLICE && c->sb_max > 0 &&
                          c->n_edges > 0 && c->n_edges <= 0xFFFFFFFFll;
     if (sblocks && n_steps > 0) {
         if ((st = check_hip(c, clear_status(c), "clear the list scans"))) return st;
@@ -1738,7 +1741,7 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
     }
     // parts (2) and (3) of plastic networks in one launch where it fits
     // (kernel timing records it as the delivery part)
-    const bool fuse = mode == SNN_DELIVER_LDS_SLICE && c->fuse && whole;
+    const bool fuse = mode == SNN_DELIVER_LDS_SLICE && c->fuse;
     for (int32_t q = 0; q < n_steps; ++q) {
         if ((st = launch_step_neurons(c))) return st;
         if (fuse) {

@@ -1,6 +1,8 @@
-"""Recorded kernel times of source blocks: a launch of up to 16 steps counts for
-as many, so the means are per step whatever the block lengths, and a recording
-that ends inside a call ends with a block."""
+"""Recorded kernel times: of the launches that an unrecorded call makes (fused
+passes with fewer workgroups per slice than configured among them); and of
+source blocks: a launch of up to 16 steps counts for as many, so the means are
+per step whatever the block lengths, and a recording that ends inside a call
+ends with a block."""
 
 import pytest
 
@@ -46,3 +48,23 @@ def test_recording_that_ends_inside_a_call():
     t, recorded = a.kernel_times()
     assert recorded == 21 and t["neuron"] > 0 and t["delivery"] > 0
     same_state(a, b, "recorded and not")
+
+
+@pytest.mark.parametrize("name,chunks,fused", [("brunel_plus", 4, True), ("brunel_plus", 16, True),
+                                               ("brunel_plus", 17, False), ("stress", 16, True),
+                                               ("stress", 17, False)])
+def test_the_recorded_launches_are_those_of_unrecorded_calls(name, chunks, fused):
+    """110 slices of the configured workgroups do not fit the pass's slots: up
+    to 16 per slice it takes fewer, beyond that the parts run by themselves,
+    recorded or not."""
+    n = 64 * 110 - 13
+    kw = dict(n=n, delay=1, p_or_fanout=0.01, n_exc=n * 4 // 5) if name == "brunel_plus" else dict(
+        n=n, p_or_fanout=60, p_fire=0.02, delay=1)
+    p = wl.preset(name, **kw)
+    a = gpu_net(p, slice_width=64, spike_chunks=chunks)
+    assert (a.graph()["block_steps"] > 0) == (fused and name == "stress")
+    a.record_kernel_times(20)
+    a.step(20, LDS)
+    t, recorded = a.kernel_times()
+    assert recorded == 20 and t["neuron"] > 0 and t["delivery"] > 0
+    assert (t["plasticity"] == 0) == fused
