@@ -88,7 +88,8 @@ def parse():
     ap.add_argument("--write-traffic", nargs=2, metavar=("FETCH_DB", "WRITE_DB"),
                     help="no run: write profiles/traffic.json for --config from two "
                          "rocprofv3 --pmc result databases of a run with --copy-probe-mib "
-                         "(FETCH_SIZE, then WRITE_SIZE)")
+                         "(FETCH_SIZE, then WRITE_SIZE); --steps, --warmup, --history-bits, "
+                         "--plastic-blocks and --no-instrumented as in that run")
     ap.add_argument("--copy-probe-mib", type=int, default=0,
                     help="after the timed region, run one device-to-device copy of this many "
                          "MiB: the reference kernel that scales rocprofv3 FETCH_SIZE/WRITE_SIZE "
@@ -126,13 +127,24 @@ def kernel_source_digest():
     return h.hexdigest()[:16]
 
 
-def write_traffic(fetch_db, write_db, workload_key, copy_mib):
+def launch_steps(calls, block):
+    """Steps of each launch of a source block's kernels, for step calls of the
+    given lengths: whole blocks, then the rest of the call."""
+    out = []
+    for k in calls:
+        out += [block] * (k // block) + ([k % block] if k % block else [])
+    return out
+
+
+def write_traffic(fetch_db, write_db, workload_key, copy_mib, steps=None):
     """HBM bytes per launch of each kernel from two rocprofv3 counter runs
     (FETCH_SIZE, then WRITE_SIZE, in KiB per dispatch), each scaled by what
     the same counter reads for the reference copy of copy_mib MiB each way
     (__amd_rocclr_copyBuffer); averaged over the dispatches after the first
-    quarter. Written to profiles/traffic.json under workload_key with the
-    current source digest."""
+    quarter. steps: the steps of each launch of the profiled run where a
+    launch runs several (launch_steps); their mean over the same dispatches
+    is kept beside the bytes. Written to profiles/traffic.json under
+    workload_key with the current source digest."""
     import sqlite3
     import collections
     vals = collections.defaultdict(lambda: collections.defaultdict(list))
@@ -163,15 +175,22 @@ def write_traffic(fetch_db, write_db, workload_key, copy_mib):
                   "fetch_scale": round(fs, 4), "write_scale": round(ws, 4),
                   "bytes_per_launch": round((fk * fs + wk * ws) * 1024),
                   "dispatches": len(f), "source_digest": kernel_source_digest()}
+        if k not in ("k_source_steps", "k_source_run"):
+            out[k]["steps_per_launch"] = 1.0
+        elif steps and len(steps) == len(vals[k]["FETCH_SIZE"]) == len(vals[k]["WRITE_SIZE"]):
+            kept = steps[len(steps) // 4:]
+            out[k]["steps_per_launch"] = sum(kept) / len(kept)
     d[workload_key] = out
     with open(path, "w") as fh:
         json.dump(d, fh, indent=1)
     print(json.dumps({workload_key: out}, indent=1))
 
 
-def load_traffic(kernel, workload_key):
+def load_traffic(kernel, workload_key, steps_per_launch=None):
     """HBM bytes per launch from committed rocprofv3 counter summaries, if they
-    were taken on the current kernel source."""
+    were taken on the current kernel source; for launches of steps_per_launch
+    steps on average, if given (None where the profiled launches' steps are
+    not known)."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None
@@ -180,7 +199,8 @@ def load_traffic(kernel, workload_key):
         ent = d[workload_key][kernel]
         if ent.get("source_digest") != kernel_source_digest():
             return None
-        return float(ent["bytes_per_launch"])
+        scale = 1.0 if steps_per_launch is None else steps_per_launch / ent["steps_per_launch"]
+        return float(ent["bytes_per_launch"]) * scale
     except (KeyError, ValueError, TypeError):
         return None
 
@@ -306,6 +326,15 @@ def cpu_baseline(p, seconds, seconds_1t):
             "cpu_model": model, "host_logical_cpus": ncpu}
 
 
+SOURCE_BLOCK = 16  # most steps per source block (snn_config.plastic_blocks = 0)
+
+
+def untimed_steps(warmup, hbits):
+    """Steps before the timed region: the requested warm-up, and at least two
+    history lengths."""
+    return max(warmup, 2 * hbits)
+
+
 def check_device_errors(net, where):
     """Ends the benchmark if a kernel flagged an error condition (a row
     behind its history window, a ring inconsistency): its numbers would be
@@ -322,8 +351,13 @@ def main():
     if args.write_traffic:
         if args.copy_probe_mib <= 0:
             sys.exit("bench.py: --write-traffic needs the --copy-probe-mib of the profiled run")
+        import workloads as wl
+        hbits = args.history_bits or wl.preset(args.config).history_bits
+        calls = [untimed_steps(args.warmup, hbits), args.steps]
+        block = min(block_arg(args.plastic_blocks) or SOURCE_BLOCK, SOURCE_BLOCK)
         write_traffic(args.write_traffic[0], args.write_traffic[1], args.config,
-                      args.copy_probe_mib)
+                      args.copy_probe_mib,
+                      launch_steps(calls + ([] if args.no_instrumented else calls[1:]), block))
         return
     world = int(os.environ.get("WORLD_SIZE", "1"))
     if args.gpus != 1 or world != 1:
@@ -369,7 +403,7 @@ def main():
     # untimed steps: the requested warm-up, and at least two history lengths,
     # so that every window is full and the forced rows are past their
     # staggered start (steady state)
-    untimed = max(args.warmup, 2 * hbits)
+    untimed = untimed_steps(args.warmup, hbits)
     net.step(untimed, mode)
     torch.cuda.synchronize()
     check_device_errors(net, "untimed steps")
@@ -466,10 +500,10 @@ def main():
             impl = b_stdp
         if fused or t_stdp > 0:
             ach = alg / (t_k * 1e-3) / 1e9
-            traffic = load_traffic(kname, p.name)
+            traffic = load_traffic(kname, p.name, nsteps)
             roofline = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
                         "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
-                        "traffic": traffic, "kernel": kname,
+                        "traffic": traffic and round(traffic), "kernel": kname,
                         "kernel_us": round(t_k * 1e3 * nsteps, 3),
                         "steps_per_launch": round(nsteps, 3),
                         "bytes_per_launch": int(alg * nsteps),

@@ -153,3 +153,46 @@ def test_plastic_block_choices_map_to_the_config_field(monkeypatch):
     for bad in ("0", "65", "x"):
         with pytest.raises(ValueError):
             b.block_arg(bad)
+
+
+def test_launch_steps():
+    b = bench_module()
+    assert b.launch_steps([32, 20, 5], 16) == [16, 16, 16, 4, 5]
+    assert b.launch_steps([3], 1) == [1, 1, 1]
+    assert b.untimed_steps(5, 128) == 256 and b.untimed_steps(300, 128) == 300
+
+
+def test_traffic_scales_to_the_steps_of_a_launch(tmp_path, monkeypatch):
+    """Counters of launches of 16 and 4 steps, looked up for a run whose
+    launches have 10 on average: the bytes are scaled by the steps. A run whose
+    launches do not match the dispatches leaves them unknown, and then there is
+    no figure; a kernel of one step per launch needs none."""
+    import sqlite3
+    b = bench_module()
+    monkeypatch.setattr(b, "ROOT", str(tmp_path))
+    monkeypatch.setattr(b, "kernel_source_digest", lambda: "abc")
+    os.makedirs(tmp_path / "profiles")
+    steps = b.launch_steps([32, 32, 20], 16)  # 16 16 16 16 16 4
+    dbs = []
+    for counter, per_step in (("FETCH_SIZE", 30.0), ("WRITE_SIZE", 10.0)):
+        path = str(tmp_path / (counter + ".db"))
+        con = sqlite3.connect(path)
+        con.execute("create table counters_collection (kernel_name text, counter_name text, "
+                    "value real)")
+        rows = [("__amd_rocclr_copyBuffer", counter, 1024.0)]
+        rows += [("void snn::(anonymous namespace)::k_source_run<true, 2>(a, b, int)", counter,
+                  per_step * k) for k in steps]
+        rows += [("void snn::(anonymous namespace)::k_synapse_pass<true, 2>(a, b, int)", counter,
+                  per_step)] * 4
+        con.executemany("insert into counters_collection values (?, ?, ?)", rows)
+        con.commit()
+        con.close()
+        dbs.append(path)
+    b.write_traffic(dbs[0], dbs[1], "stress", 1, steps)
+    e = json.load(open(tmp_path / "profiles" / "traffic.json"))["stress"]["k_source_run"]
+    assert e["steps_per_launch"] == pytest.approx((4 * 16 + 4) / 5)
+    assert b.load_traffic("k_source_run", "stress", 10.0) == pytest.approx(40 * 1024 * 10, rel=1e-6)
+    assert b.load_traffic("k_synapse_pass", "stress", 1.0) == pytest.approx(40 * 1024, rel=1e-6)
+    b.write_traffic(dbs[0], dbs[1], "stress", 1, steps[:-1])
+    assert b.load_traffic("k_source_run", "stress", 10.0) is None
+    assert b.load_traffic("k_source_run", "stress") is not None
