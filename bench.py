@@ -116,12 +116,12 @@ _COMMENT = re.compile(r"//[^\n]*|/\*.*?\*/", re.S)
 
 
 def kernel_source_digest():
-    """Digest of the library's code with comments and layout removed, so that
+    """Digest of the library's code (every source and header) with comments and layout removed, so that
     counters taken on a source stay valid across comment-only edits."""
     h = hashlib.sha256()
-    for f in ("k_neuron.hip", "k_synapse.hip", "k_graph.hip", "snn_device.h", "snn_api.hip",
-              "snn_internal.h"):
-        with open(os.path.join(ROOT, "paper_2107_04092_amd", "csrc", f)) as fh:
+    csrc = os.path.join(ROOT, "paper_2107_04092_amd", "csrc")
+    for f in sorted(f for f in os.listdir(csrc) if f.endswith((".hip", ".h"))):
+        with open(os.path.join(csrc, f)) as fh:
             code = _COMMENT.sub(" ", fh.read())
         h.update(" ".join(code.split()).encode())
     return h.hexdigest()[:16]

@@ -196,3 +196,20 @@ def test_traffic_scales_to_the_steps_of_a_launch(tmp_path, monkeypatch):
     b.write_traffic(dbs[0], dbs[1], "stress", 1, steps[:-1])
     assert b.load_traffic("k_source_run", "stress", 10.0) is None
     assert b.load_traffic("k_source_run", "stress") is not None
+
+
+def test_digest_covers_every_source(tmp_path, monkeypatch):
+    import shutil
+    from paper_2107_04092_amd import build
+    b = bench_module()
+    csrc = tmp_path / "paper_2107_04092_amd" / "csrc"
+    shutil.copytree(build.CSRC, csrc)
+    monkeypatch.setattr(b, "ROOT", str(tmp_path))
+    seen = {b.kernel_source_digest()}
+    files = {os.path.basename(f) for f in build.SOURCES}
+    files |= {f for f in os.listdir(csrc) if f.endswith(".h")}
+    for f in sorted(files):
+        with open(csrc / f, "a") as fh:
+            fh.write("\nstatic int changed_%d;\n" % len(seen))
+        seen.add(b.kernel_source_digest())
+    assert len(seen) == len(files) + 1
