@@ -441,7 +441,9 @@ class Network:
             nbytes = count * dtype.itemsize
             if off < 0 or off + nbytes > buf.numel():
                 raise RuntimeError("view outside its buffer")
-            made = self._views[key] = (buf, buf[off:off + nbytes].view(dtype))
+            # (a view made in inference mode would stay an inference tensor)
+            with self._torch.inference_mode(False):
+                made = self._views[key] = (buf, buf[off:off + nbytes].view(dtype))
         return made[1].detach()  # a tensor object of the caller's own
 
     def state(self):
