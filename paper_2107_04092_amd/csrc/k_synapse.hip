@@ -1294,16 +1294,21 @@ __global__ __launch_bounds__(kDlvBlock, 4) void k_synapse_pass(DeliverArgs d, St
 // Stress network (250M synapses), neuron part and gaps included: 32.4 -> 24.5
 // us per step; 60,001 sources of 333 targets: 15.5 -> 7.8.
 
-template <bool CT, int HW>
+// WIDE: slices of more than kSrcMaxW targets, or 2^32 edges and more (a row's
+// first edge takes the bits 10-31 of its record's flags too): a form of its
+// own, since more spike words and 64-bit edges cost the others registers.
+template <bool CT, int HW, bool WIDE>
 __device__ __forceinline__ void source_deliver(const SourceRunArgs &a, int bid, int nb,
                                                unsigned char *dyn)
 {
-    constexpr int NT = kDlvBlock, NWV = NT / kWave, R = kSrcMaxW / NT, NR = 2;
+    constexpr int NT = kDlvBlock, NWV = NT / kWave, NR = 2;
+    constexpr int R = (WIDE ? kSrcWideW : kSrcMaxW) / NT;
+    using Edge = typename std::conditional<WIDE, long long, unsigned>::type;
     static_assert(kSrcRecs <= NR * NT && kSrcRecs < 65535, "two rows per thread, 16-bit map");
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int W = a.width, B = a.steps, C = a.chunks, n = a.n;
     // per row: first edge less its flattened index, flattened end of the
-    // plastic entries, age and kSrcPre / kSrcTx, pre trace
+    // plastic entries, age (bits 0-7), pre spike (8) and kSrcTx (9), pre trace
     int4 *s_rec = reinterpret_cast<int4 *>(dyn);
     long long *acc = reinterpret_cast<long long *>(s_rec + kSrcRecs);
     uint64_t *s_hist = reinterpret_cast<uint64_t *>(acc + W);
@@ -1361,6 +1366,11 @@ __device__ __forceinline__ void source_deliver(const SourceRunArgs &a, int bid, 
             p1[rr] = pv[1];
         }
     };
+    // the first edge less its flattened index
+    auto first_of = [](const int4 &rec) -> Edge {
+        if (WIDE) return (Edge)((long long)(rec.z >> 10) << 32 | (unsigned)rec.x);
+        return (Edge)(unsigned)rec.x;
+    };
     fetch(0, 0);
     fetch_pivots();
     long long ev = 0, rows_tx = 0;
@@ -1415,9 +1425,17 @@ __device__ __forceinline__ void source_deliver(const SourceRunArgs &a, int bid, 
         for (int rr = 0; rr < NR; ++rr) {
             const int j = NR * tid + rr;
             if (j < nbt) {
-                const unsigned e0 = (unsigned)ra[rr].x + (unsigned)p0[rr];  // (edges below 2^32)
-                s_rec[j] = make_int4((int)(e0 - (unsigned)o[rr]), o[rr] + plen[rr],
-                                     (rb[rr].x & 0x1ff) | ((rb[rr].w & kSrcTx) << 1), rb[rr].y);
+                const unsigned e0 = (unsigned)ra[rr].x + (unsigned)p0[rr];
+                int base32 = (int)(e0 - (unsigned)o[rr]), high = 0;
+                if (WIDE) {
+                    const long long first =
+                        ((long long)ra[rr].y << 32 | (unsigned)ra[rr].x) + p0[rr] - o[rr];
+                    base32 = (int)first;
+                    high = (int)(first >> 32) * 1024;
+                }
+                s_rec[j] = make_int4(base32, o[rr] + plen[rr],
+                                     (rb[rr].x & 0x1ff) | ((rb[rr].w & kSrcTx) << 1) | high,
+                                     rb[rr].y);
             }
         }
         const int nb0 = b0 + kSrcRecs < s_sp[2 * q + 1] - s_sp[2 * q] ? b0 + kSrcRecs : 0;
@@ -1453,7 +1471,7 @@ __device__ __forceinline__ void source_deliver(const SourceRunArgs &a, int bid, 
                 const int x = u * NT + tid;
                 const bool in = x < we;
                 l[u] = in ? (int)s_map[x] - 1 : -1;
-                const unsigned e = in ? (unsigned)s_rec[max(l[u], 0)].x + (unsigned)(e0 + x) : 0u;
+                const Edge e = in ? first_of(s_rec[max(l[u], 0)]) + (Edge)(e0 + x) : (Edge)0;
                 cv[u] = CT ? (int)a.col16[e] : col[e];
                 wv[u] = wgt[e];
             }
@@ -1481,7 +1499,7 @@ __device__ __forceinline__ void source_deliver(const SourceRunArgs &a, int bid, 
                                                    c_dep, mu)
                                     : stdp_synapse_steps(w, h0, h1, age, pre, xp0, xpn, y, s_dp[1],
                                                          c_pot, c_dep, mu);
-                        wgt[(unsigned)rec.x + (unsigned)x] = w;
+                        wgt[first_of(rec) + (Edge)x] = w;
                         if (pre)
                             ++w_tx;
                         else
@@ -1526,13 +1544,13 @@ __device__ __forceinline__ void source_deliver(const SourceRunArgs &a, int bid, 
     }
 }
 
-template <bool CT, int HW>
+template <bool CT, int HW, bool WIDE>
 __global__ __launch_bounds__(kDlvBlock, 4) void k_source_run(SourceRunArgs d, StdpArgs s,
                                                              int32_t nd)
 {
     extern __shared__ uint4 dyn_run[];
     if ((int)blockIdx.x < nd)
-        source_deliver<CT, HW>(d, blockIdx.x, nd, reinterpret_cast<unsigned char *>(dyn_run));
+        source_deliver<CT, HW, WIDE>(d, blockIdx.x, nd, reinterpret_cast<unsigned char *>(dyn_run));
     else
         stdp_rows_body<kDlvBlock, HW == 1 ? kStdpRowsUnroll : kStdpRowsUnroll2, HW, true>(
             s, blockIdx.x - nd, gridDim.x - nd, (unsigned char *)dyn_run);
@@ -1777,25 +1795,33 @@ hipError_t launch_synapse_pass(hipStream_t s, const DeliverArgs &d, const StdpAr
 }
 
 namespace {
-template <bool CT, int HW>
-hipError_t launch_run(hipStream_t s, const SourceRunArgs &d, const StdpArgs &a, int nd, int ns,
+template <bool CT, int HW, bool WIDE>
+hipError_t launch_run_w(hipStream_t s, const SourceRunArgs &d, const StdpArgs &a, int nd, int ns,
                       size_t lds, KernelEvents ev)
 {
     static std::mutex mu;
     static int granted = 48 * 1024;
-    const hipError_t e = allow_dynamic_lds((const void *)k_source_run<CT, HW>, (int)lds, mu, granted);
+    const hipError_t e = allow_dynamic_lds((const void *)k_source_run<CT, HW, WIDE>, (int)lds, mu, granted);
     if (e != hipSuccess) return e;
-    launch_kernel(k_source_run<CT, HW>, dim3(nd + ns), dim3(kDlvBlock), lds, s, ev, d, a, nd);
+    launch_kernel(k_source_run<CT, HW, WIDE>, dim3(nd + ns), dim3(kDlvBlock), lds, s, ev, d, a, nd);
     return hipGetLastError();
+}
+template <bool CT, int HW>
+hipError_t launch_run(hipStream_t s, const SourceRunArgs &d, const StdpArgs &a, int nd, int ns,
+                      size_t lds, KernelEvents ev)
+{
+    return d.width > kSrcMaxW || d.n_edges > 0xFFFFFFFFll
+               ? launch_run_w<CT, HW, true>(s, d, a, nd, ns, lds, ev)
+               : launch_run_w<CT, HW, false>(s, d, a, nd, ns, lds, ev);
 }
 }  // namespace
 
 hipError_t launch_source_run(hipStream_t s, const SourceRunArgs &d, const StdpArgs &a, int hw,
                              int nd, int ns, size_t lds, KernelEvents ev)
 {
-    if (d.steps < 1 || d.steps > kSrcMaxSteps || d.width < kWave || d.width > kSrcMaxW ||
+    if (d.steps < 1 || d.steps > kSrcMaxSteps || d.width < kWave || d.width > kSrcWideW ||
         d.chunks < 1 || d.chunks > kSrcMaxChunks || d.n_work != d.n_slices * d.chunks ||
-        nd % 8 != 0 || nd < d.n_work || ns < 1 || d.n_edges < 1 || d.n_edges > 0xFFFFFFFFll ||
+        nd % 8 != 0 || nd < d.n_work || ns < 1 || d.n_edges < 0 || d.n_edges > kSrcMaxEdges ||
         d.stat_slots < 1 || d.syn_slots < nd + ns || (hw != 1 && hw != 2) || !a.hq || a.code ||
         !a.hcode || a.n_info < 1 || lds < source_run_lds(d.width, hw))
         return hipErrorInvalidValue;
@@ -1810,8 +1836,14 @@ hipError_t launch_source_run(hipStream_t s, const SourceRunArgs &d, const StdpAr
 int source_run_static_bytes()
 {
     int m = 0;
-    for (const void *f : {(const void *)k_source_run<true, 1>, (const void *)k_source_run<false, 1>,
-                          (const void *)k_source_run<true, 2>, (const void *)k_source_run<false, 2>}) {
+    for (const void *f : {(const void *)k_source_run<true, 1, false>,
+                          (const void *)k_source_run<false, 1, false>,
+                          (const void *)k_source_run<true, 2, false>,
+                          (const void *)k_source_run<false, 2, false>,
+                          (const void *)k_source_run<true, 1, true>,
+                          (const void *)k_source_run<false, 1, true>,
+                          (const void *)k_source_run<true, 2, true>,
+                          (const void *)k_source_run<false, 2, true>}) {
         const int b = static_lds_bytes(f);
         if (b < 0) return -1;
         m = m > b ? m : b;

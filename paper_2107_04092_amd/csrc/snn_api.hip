@@ -143,6 +143,7 @@ struct snn_ctx {
     // resident workgroups of k_source_run, its LDS
     int32_t sb_max = 0, sb_chunks = 1, sb_nd = 0, sb_slots = 0;
     size_t sb_lds = 0;
+    bool sb_map = false;  // its forced rows stage the recency bitmap
     int32_t parts = 1;  // partial inputs: the chunks of whichever delivery has more
     uint64_t *sb_hist0 = nullptr, *sb_hq = nullptr, *sb_code = nullptr, *sb_recent = nullptr;
     float *sb_y0 = nullptr;
@@ -1203,11 +1204,13 @@ snn_status snn_create(const snn_config *cfg, void *hip_stream, snn_ctx **out)
     c->parts = c->fuse ? std::max(c->chunks, c->fuse_chunks) : c->chunks;
     if (c->n_plastic_rows > 0 && c->algo != 2 && c->delay == 1 &&
         cfg->neuron_model == SNN_BERNOULLI_SOURCE && c->fuse && !c->xcd &&
-        cfg->plastic_blocks >= 0 && cfg->slice_width <= kSrcMaxW && c->nw <= kRecentMaxWords) {
+        cfg->plastic_blocks >= 0) {
         const int rstat = source_run_static_bytes();
         if (rstat < 0) return fail(c, SNN_EDEVICE, "cannot query the kernels");
+        c->sb_map = c->algo == 0 && cfg->stdp_filter != 3 && c->nw <= kRecentMaxWords;
         c->sb_lds = std::max(source_run_lds(cfg->slice_width, c->hw),
-                             (size_t)c->nw * sizeof(uint64_t) + (size_t)fused_queue_bytes(c->hw));
+                             (c->sb_map ? (size_t)c->nw * sizeof(uint64_t) : 0) +
+                                 (size_t)fused_queue_bytes(c->hw));
         const int per_cu = std::min<int>(2, (int)(lds_max / (int64_t)(c->sb_lds + rstat)));
         c->sb_slots = c->n_cu * per_cu;
         c->sb_chunks = std::max(1, std::min(c->sb_slots / 2 / c->n_slices, kSrcMaxChunks));
@@ -1632,8 +1635,7 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
     // different launch shape left can match a step tag. With kernel timing
     // on, the block's launches are timed as the neuron and delivery parts of
     // its steps.
-    const bool sblocks = mode == SNN_DELIVER_LDS_SLICE && c->sb_max > 0 &&
-                         c->n_edges > 0 && c->n_edges <= 0xFFFFFFFFll;
+    const bool sblocks = mode == SNN_DELIVER_LDS_SLICE && c->sb_max > 0;
     if (sblocks && n_steps > 0) {
         if ((st = check_hip(c, clear_status(c), "clear the list scans"))) return st;
         NeuronArgs a = neuron_args(c);
@@ -1648,7 +1650,7 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
         r.hq = c->sb_hq;
         r.hcode = c->sb_code;
         r.code = nullptr;
-        r.recent = c->algo == 0 && c->cfg.stdp_filter != 3 ? c->sb_recent : nullptr;
+        r.recent = c->sb_map ? c->sb_recent : nullptr;
         SourceRunArgs d{};
         d.n = c->n;
         d.n_slices = c->n_slices;
@@ -1660,6 +1662,11 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
         d.col = c->col;
         d.col16 = c->col16;
         d.w = c->w;
+        if (c->n_edges == 0) {  // (slots without an entry read edge 0)
+            d.col = c->piv;
+            d.w = (float *)c->piv;
+            if (c->ct) d.col16 = (const uint16_t *)c->piv;
+        }
         d.piv = c->piv;
         d.hq = c->sb_hq;
         d.txinfo = c->sb_txinfo;

@@ -535,7 +535,9 @@ constexpr int kSrcMaxSteps = kBatchMax;  // steps per source block (one scan per
 // (slice, chunk) on workgroups [0, nd), the listed forced rows on the others.
 constexpr int kSrcRecs = 704;   // rows staged at once
 constexpr int kSrcU = 11;       // entries per thread and window
-constexpr int kSrcMaxW = 4096;  // targets per slice
+constexpr int kSrcMaxW = 4096;  // targets per slice of the form for most networks
+constexpr int kSrcWideW = 7168;  // targets per slice whose LDS a workgroup can have
+constexpr int64_t kSrcMaxEdges = 1ll << 52;  // (first edge in 32 + 22 bits, signed)
 struct SourceRunArgs {
     int32_t n, n_slices, width, chunks, n_work, steps, event;
     int64_t n_edges;

@@ -50,3 +50,61 @@ def test_run_equals_step_by_step(case):
     a.flush_plasticity()
     b.flush_plasticity()
     same_state(a, b, "flush")
+
+
+WIDE = [
+    # beyond the ranges of the common form: slices of more than 4096 targets,
+    # more neurons than the recency bitmap holds, no bitmap asked for, no edges
+    (dict(n=20011, p_or_fanout=150, p_fire=0.008), 4160, 1, dict(history_bits=128)),
+    (dict(n=20011, p_or_fanout=150, p_fire=0.008), 6528, 2, dict(compressed_targets=0)),
+    (dict(n=50000, p_or_fanout=64, p_fire=0.01), 4608, 1, dict()),
+    (dict(n=784001, p_or_fanout=6, p_fire=0.005), 2048, 1, dict()),
+    (dict(n=420001, p_or_fanout=10, p_fire=0.005), 2048, 1, dict(stdp_filter=3)),
+    (dict(n=3001, p_or_fanout=0, p_fire=0.01), 512, 2, dict()),
+]
+
+
+@pytest.mark.parametrize("case", WIDE, ids=lambda c: "%d-w%d" % (c[0]["n"], c[1]))
+def test_wide_form_equals_step_by_step(case):
+    kw, width, chunks, cfg = case
+    p = wl.preset("stress", **kw)
+    log("source run, wide: %s width %d %s" % (kw, width, cfg))
+    a = gpu_net(p, slice_width=width, spike_chunks=chunks, **cfg)
+    b = gpu_net(p, slice_width=width, spike_chunks=chunks, **dict(cfg, plastic_blocks=-1))
+    assert a.graph()["block_steps"] > 0
+    for k in (1, 70, 17):
+        a.step(k, LDS)
+        for _ in range(k):
+            b.update_neurons()
+            b.update_plasticity()
+            b.deliver_spikes(LDS)
+            b.advance()
+        same_state(a, b, "%d steps" % k)
+    # the launches are those of blocks: two for 16 steps are recorded as one
+    # neuron part, far below 16 neuron updates of the step-by-step path
+    for net in (a, b):
+        net.record_kernel_times(64)
+        net.step(64, LDS)
+    (ta, _), (tb, _) = a.kernel_times(), b.kernel_times()
+    log("neuron part per step: %.2f us in blocks, %.2f us step by step" % (
+        ta["neuron"] * 1e3, tb["neuron"] * 1e3))
+    assert ta["neuron"] < tb["neuron"]
+
+
+def test_more_edges_than_32_bits_count():
+    """4.32 billion synapses (35 GB): the first edges of the last rows take more
+    than 32 bits."""
+    import torch
+    p = wl.preset("stress", n=360001, p_or_fanout=12000, p_fire=0.0005)
+    log("source run: %d rows of 12,000" % p.n)
+    nets = [gpu_net(p, slice_width=2048, spike_chunks=1, plastic_blocks=b) for b in (0, -1)]
+    assert nets[0].n_edges > 1 << 32 and nets[0].graph()["block_steps"] > 0
+    for k in (17, 50):
+        for net in nets:
+            net.step(k, LDS)
+        same_state(*nets, "%d steps" % k, weights=False)
+        wa, wb = (net.graph()["w"].view(torch.int32) for net in nets)
+        step = 1 << 28
+        for at in range(0, wa.numel(), step):
+            assert torch.equal(wa[at:at + step], wb[at:at + step]), at
+        log("  %d steps: weights equal" % k)
