@@ -108,3 +108,31 @@ def test_more_edges_than_32_bits_count():
         for at in range(0, wa.numel(), step):
             assert torch.equal(wa[at:at + step], wb[at:at + step]), at
         log("  %d steps: weights equal" % k)
+
+
+def test_a_call_of_one_step_is_a_step():
+    """Single-step calls between longer ones: the same states, in the launches
+    of the step-by-step path (a block of one step takes twice the time)."""
+    import torch
+    p = wl.preset("stress", n=20011, p_or_fanout=100)
+    a = gpu_net(p, slice_width=1024, spike_chunks=2)
+    b = gpu_net(p, slice_width=1024, spike_chunks=2, plastic_blocks=-1)
+    assert a.graph()["block_steps"] == 16
+    for k in (1, 5, 1, 1, 33, 1, 64, 1):
+        a.step(k, LDS)
+        b.step(k, LDS)
+        same_state(a, b, "%d steps" % k)
+
+    def us(net):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        torch.cuda.synchronize()
+        ev[0].record(net.stream)
+        for _ in range(100):
+            net.step(1, LDS)
+        ev[1].record(net.stream)
+        torch.cuda.synchronize()
+        return ev[0].elapsed_time(ev[1]) * 10
+
+    ta, tb = (min(us(net) for _ in range(5)) for net in (a, b))
+    log("one step per call: %.1f us, step by step %.1f us" % (ta, tb))
+    assert ta < 1.25 * tb  # (a block of one step: 1.56 times)
