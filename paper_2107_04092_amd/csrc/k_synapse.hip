@@ -1164,6 +1164,13 @@ __global__ __launch_bounds__(kDlvBlock, 4) void k_deliver_lds(DeliverArgs a)
 // deliver_lds_body, in 64 registers, so that a CU holds 32 waves instead of
 // 16. 14 steps of 62,500 neurons (868 items, 100 segments of 102 entries
 // each): 42 -> 20 us, 57 MB at 2.8 TB/s.
+// Rows of very different lengths (or targets near their source) leave most
+// teams idle beside a long segment, so a segment beyond four times what a team
+// has in flight is left to all waves of the workgroup, in pieces (20,011 neurons,
+// D = 6, 5% firing, one row in a hundred of 14,000 targets, the others of 200:
+// 10.8 -> 5.0 us per step, against 4.5 with as many edges in even rows; rows
+// of 200 with a lognormal spread of 2: 10.4 -> 6.2, 2.9 -> 2.6 in quiet
+// states). Even rows pay about 1% for it.
 constexpr int kBdRows = 1024;  // segments looked up at once
 
 template <bool CT, int RU, int U>
@@ -1171,9 +1178,12 @@ __global__ __launch_bounds__(kBdBlockMax, 8) void k_deliver_block(DeliverArgs a,
 {
     extern __shared__ uint4 dyn_bd[];
     int64_t *s_start = reinterpret_cast<int64_t *>(dyn_bd);   // kBdRows
-    int *s_len = reinterpret_cast<int *>(s_start + kBdRows);  // kBdRows: entries, bit 30: inhibitory
+    int *s_len = reinterpret_cast<int *>(s_start + kBdRows);  // kBdRows: entries, bit 30:
+                                                              // inhibitory, bit 31: long
     long long *acc = reinterpret_cast<long long *>(s_len + kBdRows);  // nacc * W
+    uint16_t *s_long = reinterpret_cast<uint16_t *>(acc + a.nacc * a.width);  // kBdRows
     __shared__ unsigned long long s_ev;
+    __shared__ int s_nlong[2];  // (of the rows looked up, and of the next ones)
     const int tid = threadIdx.x, nt = blockDim.x, nb = gridDim.x;
     const int q = (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);
     if (q >= a.n_work) return;  // whole workgroup, before any barrier
@@ -1185,10 +1195,14 @@ __global__ __launch_bounds__(kBdBlockMax, 8) void k_deliver_block(DeliverArgs a,
     const int base = s * a.width, span = a.nacc * a.width;
     const int ts = 1 << lg_team, tl = tid & (ts - 1);
     const int team = tid >> lg_team, teams = nt >> lg_team;
-    if (tid == 0) s_ev = 0ull;
+    const int most = 4 * U * ts;  // entries of a segment that one team adds
+    if (tid == 0) {
+        s_ev = 0ull;
+        s_nlong[0] = 0;
+    }
     for (int x = tid; x < span; x += nt) acc[x] = 0;
     __syncthreads();
-    for (int b0 = 0; b0 < cnt; b0 += kBdRows) {  // uniform
+    for (int b0 = 0, at = 0; b0 < cnt; b0 += kBdRows, at ^= 1) {  // uniform
         const int m = min(kBdRows, cnt - b0);
         long long own = 0;
         for (int j = tid; j < m; j += nt) {
@@ -1196,12 +1210,18 @@ __global__ __launch_bounds__(kBdBlockMax, 8) void k_deliver_block(DeliverArgs a,
             const int32_t *pv = a.piv + (int64_t)k * (a.n_slices + 1) + s;
             const int p0 = pv[0], p1 = pv[1];
             s_start[j] = a.row_ptr[k] + p0;
-            s_len[j] = (p1 - p0) | ((a.nacc == 2 && k >= a.n_exc) ? 1 << 30 : 0);
+            int l = (p1 - p0) | ((a.nacc == 2 && k >= a.n_exc) ? 1 << 30 : 0);
             own += p1 - p0;
+            if (p1 - p0 > most) {
+                s_long[atomicAdd(&s_nlong[at], 1)] = (uint16_t)j;
+                l |= 1 << 31;
+            }
+            s_len[j] = l;
         }
         own = wave_sum_i64(own);
         if (tid % kWave == 0 && own) atomicAdd(&s_ev, (unsigned long long)own);
         __syncthreads();
+        if (tid == 0) s_nlong[at ^ 1] = 0;
         // (with entries so far, edge 0 exists: the slots past a segment's end read it)
         for (int j0 = s_ev ? team : m; j0 < m; j0 += RU * teams) {
             int64_t g[RU];
@@ -1212,8 +1232,8 @@ __global__ __launch_bounds__(kBdBlockMax, 8) void k_deliver_block(DeliverArgs a,
                 const int j = j0 + r * teams, jc = j < m ? j : j0;
                 const int l = s_len[jc];
                 g[r] = s_start[jc];
-                len[r] = j < m ? l & ((1 << 30) - 1) : 0;
-                half[r] = l >> 30 ? a.width : 0;
+                len[r] = j < m && l >= 0 ? l & ((1 << 30) - 1) : 0;
+                half[r] = (l & 1 << 30) ? a.width : 0;
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int p = u * ts + tl;
@@ -1235,6 +1255,13 @@ __global__ __launch_bounds__(kBdBlockMax, 8) void k_deliver_block(DeliverArgs a,
                               (unsigned long long)to_fix(a.w[g[r] + p]));
                 }
             }
+        }
+        const int nl = s_nlong[at], wave = tid / kWave, waves = nt / kWave;  // (a power of two)
+        for (int x = 0; x < nl; ++x) {  // uniform
+            const int j = s_long[x], l = s_len[j];
+            add_segment_pieces<CT>(acc + ((l & 1 << 30) ? a.width : 0), a.col, a.col16, a.w, base,
+                                   s_start[j], l & ((1 << 30) - 1), (wave - x) & (waves - 1),
+                                   waves);
         }
         __syncthreads();  // every atomic done, the segments read
     }
@@ -1750,7 +1777,7 @@ static hipError_t launch_deliver_block_ct(hipStream_t s, const DeliverArgs &a, d
 hipError_t launch_deliver_block(hipStream_t s, const DeliverArgs &a, int64_t n_edges)
 {
     const int blocks = (a.n_work + 7) / 8 * 8;
-    const int lds = kBdRows * 12 + a.nacc * a.width * (int)sizeof(long long);
+    const int lds = kBdRows * 14 + a.nacc * a.width * (int)sizeof(long long);
     const double seg = (double)n_edges / a.n * a.width / a.n;
     // few items (wide slices): twice the waves each
     const int nt = a.n_work <= 512 ? kBdBlockMax : kDlvBlock;

@@ -427,6 +427,34 @@ __device__ __forceinline__ float stdp_synapse_code(float w, uint64_t code, int q
     return w;
 }
 
+// Adds the entries [g, g + len) of a row segment onto `acc`, by the waves of a
+// workgroup together: this wave takes the pieces of kPiece entries from number
+// `first` on, every `waves`-th. Slice-local targets (CT) or targets less
+// `base`.
+constexpr int kPiece = 4 * kWave;
+template <bool CT>
+__device__ __forceinline__ void add_segment_pieces(long long *acc, const int32_t *col,
+                                                   const uint16_t *col16, const float *w,
+                                                   int base, int64_t g, int len, int first,
+                                                   int waves)
+{
+    const int lane = threadIdx.x % kWave;
+    for (int p0 = first * kPiece; p0 < len; p0 += waves * kPiece) {  // wave-uniform
+        int c[4];
+        float x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t e = g + min(p0 + u * kWave + lane, len - 1);
+            c[u] = CT ? (int)col16[e] : col[e] - base;
+            x[u] = w[e];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (p0 + u * kWave + lane < len)
+                atomicAdd((unsigned long long *)(acc + c[u]), (unsigned long long)to_fix(x[u]));
+    }
+}
+
 // Delay-ring slot of a step (steps before 0 wrap like the ring).
 __device__ __forceinline__ int ring_slot(int64_t step, int d)
 {
