@@ -182,6 +182,10 @@ __global__ __launch_bounds__(kBlock) void k_edges_scatter(GraphArgs a, const int
 // word, weight in another, in the arrays of the graph itself); then one
 // workgroup per bucket sorts it in LDS. 8M edges of 30,011 rows: counting 391
 // -> 18 us, placing 721 -> 197 us (bound by its scattered words), sorting 750 -> 108 us.
+// A list with a bucket beyond the sort's LDS (rows of very different lengths) is
+// built the general way, so placing it would be wasted: 66M edges in lognormal
+// rows, one of them of 16,000: 21.1 -> 18.2 ms, as before there were buckets, and
+// 15.6 with the shifts of k_row_sort (670,000 edges: 909 -> 824 us).
 constexpr int kGroupBlock = 1024;
 constexpr int kGroupU = 8;  // edges a thread loads at once
 
@@ -223,8 +227,10 @@ __global__ __launch_bounds__(kGroupBlock) void k_bucket_count(GraphArgs a, Bucke
 __global__ __launch_bounds__(kGroupBlock) void k_bucket_place(GraphArgs a, BucketArgs b)
 {
     // per bucket: the stretch's count, then the next free place less the
-    // bucket's start (a bucket holds fewer than 2^31 edges)
+    // bucket's start
     extern __shared__ int s_n[];  // nb
+    // a bucket beyond what the sort holds: the rows are built the general way
+    if (*a.maxlen > kBucketCap) return;  // uniform
     for (int x = threadIdx.x; x < b.nb; x += kGroupBlock) s_n[x] = 0;
     __syncthreads();
     const int64_t e0 = blockIdx.x * b.stretch, e1 = min(e0 + b.stretch, b.e);
@@ -299,7 +305,9 @@ __device__ __forceinline__ float ord2f(uint32_t o)
     return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
 }
 
-// Sorts each row by (target, weight) with a bitonic network in LDS.
+// Sorts each row by (target, weight) with a bitonic network in LDS. Strides are
+// powers of two: comparators are found by masks, not by integer division (10M
+// edges, one row in a hundred of 14,000: the build 4010 -> 3370 us).
 constexpr int kSortBlock = 1024;
 __global__ __launch_bounds__(kSortBlock) void k_row_sort(GraphArgs a)
 {
@@ -322,7 +330,7 @@ __global__ __launch_bounds__(kSortBlock) void k_row_sort(GraphArgs a)
     for (int size = 2; size <= p2; size <<= 1) {
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
             for (int x = tid; x < (p2 >> 1); x += kSortBlock) {
-                const int lo = 2 * stride * (x / stride) + (x % stride);
+                const int lo = x + (x & -stride);  // 2 stride (x / stride) + x % stride
                 const int hi = lo + stride;
                 const bool up = (lo & size) == 0;
                 const unsigned long long u = keys[lo], v = keys[hi];
@@ -439,9 +447,9 @@ __global__ __launch_bounds__(kSortBlock) void k_bucket_sort(GraphArgs a, BucketA
                 for (int stride = size >> 1; stride > 0; stride >>= 1) {
                     const bool mirror = stride == size >> 1;
                     for (int x = tid; x < (p2 >> 1); x += kSortBlock) {
-                        const int blk = x / stride, in = x - blk * stride;
-                        const int i = 2 * stride * blk + in;
-                        const int j = mirror ? 2 * stride * (blk + 1) - 1 - in : i + stride;
+                        const int in = x & (stride - 1), at2 = 2 * (x - in);
+                        const int i = at2 + in;
+                        const int j = mirror ? at2 + 2 * stride - 1 - in : i + stride;
                         if (j < len) {
                             const unsigned long long u = s_e[lo + i], v = s_e[lo + j];
                             if (u > v) {
@@ -567,8 +575,8 @@ hipError_t launch_edges_scatter(hipStream_t s, const GraphArgs &a, const int32_t
 
 bool choose_buckets(BucketArgs &b, int32_t n, int64_t e, int64_t max_row)
 {
-    // rows per bucket: about kBucketAim edges, but no fewer than 512 buckets
-    // where there are rows for them, and as many as LDS can count
+    // rows per bucket: about kBucketAim edges, but no fewer than 512
+    // buckets where there are rows for them, and as many as LDS can count
     int shift = 0;
     while (shift < kBucketShift && ((int64_t)n >> (shift + 1)) >= 512 &&
            e * (2ll << shift) / n <= kBucketAim)

@@ -61,7 +61,7 @@ def edges(kind, n, e, rs):
     ("signs", 3000, 400000), ("plain", 140001, 300000), ("plain", 70000, 70000),
     ("hub targets", 2000, 100000), ("hub targets", 20011, 500000), ("few sources", 300, 60000),
     ("few sources", 5000, 70000), ("one bucket full", 600, 80000), ("plain", 8, 90000),
-    ("plain", 12, 150000),
+    ("plain", 12, 150000), ("one bucket full", 5000, 16000), ("few sources", 40000, 60000),
 ], ids=lambda c: "%s-%d-%d" % c)
 def test_edge_lists(case):
     kind, n, e = case
