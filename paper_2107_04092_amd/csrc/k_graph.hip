@@ -575,10 +575,10 @@ hipError_t launch_edges_scatter(hipStream_t s, const GraphArgs &a, const int32_t
 
 bool choose_buckets(BucketArgs &b, int32_t n, int64_t e, int64_t max_row)
 {
-    // rows per bucket: about kBucketAim edges, but no fewer than 512
+    // rows per bucket: about kBucketAim edges, but no fewer than kBucketFew
     // buckets where there are rows for them, and as many as LDS can count
     int shift = 0;
-    while (shift < kBucketShift && ((int64_t)n >> (shift + 1)) >= 512 &&
+    while (shift < kBucketShift && ((int64_t)n >> (shift + 1)) >= kBucketFew &&
            e * (2ll << shift) / n <= kBucketAim)
         ++shift;
     while (shift < kBucketShift && (((int64_t)n - 1) >> shift) + 1 > kBucketMax) ++shift;

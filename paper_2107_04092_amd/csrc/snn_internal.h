@@ -295,6 +295,10 @@ struct BucketArgs {
 };
 constexpr int kBucketShift = 8;     // most rows per bucket: 2^8 (row in the top byte of a word)
 constexpr int kBucketAim = 5120;    // edges per bucket aimed at
+// fewest buckets aimed at: one workgroup of the sort fits a CU and costs about
+// 6 us however few its edges (its ranges' counters), so small graphs take one
+// round of up to 256 (2,000 rows of 20 edges: 172.8 us with 512, 155.5 with 128)
+constexpr int kBucketFew = 128;
 constexpr int kBucketCap = 12288;   // most edges a bucket can have (LDS: 8 B each)
 constexpr int kBucketSubs = 8192;   // target ranges per bucket (LDS: 4 B each)
 constexpr int kBucketMax = 32768;   // most buckets (LDS: 4 B each)

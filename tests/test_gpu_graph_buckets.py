@@ -62,6 +62,7 @@ def edges(kind, n, e, rs):
     ("hub targets", 2000, 100000), ("hub targets", 20011, 500000), ("few sources", 300, 60000),
     ("few sources", 5000, 70000), ("one bucket full", 600, 80000), ("plain", 8, 90000),
     ("plain", 12, 150000), ("one bucket full", 5000, 16000), ("few sources", 40000, 60000),
+    ("signs", 255, 30000), ("signs", 256, 30000), ("plain", 513, 700),
 ], ids=lambda c: "%s-%d-%d" % c)
 def test_edge_lists(case):
     kind, n, e = case
