@@ -120,8 +120,9 @@ struct snn_ctx {
     // delay blocks (no plasticity, D >= 2): steps per block, partial inputs
     int32_t batch_max = 0;
     // one launch per step (StepOneArgs): targets per workgroup (0: off), masks
-    int32_t one_gw = 0;
+    int32_t one_gw = 0, one_parts = 1;
     uint64_t *one_mask = nullptr;
+    int32_t *one_arrived = nullptr;
     bool fuse = false;  // plastic: parts (2) and (3) of snn_step in one launch
     int32_t fuse_slots = 0;  // workgroups of the fused pass resident at once
     int32_t fuse_chunks = 1;  // workgroups per slice in the fused pass
@@ -472,6 +473,7 @@ void plan_workspace(snn_ctx *c, uint8_t *base)
     c->phq = p.take<uint64_t>(c->pb_max > 0 ? 2 * n * c->hw : 1);
     c->bclk = p.take<BlockClock>(1);
     c->one_mask = p.take<uint64_t>(c->one_gw > 0 ? 2 * (int64_t)c->nw : 1);
+    c->one_arrived = p.take<int32_t>(c->one_gw > 0 ? (c->n + c->one_gw - 1) / c->one_gw : 1);
     {
         const bool on = c->sb_max > 0;
         const int64_t v = c->sb_max > 1 ? c->sb_max - 1 : 0;  // steps before a block's last
@@ -1202,6 +1204,16 @@ snn_status snn_create(const snn_config *cfg, void *hip_stream, snn_ctx **out)
     // take half of the resident ones, the forced rows the rest.
     c->sb_max = 0;
     c->parts = c->fuse ? std::max(c->chunks, c->fuse_chunks) : c->chunks;
+    // The one-launch step: the configured workgroups per slice, up to one per
+    // CU (those without a part cost a quiet step 0.1 to 0.3 us; 12 per group
+    // of 20,011 neurons cost 0.9 where the configured four do not show).
+    if (c->one_gw > 0) {
+        const int groups = (c->n + c->one_gw - 1) / c->one_gw;
+        const int64_t want = (int64_t)c->chunks * (c->one_gw / cfg->slice_width);
+        c->one_parts = (int32_t)std::max<int64_t>(
+            1, std::min<int64_t>(want, std::min(c->n_cu / groups, kOneMaxParts)));
+        c->parts = std::max(c->parts, c->one_parts);
+    }
     if (c->n_plastic_rows > 0 && c->algo != 2 && c->delay == 1 &&
         cfg->neuron_model == SNN_BERNOULLI_SOURCE && c->fuse && !c->xcd &&
         cfg->plastic_blocks >= 0) {
@@ -1252,6 +1264,8 @@ snn_status snn_bind_workspace(snn_ctx *c, void *device_ptr, size_t bytes)
     if (e == hipSuccess)
         e = launch_fill_ll(c->stream, c->apart, (int64_t)c->parts * c->nacc * c->n, 0);
     if (e == hipSuccess) e = launch_fill_f32(c->stream, c->ain, (int64_t)c->nacc * c->n, 0.f);
+    if (e == hipSuccess && c->one_gw > 0)
+        e = launch_fill_i32(c->stream, c->one_arrived, (c->n + c->one_gw - 1) / c->one_gw, 0);
     if (e == hipSuccess) e = launch_fill_i32(c->stream, c->ring_cnt, c->delay, 0);
     if (e == hipSuccess) e = launch_fill_i32(c->stream, c->row_cnt, 1, 0);
     if (e == hipSuccess) e = launch_fill_i32(c->stream, c->tx_cnt, 1, 0);
@@ -1599,10 +1613,13 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
         b.gw = c->one_gw;
         b.mult = c->one_gw / c->cfg.slice_width;
         b.n_slices = c->n_slices;
-        // lanes per row: its entries per workgroup on average, 4 to 64
+        // lanes per row, 4 to 64: two entries each on average
         const double seg = (double)c->n_edges / c->n * c->one_gw / c->n;
         b.lg_team = 2;
-        while (b.lg_team < 6 && (1 << b.lg_team) < seg) ++b.lg_team;
+        while (b.lg_team < 6 && (2 << b.lg_team) < seg) ++b.lg_team;
+        b.parts = c->one_parts;
+        b.per_part = std::max(1, (int)(kOnePart / (seg + kOneRow)));
+        b.arrived = c->one_arrived;
         b.row_ptr = c->row_ptr;
         b.col = c->col;
         b.w = c->w;

@@ -352,7 +352,10 @@ struct StepOneArgs {
     const float *w;
     const int32_t *piv;       // [n][n_slices + 1]
     int32_t *ring, *ring_cnt, *tx_cnt;
-    long long *apart;         // part 0: the pending input after the last step
+    int32_t parts;            // workgroups per group of targets at most ...
+    int32_t per_part;         // ... one for every per_part spikes of the step
+    int32_t *arrived;         // [groups]: parts of the launch that have ended (0 before it)
+    long long *apart;         // the parts' sums; part 0: the pending input after the last step
     int64_t *gstats, *dlv_stats;
     int32_t dlv_slots;
     unsigned long long *status;
@@ -360,6 +363,14 @@ struct StepOneArgs {
 };
 constexpr int kOneMaxN = 65536;  // a mask word per thread
 constexpr int kOneMaxW = 4096;   // targets per workgroup
+constexpr int kOneMaxParts = 16;
+// Work of a part: entries, and kOneRow more per row. An exchange of sums costs
+// about 2.5 us and a workgroup adds 1.7 entries per ns: 5,003 neurons (250 spikes
+// of 100 entries at most) take 10.4, 8.9, 8.3 and 7.6 us per step with 2,048, 4,096,
+// 6,144 and 12,288; groups of 4,096 targets (62,500 neurons, 16 groups) do not
+// tell them apart: 20.9 (27 whole, 20.0 separately).
+constexpr int kOnePart = 12288;
+constexpr int kOneRow = 6;
 hipError_t launch_step_one(hipStream_t s, const NeuronArgs &a, const StepOneArgs &b);
 
 // Delay-blocked steps of a network without plasticity and delay D >= 2

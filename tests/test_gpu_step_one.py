@@ -56,6 +56,33 @@ def test_one_launch_per_step_equals_the_parts(case):
     same_state(a, b, "mixed", weights=False)
 
 
+BUSY = [
+    # the same, with bursts: steps of no spikes, of a few and of a third of the
+    # neurons, so that groups run whole and in two to all of their parts
+    ("vogels", dict(n=4097, n_exc=3277, p_or_fanout=0.1), 1024, 4, dict()),
+    ("vogels", dict(n=20011, n_exc=16000, p_or_fanout=0.02), 64, 1, dict(history_bits=128)),
+    ("vogels", dict(n=9001, n_exc=7200, p_or_fanout=0.1), 4096, 16, dict(history_bits=128)),
+    ("brunel", dict(n=12345, n_exc=9876, delay=1), 4096, 3, dict()),
+    ("brunel", dict(n=16385, n_exc=13000, delay=1, p_or_fanout=0.03), 2048, 9,
+     dict(compressed_targets=0)),
+    ("tiny", dict(n=65536, n_exc=52000, p_or_fanout=0.002), 512, 2, dict()),
+]
+
+
+@pytest.mark.parametrize("case", BUSY, ids=lambda c: "%s-%d-w%d" % (c[0], c[1]["n"], c[2]))
+def test_busy_steps_in_parts(case):
+    name, kw, width, chunks, cfg = case
+    p = wl.preset(name, v_inf=400.0, tau_ref=0.3, w_exc=1e-3, w_inh=-1e-3, **kw)
+    log("busy steps in parts: %s %s width %d" % (name, kw, width))
+    a = gpu_net(p, slice_width=width, spike_chunks=chunks, **cfg)
+    b = gpu_net(p, slice_width=width, spike_chunks=chunks, **cfg)
+    for k in (1, 2, 30, 7):
+        a.step(k, LDS)
+        parts(b, k)
+        same_state(a, b, "%d steps" % k, weights=False)
+    assert a.stats()["spikes"] > 40 * p.n // 20
+
+
 def test_captured():
     import torch
     p = wl.preset("vogels", n=6001, n_exc=4800, p_or_fanout=0.013)
