@@ -231,7 +231,11 @@ __global__ __launch_bounds__(kPbPlanBlock) void k_block_plan(BlockArgs b)
 // (a scan, a map and five barriers per step before).
 // Blocks with more records than LDS holds, or entries than the map, run in
 // stretches of whole steps that fit; a step that does not fit by itself takes
-// its records in portions, loaded and computed in turn.
+// its records in portions, as many as have their entries in the map. A step of
+// more entries than are loaded ahead loads each window while the one before is
+// computed: busy states are bound by that stream (that network with 10% of its
+// neurons firing per step on average, in bursts: 105 us per step with 8,192
+// entries in flight and no look-ahead, 139 with 2,048, 89.5 now).
 //
 // At the end the state goes back, the accumulator becomes partial sum 0 (the
 // input of step t0 + B), each target's history words at block start and its
@@ -284,6 +288,7 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
     __shared__ long long sh[NWV];
     __shared__ int shi[NWV];
     __shared__ int s_cnt[kBatchMax], s_base[kBatchMax + 1];
+    __shared__ int s_fit[2];  // records, and their entries, that the map holds in full
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     // neighbouring groups (which read neighbouring entries of each row) on
     // one XCD: workgroup b runs on XCD b mod 8
@@ -427,6 +432,10 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
             if (pq < 16)
                 for (int z = max(pq + 1, q0); z <= min(q, q1); ++z) s_yoff[z] = y;
             if (len[u] > 0 && y < kPbMap) s_map[y] = (uint16_t)(x + 1);  // marks its first entry
+            if (y <= kPbMap && kPbMap < y + len[u]) {  // the first record not in it in full
+                s_fit[0] = x;
+                s_fit[1] = y;
+            }
             y += len[u];
         }
         __syncthreads();  // the marks, r_info (the record before the thread's first)
@@ -581,11 +590,14 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
         }
         __builtin_amdgcn_wave_barrier();  // the queue is rewritten next
     };
-    // entries [y0, y1), loaded and computed a window at a time
-    auto windows = [&](int y0, int y1, PbEntries &E) {
-        for (int y = y0; y < y1; y += kPbAhead) {  // uniform
-            issue(y, y1, E);
+    // entries [y0, y1) but for the last window, which E holds afterwards, as it
+    // holds the first one before: each window loaded while the one before is
+    // computed
+    auto windows = [&](int y0, int y1, PbEntries &E, PbEntries &F) {
+        for (int y = y0 + kPbAhead; y < y1; y += kPbAhead) {  // uniform
+            issue(y, y1, F);
             compute(E);
+            E = F;
         }
     };
     auto neuron_step = [&](int q) {
@@ -632,6 +644,7 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
     };
 
     PbEntries E0, E1;
+    int most = kPbRecords;  // records of a step's portion loaded
     if (driven) draw(0);
     __syncthreads();  // s_x
     for (int q = 0; q < B;) {
@@ -657,9 +670,9 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
                 __syncthreads();  // histories, traces, the cleared accumulator
                 const int y0 = s_yoff[k], y1 = s_yoff[k + 1];
                 const int z1 = k + 1 < qx ? s_yoff[k + 2] : y1;
+                windows(y0, y1, E, F);
                 issue(y1, z1, F);
                 compute(E);
-                if (y1 - y0 > kPbAhead) windows(y0 + kPbAhead, y1, E);
                 draw_next(k);
                 __syncthreads();  // every atomic and weight store of step k done
                 reload(F);
@@ -671,18 +684,24 @@ __global__ __launch_bounds__(kPbBlock) void k_block_run(NeuronArgs a, BlockArgs 
             }
             q = qx;
         } else {
-            // a step that does not fit: its records in portions (halved until
-            // their entries fit the map; one record always does)
+            // a step that does not fit: its records in portions, as many as
+            // have their entries in the map (one record always does), about
+            // that many loaded for the next portion
             neuron_step(q);
             for (int j = 0; j < s_cnt[q];) {
-                int m = min(s_cnt[q] - j, kPbRecords);
+                int m = min(s_cnt[q] - j, most);
                 int total = load_records(q, q, j, m);
-                while (total > kPbMap) {  // uniform
-                    m = (m + 1) / 2;
-                    total = load_records(q, q, j, m);
-                }
                 __syncthreads();
-                windows(0, total, E0);
+                if (total > kPbMap) {  // uniform
+                    m = s_fit[0];
+                    total = s_fit[1];
+                    most = min(m + m / 8 + 1, kPbRecords);
+                } else if (total < kPbMap / 2) {
+                    most = min(2 * most, kPbRecords);
+                }
+                issue(0, total, E0);
+                windows(0, total, E0, E1);
+                compute(E0);
                 j += m;
             }
             __syncthreads();  // every atomic of step q done (and the neuron update published)
