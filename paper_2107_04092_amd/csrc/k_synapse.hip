@@ -868,7 +868,7 @@ static_assert(kDlvRounds == 2, "two staged spikes per thread");
 // histories, W traces]. Keeping the staging arrays in the dynamic region
 // lets a launch that also runs other work reuse the bytes.
 template <bool CT, typename MapT>
-__device__ __forceinline__ void deliver_lds_body(const DeliverArgs &a, int bid, int nb,
+__device__ __forceinline__ void deliver_lds_body(const DeliverArgs &a, int bid, int nb, int C,
                                                  unsigned char *dyn)
 {
     DlvSharedT<MapT> &S = *reinterpret_cast<DlvSharedT<MapT> *>(dyn);
@@ -885,21 +885,20 @@ __device__ __forceinline__ void deliver_lds_body(const DeliverArgs &a, int bid, 
     int &s_nlong = S.nlong;
     const int tid = threadIdx.x;
     const int q = (bid & 7) * (nb >> 3) + (bid >> 3);
-    if (q >= a.n_work) return;  // whole workgroup, before any barrier
+    if (q >= a.n_slices * C) return;  // whole workgroup, before any barrier
     // step t = clk->t - 1 delivers the spikes of step t - D + 1
     const int64_t t = a.clk->t - 1;
     const int slot = ring_slot(t - (a.delay - 1), a.delay);
     if (q == 0 && threadIdx.x == 0) {
         // the next neuron update reads this delivery's output: the fp32
         // input with one chunk, else the C partial sums
-        a.clk->input_forced = a.chunks == 1 ? 1 : 0;
-        a.clk->n_parts = a.chunks;
+        a.clk->input_forced = C == 1 ? 1 : 0;
+        a.clk->n_parts = C;
     }
     // (the transmitted list's count is at a fixed address: loading it does not
     // wait for the clock)
     const int32_t *list = a.ring + (int64_t)slot * a.n;
-    const int s = q / a.chunks, c = q - s * a.chunks;
-    const int C = a.chunks;
+    const int s = q / C, c = q - s * C;
     const int base = s * a.width;
     const int span = a.nacc * a.width;
     // the count first (one scalar load), then the first batch's snapshots
@@ -1123,7 +1122,7 @@ __device__ __forceinline__ void deliver_lds_body(const DeliverArgs &a, int bid, 
         add_stat(a.stats + 2 * (int64_t)bid, ev);
         add_stat(a.stats + 2 * (int64_t)bid + 1, (long long)s_written);
     }
-    if (a.chunks == 1) {
+    if (C == 1) {
         for (int x = tid; x < a.width; x += kDlvBlock) {
             const int j = base + x;
             if (j < a.n) {
@@ -1148,7 +1147,8 @@ template <bool CT>
 __global__ __launch_bounds__(kDlvBlock, 4) void k_deliver_lds(DeliverArgs a)
 {
     extern __shared__ uint4 dyn_dlv[];
-    deliver_lds_body<CT, int>(a, blockIdx.x, gridDim.x, reinterpret_cast<unsigned char *>(dyn_dlv));
+    deliver_lds_body<CT, int>(a, blockIdx.x, gridDim.x, a.chunks,
+                              reinterpret_cast<unsigned char *>(dyn_dlv));
 }
 
 // Delivery of a delay block (networks without plasticity, D >= 2): the inputs
@@ -1276,7 +1276,7 @@ __global__ __launch_bounds__(kBdBlockMax, 8) void k_deliver_block(DeliverArgs a,
     }
 }
 
-// Fused synapse pass of one step: the forced rows plasticity and slice
+// Fused synapse pass of one step: the forced rows' plasticity and slice
 // delivery (with the transmitting rows' plasticity) in one launch. A forced
 // row does not transmit at t, so the two parts touch disjoint rows, and
 // neither reads what the other writes (targets' histories, post traces and
@@ -1286,13 +1286,22 @@ __global__ __launch_bounds__(kBdBlockMax, 8) void k_deliver_block(DeliverArgs a,
 // start), so two workgroups share a CU where it is at most half the CU's;
 // four waves per SIMD bound the registers to match. With 128-step
 // histories the delivery role keeps its segment map in 16 bits.
+//
+// Where the configured workgroups per slice would leave the forced rows too
+// few (snn_create), a quiet step takes fewer of them, but a step of
+// d.busy_from spikes and more is bound by delivery and has few forced rows:
+// there d.busy_chunks deliver per slice. 100,003 neurons in 98 slices of four,
+// 3% of them firing on average: 50.3 us per step (64.5 with two in every step,
+// 55.4 in separate launches), 10% 130 (178, 133), quiet 24.0 (23.5, 33.4).
 template <bool CT, int HW>
-__global__ __launch_bounds__(kDlvBlock, 4) void k_synapse_pass(DeliverArgs d, StdpArgs s,
-                                                               int32_t nd)
+__global__ __launch_bounds__(kDlvBlock, 4) void k_synapse_pass(DeliverArgs d, StdpArgs s)
 {
     extern __shared__ uint4 dyn_pass[];
+    int chunks = d.chunks;
+    if (d.busy_chunks > chunks && *d.tx_cnt >= d.busy_from) chunks = d.busy_chunks;  // uniform
+    const int nd = (d.n_slices * chunks + 7) & ~7;
     if ((int)blockIdx.x < nd)
-        deliver_lds_body<CT, FusedMap<HW>>(d, blockIdx.x, nd,
+        deliver_lds_body<CT, FusedMap<HW>>(d, blockIdx.x, nd, chunks,
                                            reinterpret_cast<unsigned char *>(dyn_pass));
     else if (s.xcd)
         stdp_rows_xcd_body<kDlvBlock, kStdpXcdUnroll, HW>(
@@ -1807,16 +1816,18 @@ hipError_t launch_synapse_pass(hipStream_t s, const DeliverArgs &d, const StdpAr
                             (const void *)k_synapse_pass<true, 1>,
                             (const void *)k_synapse_pass<true, 2>};
     // (the XCD form needs a forced-row workgroup on every XCD)
-    if (nd % 8 != 0 || ns < 1 || (a.xcd && ns < kXcds)) return hipErrorInvalidValue;
+    const int most = (d.n_slices * std::max(d.chunks, d.busy_chunks) + 7) / 8 * 8;
+    if (nd != (d.n_slices * d.chunks + 7) / 8 * 8 || nd + ns - most < (a.xcd ? kXcds : 1))
+        return hipErrorInvalidValue;
     if (a.xcd && a.xparts != 2 && a.xparts != 4 && a.xparts != 8) return hipErrorInvalidValue;
     const hipError_t e = allow_dynamic_lds(kerns[k], (int)lds, mu, granted[k]);
     if (e != hipSuccess) return e;
     const dim3 g(nd + ns), b(kDlvBlock);
     switch (k) {
-    case 0: launch_kernel((k_synapse_pass<false, 1>), g, b, lds, s, ev, d, a, nd); break;
-    case 1: launch_kernel((k_synapse_pass<false, 2>), g, b, lds, s, ev, d, a, nd); break;
-    case 2: launch_kernel((k_synapse_pass<true, 1>), g, b, lds, s, ev, d, a, nd); break;
-    default: launch_kernel((k_synapse_pass<true, 2>), g, b, lds, s, ev, d, a, nd); break;
+    case 0: launch_kernel((k_synapse_pass<false, 1>), g, b, lds, s, ev, d, a); break;
+    case 1: launch_kernel((k_synapse_pass<false, 2>), g, b, lds, s, ev, d, a); break;
+    case 2: launch_kernel((k_synapse_pass<true, 1>), g, b, lds, s, ev, d, a); break;
+    default: launch_kernel((k_synapse_pass<true, 2>), g, b, lds, s, ev, d, a); break;
     }
     return hipGetLastError();
 }

@@ -27,6 +27,9 @@ namespace {
 constexpr int kMaxDevices = 64;
 constexpr int kFuseChunks = 8;  // most workgroups per slice that the fused pass takes by itself
 constexpr int kFuseFewer = 16;  // most configured that it replaces by fewer
+// entries per workgroup from which a step is busy (4,096 and 8,192 do not differ,
+// in quiet or in busy states)
+constexpr double kFuseBusy = 8192;
 std::mutex g_scratch_mu;
 unsigned long long *g_scratch[kMaxDevices] = {};  // device address of `scratch`, per device
 
@@ -126,6 +129,7 @@ struct snn_ctx {
     bool fuse = false;  // plastic: parts (2) and (3) of snn_step in one launch
     int32_t fuse_slots = 0;  // workgroups of the fused pass resident at once
     int32_t fuse_chunks = 1;  // workgroups per slice in the fused pass
+    int32_t fuse_busy = 1;    // ... of busy steps, if more
     long long *abatch = nullptr;  // [batch_max][nacc][n]
     // plastic blocks (BlockArgs): most steps per block (0: off), targets per
     // group and groups; the group pivots (graph buffer), the plan's lists
@@ -975,6 +979,9 @@ snn_status launch_step_synapse_pass(snn_ctx *c, KernelEvents ev)
     DeliverArgs d = deliver_args(c);
     d.chunks = c->fuse_chunks;
     d.n_work = c->n_slices * d.chunks;
+    const double seg = (double)c->n_edges / c->n * c->cfg.slice_width / c->n;  // entries
+    d.busy_chunks = c->fuse_busy;
+    d.busy_from = (int32_t)std::max(1.0, std::min(2.0e9, kFuseBusy * d.chunks / (seg + 2)));
     const int nd = (d.n_work + 7) / 8 * 8;
     const int ns = std::max(8, c->fuse_slots - nd);
     StdpArgs a = stdp_args(c, false, (int64_t)ns * (kDlvBlock / kWave));
@@ -1179,8 +1186,8 @@ snn_status snn_create(const snn_config *cfg, void *hip_stream, snn_ctx **out)
         // (30,000 neurons in 30 slices, 17 each: 26.4 us against 16.4; 16,384
         // in 32, 17 each: 29.1 against 16.5) but keeps the partial sums and
         // the three timed parts of a configuration tuned for bursts (30% of
-        // the 30,000 firing in a step: 35.9 against 41.3). Few wide slices get more than configured (up to kFuseChunks), until
-        // they fill about a fifth of the CUs: a step of 12,345 plastic
+        // the 30,000 firing in a step: 35.9 against 41.3). Few wide slices get
+        // more than configured (up to kFuseChunks), until they fill about a fifth of the CUs: a step of 12,345 plastic
         // neurons in 13 slices takes 20.2, 17.5, 16.5 and 16.7 us with one,
         // two, four and eight per slice, in 7 slices 26.6, 20.7, 17.8 and
         // 16.9; 60,000 in 30 slices 27.7, 22.0 and 23.5 with one, two and
@@ -1194,6 +1201,11 @@ snn_status snn_create(const snn_config *cfg, void *hip_stream, snn_ctx **out)
                c->fuse_slots - items(c->fuse_chunks + 1) >= c->n_cu / 2)
             c->fuse_chunks += 1;
         c->fuse = per_cu >= 1 && c->fuse_slots - items(c->fuse_chunks) >= c->n_cu / 2;
+        // busy steps: up to the configured number, a quarter slot per CU left
+        c->fuse_busy = c->fuse_chunks;
+        while (c->fuse_busy < c->chunks &&
+               c->fuse_slots - items(c->fuse_busy + 1) >= c->n_cu / 4)
+            c->fuse_busy += 1;
         // the forced-row workgroups of the pass keep a statistics slot each
         if (c->fuse && c->syn_slots < c->fuse_slots) c->syn_slots = c->fuse_slots;
     }

@@ -232,6 +232,8 @@ struct DeliverArgs {
     int64_t part_stride;
     int32_t n, n_exc, width, n_slices, chunks, nacc, n_work, hw;
     const uint16_t *col16;   // compressed targets: slice-local indices (nullptr: read `col`)
+    int32_t busy_chunks, busy_from;  // fused pass: workgroups per slice of steps from so many
+                                     // spikes on (busy_chunks <= chunks: as in every step)
     int64_t *stats;          // [gridDim.x][2]: events delivered, weights written
     int32_t delay;
     // delay block (k_deliver_block): the inputs of its steps; n_work counts

@@ -61,3 +61,25 @@ def test_more_workgroups_per_slice(name, case):
             b.deliver_spikes(LDS)
             b.advance()
         same_state(a, b, "%d steps" % k)
+
+
+@pytest.mark.parametrize("cfg", [
+    dict(), dict(history_bits=128, compressed_targets=0), dict(stdp_xcd=2),
+], ids=str)
+@pytest.mark.parametrize("chunks", [3, 4])
+def test_busy_steps_take_more_workgroups_per_slice(chunks, cfg):
+    """Steps on both sides of the number of spikes (1,470 with 9.1 entries per row
+    and slice) from which the configured workgroups per slice deliver."""
+    n = 64 * 110 - 13
+    log("fused pass: busy steps, %d workgroups per slice, %s" % (chunks, cfg))
+    p = wl.preset("stress", n=n, p_or_fanout=1000, p_fire=0.21, delay=1)
+    a = gpu_net(p, slice_width=64, spike_chunks=chunks, plastic_blocks=-1, **cfg)
+    b = gpu_net(p, slice_width=64, spike_chunks=chunks, plastic_blocks=-1, **cfg)
+    for k in (1, 20, 9):
+        a.step(k, LDS)
+        for _ in range(k):
+            b.update_neurons()
+            b.update_plasticity()
+            b.deliver_spikes(LDS)
+            b.advance()
+        same_state(a, b, "%d steps" % k)
