@@ -1238,8 +1238,22 @@ snn_status snn_create(const snn_config *cfg, void *hip_stream, snn_ctx **out)
         const int per_cu = std::min<int>(2, (int)(lds_max / (int64_t)(c->sb_lds + rstat)));
         c->sb_slots = c->n_cu * per_cu;
         c->sb_chunks = std::max(1, std::min(c->sb_slots / 2 / c->n_slices, kSrcMaxChunks));
+        // Where nearly every row transmits within its window, so that few are
+        // forced (per step n / window of those that have not fired in it), and
+        // half of the slots in whole chunks leaves CUs without a delivery
+        // workgroup, it takes seven eighths: 100,000 sources in 98 slices, 5%
+        // firing: two per slice 83 us per step, four 61 (30%: 442, 336; one
+        // launch per step 101 and 342). Not where the half is about one per
+        // CU: 250,000 in 123 slices, 30%: two 283, three 385.
+        const double rows = (double)c->n_plastic_rows, window = 64.0 * c->hw;
+        const bool few = rows / window * std::pow(1.0 - cfg->p_fire, window) <
+                             cfg->p_fire * rows / 64 &&
+                         (int64_t)c->n_slices * c->sb_chunks < c->n_cu * 7 / 8;
+        if (few)
+            c->sb_chunks =
+                std::max(1, std::min(c->sb_slots * 7 / 8 / c->n_slices, kSrcMaxChunks));
         c->sb_nd = (c->n_slices * c->sb_chunks + 7) / 8 * 8;
-        if (per_cu >= 1 && c->sb_slots - c->sb_nd >= c->n_cu / 2) {
+        if (per_cu >= 1 && c->sb_slots - c->sb_nd >= c->n_cu / (few ? 4 : 2)) {
             c->sb_max = cfg->plastic_blocks > 0
                             ? std::min<int32_t>(cfg->plastic_blocks, kSrcMaxSteps)
                             : kSrcMaxSteps;

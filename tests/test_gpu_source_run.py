@@ -32,6 +32,9 @@ CASES = [
      dict(plastic_blocks=2, history_bits=128)),
     (dict(n=100003, p_or_fanout=20, p_fire=0.005), 2048, 2, dict(stdp_filter=3)),
     (dict(n=5000, p_or_fanout=100, p_fire=0.02), 512, 1, dict(plasticity_algorithm=1)),
+    # hardly any row is forced: seven eighths of the slots deliver
+    (dict(n=6251, p_or_fanout=200, p_fire=0.1), 64, 4, dict()),
+    (dict(n=6251, p_or_fanout=200, p_fire=0.1), 64, 1, dict(history_bits=128)),
 ]
 
 
