@@ -1639,10 +1639,13 @@ snn_status snn_step(snn_ctx *c, int32_t n_steps, int32_t mode)
         b.gw = c->one_gw;
         b.mult = c->one_gw / c->cfg.slice_width;
         b.n_slices = c->n_slices;
-        // lanes per row, 4 to 64: two entries each on average
+        // lanes per row: its entries per workgroup on average, 4 to 64, so that
+        // hardly a row of a quiet step takes a second round trip (two entries
+        // per lane: 20,011 sparse neurons 5.3 -> 6.0 us; 30% of 62,500 firing,
+        // 88.8 -> 84.4)
         const double seg = (double)c->n_edges / c->n * c->one_gw / c->n;
         b.lg_team = 2;
-        while (b.lg_team < 6 && (2 << b.lg_team) < seg) ++b.lg_team;
+        while (b.lg_team < 6 && (1 << b.lg_team) < seg) ++b.lg_team;
         b.parts = c->one_parts;
         b.per_part = std::max(1, (int)(kOnePart / (seg + kOneRow)));
         b.arrived = c->one_arrived;
