@@ -114,7 +114,14 @@ typedef struct snn_config {
                              device's LDS (160 KiB); SNN_EINVAL otherwise */
     int32_t spike_chunks; /* C in 1..64: workgroups that share one slice, each
                              taking 1/C of the spike list (partial sums are
-                             added by the next neuron update) */
+                             added by the next neuron update), in the part
+                             call snn_deliver_spikes and in steps that run it
+                             as a launch of its own. Where snn_step runs a
+                             step otherwise it chooses: the fused pass of
+                             parts (2) and (3) takes fewer or more where C
+                             would leave the forced rows or the device too
+                             few, the one-launch steps up to C, the blocks
+                             their own number. No result depends on it */
     int32_t stdp_slice_mult; /* STDP target groups span stdp_slice_mult * W
                              neurons (0 = about 4096); their history words and
                              post traces (12 B each) are staged in LDS */
@@ -175,10 +182,11 @@ typedef struct snn_config {
                              Bernoulli sources with D = 1 whose step fuses
                              parts (2) and (3): snn_step runs the neuron
                              updates of up to 16 steps in one launch, then
-                             each step's synapse pass (see snn_step). 0 =
-                             on; k > 0 = on, at most k steps per block; -1
-                             = off (the parts step by step). Same results
-                             either way */
+                             their synapse part in another (see snn_step;
+                             a call of one step runs as a step). 0 = on;
+                             k > 0 = on, at most k steps per block; -1 = off
+                             (the parts step by step). Same results either
+                             way */
     int32_t plastic_block_width; /* targets per group of those blocks: 64, 128
                              or 256, dividing slice_width; 0 = automatic */
     int32_t neuron_model; /* enum snn_neuron_model */
@@ -300,10 +308,10 @@ void snn_destroy(snn_ctx *ctx);
 const char *snn_last_error(const snn_ctx *ctx);
 
 /* Bytes of device workspace for neuron state, spike lists, the delay ring,
- * row pointers and statistics, and the per-step lists, snapshots and
- * histories of the blocks snn_step runs (plastic_blocks; for source blocks
- * about 93 bytes per neuron and step of a block besides its last: 350 MB
- * for 250,000 neurons). Depends only on the configuration. */
+ * row pointers and statistics, and the lists and snapshots of the blocks
+ * snn_step runs (plastic_blocks; for source blocks 32 bytes per neuron and
+ * step of a block besides its last: 120 MB for 250,000 neurons). Depends on
+ * the configuration and on the device's number of CUs. */
 snn_status snn_workspace_size(const snn_ctx *ctx, size_t *bytes);
 
 /* Binds a device buffer of at least snn_workspace_size bytes (256-byte
@@ -381,7 +389,9 @@ snn_status snn_advance(snn_ctx *ctx);
  * D >= 2 the inputs of up to D-1 steps (at most 16; 8 for CUBA) come from
  * spikes already in the delay ring, so one delivery launch computes them
  * all before one neuron launch runs those steps (Sec. I: the input of step
- * t depends on the spikes of step t-D only). Plastic networks with D >= 2
+ * t depends on the spikes of step t-D only); with D = 1, up to 65536 neurons
+ * and slices of up to 4096, each launch delivers one step's spikes and
+ * updates the neurons of the next (n_steps + 1 launches). Plastic networks with D >= 2
  * and n <= 65536 (lazy plasticity, snn_config.plastic_blocks) run in blocks
  * of up to D-1 steps (at most 15): the weight a row delivers at t depends
  * only on spikes of its targets and on pre spikes that arrived by t (Sec.
@@ -392,16 +402,16 @@ snn_status snn_advance(snn_ctx *ctx);
  * update, and the plasticity and delivery of every listed row's synapses
  * onto them; a forced update that is its row's last of the block delivers
  * nothing and is computed after the block's last step, from the targets'
- * histories at its step); a last launch per call rebuilds the per-step
- * lists. Plastic networks of Bernoulli sources with D = 1 (lazy plasticity,
+ * histories at its step); the last block's deferred updates share their
+ * launch with the per-step lists as single steps leave them. Plastic networks of Bernoulli sources with D = 1 (lazy plasticity,
  * snn_config.plastic_blocks, the fused pass below on whole forced rows) run
  * the neuron part of up to 16 steps in one launch: a source fires on a
  * counter-based draw that no input changes, so the spikes, histories and
  * the rows each step brings up to date (with the t_last and pre trace each
  * update leaves for the next) are known before any of those steps' synapse
- * passes; the launch writes, for each step, the lists, snapshots and
- * histories its pass reads, and the passes then run one per step, in order.
- * Other
+ * passes; the launch writes their lists and snapshots, and one more launch
+ * runs the synapse part of all of the block's steps, each of its delivery
+ * workgroups owning a slice and a chunk of the rows through the block. Other
  * plastic networks run parts (2) and (3) in one launch where its LDS
  * leaves the forced rows at least half a workgroup slot per CU beside the
  * delivery work items: the forced rows and the transmitting rows of a step

@@ -1788,7 +1788,8 @@ hipError_t launch_deliver_block(hipStream_t s, const DeliverArgs &a, int64_t n_e
     const int blocks = (a.n_work + 7) / 8 * 8;
     const int lds = kBdRows * 14 + a.nacc * a.width * (int)sizeof(long long);
     const double seg = (double)n_edges / a.n * a.width / a.n;
-    // few items (wide slices): twice the waves each
+    // few items (wide slices, or few steps): at most one workgroup per CU and a
+    // little over, so each has twice the waves
     const int nt = a.n_work <= 512 ? kBdBlockMax : kDlvBlock;
     return a.col16 ? launch_deliver_block_ct<true>(s, a, seg, nt, blocks, lds)
                    : launch_deliver_block_ct<false>(s, a, seg, nt, blocks, lds);

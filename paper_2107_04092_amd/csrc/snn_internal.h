@@ -550,6 +550,9 @@ constexpr int kSrcMaxSteps = kBatchMax;  // steps per source block (one scan per
 
 // The synapse part of a source block (k_source_run): delivery of work items
 // (slice, chunk) on workgroups [0, nd), the listed forced rows on the others.
+// 704 records of 16 B and a map of 5,632 entries beside a slice of 2,048 targets
+// with 128-step histories are 80,384 of the 81,920 B that let two workgroups
+// share a CU (each role's time is latency: 16 waves per CU instead of 8).
 constexpr int kSrcRecs = 704;   // rows staged at once
 constexpr int kSrcU = 11;       // entries per thread and window
 constexpr int kSrcMaxW = 4096;  // targets per slice of the form for most networks
